@@ -1,0 +1,76 @@
+"""GPU parity of the batch paths at the sizes where they change: claims that
+crowd into few buckets, export by trips, dedupe and resize forms.
+
+Everything is exact: outputs, key counts and contents equal the dictionary
+oracle's.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2510_15095_amd import workload as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def case(msg):
+    print(f"[case] {msg}", flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def H():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2510_15095_amd import hive
+    return hive
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def host(t):
+    return t.cpu().numpy()
+
+
+def make(H, S, nb, set32=False, **cfg):
+    if set32:
+        return H.Table(nb, slots_per_bucket=32, entry_bits=32, **cfg)
+    return H.Table(nb, slots_per_bucket=S, **cfg)
+
+
+def values(keys, set32):
+    return np.zeros(keys.size, np.uint32) if set32 else wl.values_for(keys)
+
+
+@pytest.mark.parametrize("S,set32", [(16, False), (32, False), (64, False), (32, True)])
+@pytest.mark.parametrize("nb,over", [(1, 0), (1, 7), (3, 0), (64, 0), (64, 100)])
+def test_claims_crowd_into_full_buckets(H, S, set32, nb, over):
+    """One batch fills every slot of the table (and `over` entries go to the
+    stash): its claims of one bucket all run side by side, each from a slot of
+    its own, and together take every slot."""
+    case(f"crowded claims S={S} set32={set32} nb={nb} over={over}")
+    n = nb * S + over
+    ks = wl.KeyStream(501 + nb)
+    keys = ks.range(0, n)
+    t, o = make(H, S, nb, set32, stash_capacity=4096, pending_capacity=4096), oracle.O1()
+    for part in (keys[: n // 2], keys[n // 2:]):
+        t.insert(dev(part), dev(values(part, set32)), flags=H.HIVE_UNIQUE)
+        o.insert(part, values(part, set32))
+    st = t.stats()
+    assert st["status"] == H.HIVE_OK and st["live"] == n
+    words, where = t.dump(with_where=True)
+    assert np.array_equal(words, o.dump())
+    assert np.bincount(where[where >= 0], minlength=nb).max() <= S
+    q = ks.range(0, 2 * n)
+    v, f = t.lookup(dev(q))
+    ov, of = o.lookup(q)
+    assert np.array_equal(host(f), of)
+    if not set32:
+        assert np.array_equal(host(v), ov)
+    t.close()
