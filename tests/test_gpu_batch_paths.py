@@ -74,3 +74,32 @@ def test_claims_crowd_into_full_buckets(H, S, set32, nb, over):
     if not set32:
         assert np.array_equal(host(v), ov)
     t.close()
+
+
+@pytest.mark.parametrize("S,set32", [(16, False), (64, False), (32, True)])
+@pytest.mark.parametrize("slots,extra", [(64, 0), (64, 9), (16384, 0), (16384 + 64, 3), (70_400, 300)])
+def test_dump_by_trips(H, S, set32, slots, extra):
+    """Export of tables of less than a trip of 16,384 words, exactly one, a
+    little more and several, with entries in the stash and the pending list,
+    with and without places, and into a buffer that is too small (the count
+    is whole, the words that fit are entries of the table)."""
+    import torch
+    nb = slots // S
+    n = nb * S * 3 // 4 + extra
+    case(f"dump S={S} set32={set32} buckets={nb} entries={n}")
+    ks = wl.KeyStream(777 + slots)
+    keys = ks.range(0, n)
+    t, o = make(H, S, nb, set32, max_evictions=0, stash_capacity=16, pending_capacity=8192), oracle.O1()
+    t.insert(dev(keys), dev(values(keys, set32)), flags=H.HIVE_UNIQUE)
+    o.insert(keys, values(keys, set32))
+    gone = keys[::5]
+    t.delete(dev(gone), flags=H.HIVE_UNIQUE)
+    o.delete(gone)
+    words, where = t.dump(with_where=True)
+    assert np.array_equal(words, o.dump())
+    assert where.min() >= -2 and where.max() < nb
+    small = torch.zeros(len(o) // 2, dtype=torch.uint64, device="cuda")
+    assert H.hive_dump(t.h, small) == len(o)
+    got = host(small)
+    assert np.unique(got).size == got.size and np.isin(got, words).all()
+    t.close()
