@@ -291,113 +291,284 @@ __device__ __forceinline__ void dedupe_thread(uint64_t *dd, uint64_t mask, uint3
 }
 
 // ---------------------------------------------------------------------------
-// Dedupe of plain launches by hash partitions, with no global atomics.
+// Dedupe of batches of up to DDS_MAX operations in one launch.
+//
+// Block p owns the keys of hash range p, reads the whole batch's keys (they
+// stay in the L2: tens of KB read by every block, coalesced), keeps its own
+// operations as records in LDS, collapses them in an LDS table (largest index
+// of an insert, smallest of a delete) and writes the flags of its operations:
+// no staging, no atomics outside LDS.  Bound by the launch and a few dependent
+// round trips: 7 us at 64 operations, 11 us at 2^14.  Every block reads every
+// key, so the time grows with blocks x keys: at 2^15 operations the two
+// launches of ddr_chunk_kernel and ddr_resolve_kernel take about as long (19
+// us), at 2^16 they are ahead (18 us against 23, and 55 on Zipf(0.99) keys).
+// Five launches (collect, two of prefix sums, scatter, resolve) took 35 us
+// from 2^12 operations on and 46 us at 2^14.
+//
+// A block whose range holds more distinct keys than its table takes splits
+// the range: it works through sub-ranges, halving the width whenever one
+// overflows and doubling it after one that fits.  The hash is a bijection of
+// the 32-bit keys, so a sub-range of at most DDS_CAP values always fits and
+// the loop ends.  Operations beyond the record list (a hot key's) go to the
+// table directly, and the flags then take a second reading of the keys.
+// ---------------------------------------------------------------------------
+constexpr int DDS_BLOCK = 1024;
+constexpr uint64_t DDS_MAX = 1ull << 14;
+constexpr uint32_t DDS_PER = 512;     // operations per range aimed at
+constexpr int DDS_TAB = 4096;         // table entries (32 KiB)
+constexpr uint32_t DDS_CAP = DDS_TAB * 5 / 8;
+constexpr int DDS_LIST = 8192;        // records held (64 KiB)
+constexpr int DDS_LOADS = 8;          // keys in flight per thread
+static_assert(DDS_MAX < (1ull << 31), "an index shares a word with the type bit");
+static_assert(DDS_CAP + DDS_BLOCK < DDS_TAB, "one claim per thread past the limit still leaves EMPTY words");
+
+struct DdsArgs {
+  const uint8_t *ops;
+  const uint32_t *keys;
+  uint8_t *win;
+  uint32_t n, mode, bits;  // 2^bits ranges
+};
+
+// Range hash (a bijection: odd factor) of a key.
+__device__ __forceinline__ uint32_t dds_hash(uint32_t k) { return k * 0x9E3779B1u; }
+
+__device__ __forceinline__ uint32_t dds_range(uint32_t k, uint32_t bits) {
+  return bits ? dds_hash(k) >> (32 - bits) : 0u;
+}
+
+// Record e (key << 32 | type << 31 | index) into the table.
+__device__ __forceinline__ void dds_settle(uint64_t *tab, uint64_t e, bool keep_last, uint32_t *claims) {
+  const uint32_t k = (uint32_t)(e >> 32);
+  for (uint32_t s = mix32(k) & (DDS_TAB - 1);; s = (s + 1) & (DDS_TAB - 1)) {
+    uint64_t cur = *(volatile uint64_t *)&tab[s];
+    if (cur == EMPTY) {
+      cur = atomicCAS((unsigned long long *)&tab[s], (unsigned long long)EMPTY, (unsigned long long)e);
+      if (cur == EMPTY) {
+        atomicAdd(claims, 1u);
+        return;
+      }
+    }
+    if ((uint32_t)(cur >> 32) == k) {
+      // only an update that can change the word (a hot
+      // key's later occurrences mostly lose, and atomics on one word serialize)
+      if (keep_last) {
+        if (cur < e) atomicMax((unsigned long long *)&tab[s], (unsigned long long)e);
+      } else if (cur > e) {
+        atomicMin((unsigned long long *)&tab[s], (unsigned long long)e);
+      }
+      return;
+    }
+  }
+}
+
+// Whether record e is the one its key's table word kept.
+__device__ __forceinline__ bool dds_kept(const uint64_t *tab, uint64_t e) {
+  const uint32_t k = (uint32_t)(e >> 32);
+  uint32_t s = mix32(k) & (DDS_TAB - 1);
+  while ((uint32_t)(tab[s] >> 32) != k) s = (s + 1) & (DDS_TAB - 1);
+  return tab[s] == e;
+}
+
+// Operations base + j * DDS_BLOCK + thread of the batch as records, EMPTY
+// where there is none to record or its key is outside [lo, lo + width).
+__device__ __forceinline__ void dds_read(const DdsArgs &d, uint32_t base, uint32_t lo, uint64_t width, uint64_t *e) {
+  uint32_t k[DDS_LOADS], o[DDS_LOADS];
+#pragma unroll
+  for (int j = 0; j < DDS_LOADS; ++j) {
+    const uint32_t i = base + j * DDS_BLOCK + threadIdx.x;
+    k[j] = i < d.n ? d.keys[i] : 0u;
+    o[j] = (d.mode == OP_MIXED && i < d.n) ? d.ops[i] : d.mode;
+  }
+#pragma unroll
+  for (int j = 0; j < DDS_LOADS; ++j) {
+    const uint32_t i = base + j * DDS_BLOCK + threadIdx.x;
+    // a mixed batch's deletes carry the type bit: the key sets of the types are
+    // disjoint by contract, so one table takes both
+    const uint32_t ty = (d.mode == OP_MIXED && o[j] == OP_DELETE) ? 1u : 0u;
+    const bool rec = (o[j] == OP_INSERT || o[j] == OP_DELETE) && valid_key(k[j]) &&
+                     (uint64_t)(dds_hash(k[j]) - lo) < width;
+    e[j] = rec ? ((uint64_t)k[j] << 32) | (ty << 31) | i : EMPTY;
+  }
+}
+
+__global__ __launch_bounds__(DDS_BLOCK) void dds_kernel(DdsArgs d) {
+  __shared__ uint64_t tab[DDS_TAB];
+  __shared__ uint64_t list[DDS_LIST];
+  __shared__ uint32_t s_count, s_claims;
+  const int lane = threadIdx.x & 63;
+  // inserts keep the last occurrence (type 0 of a mixed batch), deletes the first
+  const auto keep_last = [&](uint64_t e) { return d.mode == OP_MIXED ? ((uint32_t)e >> 31) == 0 : d.mode == OP_INSERT; };
+  const uint64_t whole = 1ull << (32 - d.bits), first = (uint64_t)blockIdx.x * whole, last = first + whole;
+  uint64_t lo = first, width = whole;
+  while (lo < last) {
+    width = min(width, last - lo);
+    for (int j = threadIdx.x; j < DDS_TAB; j += DDS_BLOCK) tab[j] = EMPTY;
+    if (threadIdx.x == 0) s_count = s_claims = 0;
+    __syncthreads();
+    for (uint32_t base = 0; base < d.n; base += DDS_LOADS * DDS_BLOCK) {
+      uint64_t e[DDS_LOADS], m[DDS_LOADS];
+      dds_read(d, base, (uint32_t)lo, width, e);
+      uint32_t c = 0;
+#pragma unroll
+      for (int j = 0; j < DDS_LOADS; ++j) {
+        m[j] = ballot(e[j] != EMPTY);
+        c += (uint32_t)__popcll(m[j]);
+      }
+      if (c == 0) continue;
+      uint32_t at = 0;
+      if (lane == 0) at = atomicAdd(&s_count, c);
+      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+      for (int j = 0; j < DDS_LOADS; ++j) {
+        if (e[j] != EMPTY) {
+          const uint32_t pos = at + rank_below(m[j]);
+          if (pos < DDS_LIST)
+            list[pos] = e[j];
+          else if (*(volatile uint32_t *)&s_claims <= DDS_CAP)
+            dds_settle(tab, e[j], keep_last(e[j]), &s_claims);
+        }
+        at += (uint32_t)__popcll(m[j]);
+      }
+    }
+    __syncthreads();
+    const uint32_t held = min(s_count, (uint32_t)DDS_LIST);
+    const bool spilled = s_count > DDS_LIST;
+    for (uint32_t t = threadIdx.x; t < held; t += DDS_BLOCK)
+      if (*(volatile uint32_t *)&s_claims <= DDS_CAP) dds_settle(tab, list[t], keep_last(list[t]), &s_claims);
+    __syncthreads();
+    const uint32_t claims = s_claims;
+    const bool over = claims > DDS_CAP;  // the same in the whole block
+    if (!over) {
+      for (uint32_t t = threadIdx.x; t < held; t += DDS_BLOCK) {
+        const uint64_t e = list[t];
+        d.win[(uint32_t)e & 0x7FFFFFFFu] = dds_kept(tab, e);
+      }
+      if (spilled) {
+        for (uint32_t base = 0; base < d.n; base += DDS_LOADS * DDS_BLOCK) {
+          uint64_t e[DDS_LOADS];
+          dds_read(d, base, (uint32_t)lo, width, e);
+#pragma unroll
+          for (int j = 0; j < DDS_LOADS; ++j)
+            if (e[j] != EMPTY) d.win[(uint32_t)e[j] & 0x7FFFFFFFu] = dds_kept(tab, e[j]);
+        }
+      }
+    }
+    __syncthreads();  // the table, the list and the counts are free
+    if (over) {
+      width = (width + 1) / 2;
+    } else {
+      lo += width;
+      if (claims <= DDS_CAP / 2) width *= 2;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Dedupe of larger batches in two launches, with no global atomics.
 //
 // Device-scope atomics on random words run at about 26 G/s on this GPU
 // however many are in flight (measured: 3.1 M CAS into a 64 MiB set take
 // 119 us at one or at eight per thread), so a set in HBM costs at least one
-// such atomic per distinct key of a chunk.  Instead, records
-// (key << 32 | index) are partitioned by the top DDP_BITS bits of mix32(key),
-// per operation type, and each partition is deduplicated in LDS:
-//   1. collect, per chunk of DD_CHUNK operations and type: the chunk's
-//      repeats collapse in an LDS table (a Zipf(0.99) hot key is about 5% of
-//      the operations), its distinct records go to its staging area with a
-//      histogram over the partitions, and the flags of the type's operations
-//      are written: 1 for the chunk's winners, 0 for the rest;
-//   2. segment sums: the histograms summed over segments of DDP_SEG chunks;
-//   3. scan: per partition, exclusive prefixes over the segments and the
-//      partition's total;
-//   4. scatter: per segment, each record to its partition's run of `rec`;
-//   5. resolve: per partition, an LDS table keeps per key the largest insert
-//      index (the last occurrence wins) or the smallest delete index (the
-//      first reports the deletion), and clears the flags of the records that
-//      lose to another chunk's (random one-byte stores run at about 77 G/s:
-//      one per distinct key took 30 us of a 2^22-operation batch).  A partition
-//      with more distinct keys than the table takes falls back to a table of
-//      its own in HBM (twice its records, in the staging area), by atomics.
-// P1 then reads one flag byte per operation, coalesced, instead of looking
-// the key up in a set.
+// such atomic per distinct key of a chunk.  Instead:
+//   1. chunk: a block collapses the repeats of its chunk in an LDS table (a
+//      Zipf(0.99) hot key is about 5% of the operations), sorts the distinct
+//      records by hash range in LDS (a counting sort) and writes them, range
+//      after range, with the ranges' bounds; the flags of its operations
+//      become 1 for the chunk's winners and 0 for the rest;
+//   2. resolve: a block per range reads the range's run of every chunk and
+//      settles the records in an LDS table.  Whichever of two records of one
+//      key loses is known when they meet, and its flag is cleared then, so
+//      there is no second pass over the records.
+// P1 then reads one flag byte per operation, coalesced.  The records are
+// written once and read once, in runs.  (Staging them by chunk, prefix sums
+// over chunks in two launches and a scatter to whole partitions before a
+// resolve of two passes took five launches, and partitions of more distinct
+// keys than their tables a set in HBM.)  Time at 2^16, 2^18 and 2^20 inserts
+// of 2^20 keys: 18, 21 and 35 us (five launches: 46, 51 and 65 us); at 2^22,
+// 2^24 and 2^26 distinct keys: 110, 445 and 2,470 us (483, 1,738 and 7,865);
+// a 2^22 Zipf(0.99) mixed batch 62 us (84).  Slower than before is only a
+// batch of 2^24 operations and more in which every key repeats 16 times and
+// more (2^24 of 2^20 keys: 517 us against 477).  Bound by LDS atomics
+// and the latency between the phases of a block.
+//
+// Inserts and deletes of a mixed batch share the ranges; bit 31 of a record
+// is the type, so a mixed batch of 2^31 operations and more runs once per
+// type (`only`).  A range with more distinct keys than the table takes is
+// worked through in sub-ranges, as in dds_kernel; beyond 2^25 operations that
+// is the ordinary course, and the first width is picked from the range's
+// record count.  Runs get short with many ranges (two records at 2^25), but
+// the runs of neighbouring ranges share cache lines, and the neighbours run
+// on one XCD at about the same time.
 // ---------------------------------------------------------------------------
-constexpr int DD_PER_THREAD = 8;
-constexpr uint64_t DD_CHUNK = (uint64_t)BLOCK * DD_PER_THREAD;
-constexpr int DD_LDS = 2 * (int)DD_CHUNK;
-constexpr int DDP_BITS = 9;
-constexpr int DDP_BINS = 1 << DDP_BITS;  // partitions per operation type
-constexpr uint64_t DDP_SEG = 8;          // chunks per segment
-constexpr int DDP_SCATTER_LOADS = 8;     // staged records per thread in flight (scatter)
-constexpr int DDP_RESOLVE_LOADS = 8;     // records per thread in flight (resolve)
-constexpr int DDP_TAB = 8192;            // entries of a resolve table (64 KiB)
-constexpr uint32_t DDP_CAP = DDP_TAB * 3 / 4;
-static_assert(DDP_BINS % 64 == 0 && DDP_BINS <= BLOCK * 2, "partition counts per block");
+constexpr int DDR_BLOCK = 1024;
+constexpr int DDR_BINS = 512;       // most hash ranges of batches of up to DDR_MORE operations
+constexpr int DDR_BINS_BIG = 4096;  // and beyond
+constexpr uint64_t DDR_MORE = 1ull << 22;
 
-__device__ __forceinline__ uint32_t ddp_bin(uint32_t k) { return mix32(k) >> (32 - DDP_BITS); }
-
-struct DdpArgs {
+struct DdrArgs {
   const uint8_t *ops;
   const uint32_t *keys;
-  uint64_t n, nch, nseg;
-  uint32_t mode, nt;  // nt: operation types recorded (2 for mixed batches)
-  uint64_t *stage;    // max(nt, 2) * nch * DD_CHUNK words: staged records, then fallback tables
-  uint64_t *rec;      // n words, partition by partition
-  uint8_t *win;       // nch * DD_CHUNK flags, one per operation
-  uint16_t *hist;     // nt * nch * DDP_BINS
-  uint32_t *cnt;      // nt * nch: staged records per chunk
-  uint32_t *seg;      // nt * nseg * DDP_BINS: segment sums, then exclusive prefixes over segments
-  uint32_t *tot;      // nt * DDP_BINS: records per partition
+  uint8_t *win;
+  uint64_t *rec;     // chunk c's records from c * chunk on, sorted by range
+  uint32_t *bounds;  // [chunk][range]: first record of the range's run | its end << 16
+  uint32_t n, mode, bits, nch;  // 2^bits ranges, nch chunks
+  uint32_t only;                // OP_NONE, or the one type of a mixed batch to record
 };
 
-// Operation type ti of a batch (0 and 1: inserts and deletes of a mixed one).
-__device__ __forceinline__ uint32_t ddp_op(const DdpArgs &d, uint32_t ti) {
-  return d.mode == OP_MIXED ? (ti == 0 ? OP_INSERT : OP_DELETE) : d.mode;
+// Whether index words carry the type in bit 31, and the mask of their index.
+__device__ __forceinline__ bool ddr_typed(const DdrArgs &d) { return d.mode == OP_MIXED && d.only == OP_NONE; }
+__device__ __forceinline__ uint32_t ddr_index(const DdrArgs &d, uint64_t e) {
+  return (uint32_t)e & (ddr_typed(d) ? 0x7FFFFFFFu : ~0u);
+}
+// The last occurrence of an insert wins, the first of a delete.
+__device__ __forceinline__ bool ddr_keep_last(const DdrArgs &d, uint64_t e) {
+  return ddr_typed(d) ? ((uint32_t)e >> 31) == 0 : (d.only == OP_NONE ? d.mode : d.only) == OP_INSERT;
 }
 
-// Step 1.  Block c: chunk c, every recorded operation type at once (a mixed
-// batch's inserts and deletes share the block's loads and table: their keys
-// are disjoint by contract, so one table collapses both).  A table entry
-// holds the key, the operation's type in bit 31 and its index within the
-// chunk: a key's entries share one type, so the per-type rule (inserts keep
-// the last occurrence, deletes the first) compares their indices alone.
-__global__ __launch_bounds__(BLOCK) void ddp_collect_kernel(DdpArgs d) {
-  __shared__ uint64_t tab[DD_LDS];
-  const uint64_t c = blockIdx.x;
-  const uint64_t base = c * DD_CHUNK;
-  static_assert(DD_CHUNK <= (1ull << 31), "chunk indices share a word with the type bit");
-  // the chunk's operands first, all loads in flight together; ty: the
-  // operation's type (0 or 1), or -1 when it is not recorded
-  uint32_t kk[DD_PER_THREAD];
-  int ty[DD_PER_THREAD];
+template <int PER, int BINS>
+__global__ __launch_bounds__(DDR_BLOCK) void ddr_chunk_kernel(DdrArgs d) {
+  constexpr int Q = BINS > DDR_BLOCK ? BINS / DDR_BLOCK : 1;  // ranges per thread of the prefix sums
+  constexpr int SCAN = BINS / Q;                              // threads that take part
+  constexpr uint32_t CH = (uint32_t)DDR_BLOCK * PER, TAB = 2 * CH;
+  static_assert(CH < 65536, "run bounds are 16 bits");
+  __shared__ uint64_t tab[TAB];
+  __shared__ uint32_t cnt[BINS], part[SCAN / 64];
+  const uint64_t base = (uint64_t)blockIdx.x * CH;
+  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+  const uint32_t nb = 1u << d.bits;
+  uint32_t kk[PER];
+  int ty[PER];  // 0, or 1 for a mixed batch's deletes; -1: not recorded
 #pragma unroll
-  for (int j = 0; j < DD_PER_THREAD; ++j) {
-    const uint64_t i = base + (uint64_t)j * BLOCK + threadIdx.x;
+  for (int j = 0; j < PER; ++j) {
+    const uint64_t i = base + j * DDR_BLOCK + tid;
     ty[j] = -1;
+    kk[j] = 0;
     if (i < d.n) {
-      if (d.mode != OP_MIXED) ty[j] = 0;
-      else {
-        const uint8_t o = d.ops[i];
-        ty[j] = o == OP_INSERT ? 0 : (o == OP_DELETE ? 1 : -1);
+      kk[j] = d.keys[i];
+      if (d.mode != OP_MIXED) {
+        ty[j] = 0;
+      } else {
+        const uint32_t o = d.ops[i];
+        if (d.only != OP_NONE) ty[j] = o == d.only ? 0 : -1;
+        else ty[j] = o == OP_INSERT ? 0 : (o == OP_DELETE ? 1 : -1);
       }
     }
-    kk[j] = i < d.n ? d.keys[i] : 0u;
   }
-  // the flags of recorded operations start cleared; the chunk's winners set
-  // theirs below (after barriers of this block), and the resolve step clears
-  // those that lose to another chunk
 #pragma unroll
-  for (int j = 0; j < DD_PER_THREAD; ++j)
-    if (ty[j] >= 0) d.win[base + (uint64_t)j * BLOCK + threadIdx.x] = 0;
-  for (int j = threadIdx.x; j < DD_LDS; j += BLOCK) tab[j] = EMPTY;
+  for (int j = 0; j < PER; ++j)
+    if (ty[j] >= 0) d.win[base + j * DDR_BLOCK + tid] = 0;
+  for (uint32_t j = tid; j < TAB; j += DDR_BLOCK) tab[j] = EMPTY;
+  for (int j = tid; j < BINS; j += DDR_BLOCK) cnt[j] = 0;
   __syncthreads();
-  // slot[j]: the table slot whose key operation j's thread claimed (the
-  // key's first record in this chunk), DD_LDS when it claimed none
-  uint32_t slot[DD_PER_THREAD];
+  uint32_t slot[PER];  // the table slot this operation claimed, TAB when none
 #pragma unroll
-  for (int j = 0; j < DD_PER_THREAD; ++j) {
-    slot[j] = DD_LDS;
+  for (int j = 0; j < PER; ++j) {
+    slot[j] = TAB;
     const uint32_t k = kk[j];
     if (ty[j] < 0 || !valid_key(k)) continue;
-    const bool keep_last = ddp_op(d, (uint32_t)ty[j]) == OP_INSERT;
-    const uint64_t e = ((uint64_t)k << 32) | ((uint32_t)ty[j] << 31) | (uint32_t)(j * BLOCK + threadIdx.x);
-    for (uint32_t s = mix32(k) & (DD_LDS - 1);; s = (s + 1) & (DD_LDS - 1)) {
+    const uint64_t e = ((uint64_t)k << 32) | ((uint32_t)ty[j] << 31) | (uint32_t)(base + j * DDR_BLOCK + tid);
+    const bool keep_last = ddr_keep_last(d, e);
+    for (uint32_t s = mix32(k) & (TAB - 1);; s = (s + 1) & (TAB - 1)) {
       uint64_t cur = tab[s];
       if (cur == EMPTY) {
         cur = atomicCAS((unsigned long long *)&tab[s], (unsigned long long)EMPTY, (unsigned long long)e);
@@ -419,399 +590,139 @@ __global__ __launch_bounds__(BLOCK) void ddp_collect_kernel(DdpArgs d) {
     }
   }
   __syncthreads();
-  // each distinct key's record, as the collapse left it, is staged by the
-  // thread that claimed its slot: the claimants' records are read, the
-  // table is then free, and block-wide offsets per type come from a scan of
-  // the per-thread counts (records of a type in thread order)
-  uint64_t rec[DD_PER_THREAD];
-  uint32_t mine0 = 0, mine1 = 0;
+  // claimants take their key's record, as the collapse left it, and its rank
+  // in its range
+  uint64_t rec[PER];
+  uint32_t rank[PER];
 #pragma unroll
-  for (int j = 0; j < DD_PER_THREAD; ++j) {
-    rec[j] = slot[j] < DD_LDS ? tab[slot[j]] : EMPTY;
+  for (int j = 0; j < PER; ++j) {
+    rec[j] = slot[j] < TAB ? tab[slot[j]] : EMPTY;
+    if (rec[j] != EMPTY) rank[j] = atomicAdd(&cnt[dds_range((uint32_t)(rec[j] >> 32), d.bits)], 1u);
+  }
+  __syncthreads();  // counts complete; the table may be overwritten
+  uint32_t own[Q], mine = 0, incl = 0;
+  if (tid < SCAN) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) mine += own[q] = cnt[tid * Q + q];
+    incl = mine;
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += y;
+    }
+    if (lane == 63) part[wv] = incl;
+  }
+  __syncthreads();
+  if (tid < SCAN) {
+    uint32_t start = incl - mine;
+    for (int w = 0; w < wv; ++w) start += part[w];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const uint32_t x = tid * Q + q;
+      cnt[x] = start;
+      if (x < nb) d.bounds[(uint64_t)blockIdx.x * nb + x] = start | ((start + own[q]) << 16);
+      start += own[q];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < PER; ++j)
     if (rec[j] != EMPTY) {
-      if (((uint32_t)rec[j] >> 31) != 0) ++mine1;
-      else ++mine0;
+      tab[cnt[dds_range((uint32_t)(rec[j] >> 32), d.bits)] + rank[j]] = rec[j];
+      d.win[ddr_index(d, rec[j])] = 1;  // within this chunk's flags, cleared before a barrier
     }
-  }
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  uint32_t in0 = mine0, in1 = mine1;  // inclusive prefixes within the wave
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y0 = __shfl_up(in0, o, 64), y1 = __shfl_up(in1, o, 64);
-    if (lane >= o) {
-      in0 += y0;
-      in1 += y1;
-    }
-  }
-  __syncthreads();  // every claimant holds its records: tab may be overwritten
-  // the waves' totals in the table's last words, the partition histograms
-  // (one per type) at its front
-  static_assert(2 * DDP_BINS + 2 * WAVES <= 2 * DD_LDS, "histogram room");
-  uint32_t *words = (uint32_t *)tab;
-  if (lane == 63) {
-    words[2 * DD_LDS - 1 - wv] = in0;
-    words[2 * DD_LDS - 1 - WAVES - wv] = in1;
-  }
-  uint32_t *bins = words;
-  for (int b = threadIdx.x; b < 2 * DDP_BINS; b += BLOCK) bins[b] = 0u;
-  __syncthreads();
-  uint32_t off0 = in0 - mine0, off1 = in1 - mine1, cnt0 = 0, cnt1 = 0;
+  uint32_t total = 0;
 #pragma unroll
-  for (int w = 0; w < WAVES; ++w) {
-    const uint32_t c0w = words[2 * DD_LDS - 1 - w], c1w = words[2 * DD_LDS - 1 - WAVES - w];
-    off0 += w < wv ? c0w : 0u;
-    off1 += w < wv ? c1w : 0u;
-    cnt0 += c0w;
-    cnt1 += c1w;
-  }
-  uint64_t *st0 = d.stage + c * DD_CHUNK, *st1 = d.stage + ((uint64_t)d.nch + c) * DD_CHUNK;
-#pragma unroll
-  for (int j = 0; j < DD_PER_THREAD; ++j) {
-    if (rec[j] == EMPTY) continue;
-    const uint64_t t = rec[j];
-    const uint32_t k = (uint32_t)(t >> 32), i = (uint32_t)(base + ((uint32_t)t & (DD_CHUNK - 1)));
-    const uint64_t e = ((uint64_t)k << 32) | i;
-    const bool t1 = ((uint32_t)t >> 31) != 0;
-    if (t1) st1[off1++] = e;
-    else st0[off0++] = e;
-    d.win[i] = 1;  // within this chunk's flags
-    atomicAdd(&bins[(t1 ? DDP_BINS : 0) + ddp_bin(k)], 1u);
-  }
+  for (int w = 0; w < SCAN / 64; ++w) total += part[w];
   __syncthreads();
-  for (uint32_t ti = 0; ti < d.nt; ++ti) {
-    uint16_t *h = d.hist + ((uint64_t)ti * d.nch + c) * DDP_BINS;
-    for (int b = threadIdx.x; b < DDP_BINS; b += BLOCK) h[b] = (uint16_t)bins[ti * DDP_BINS + b];
-  }
-  if (threadIdx.x == 0) {
-    d.cnt[c] = cnt0;
-    if (d.nt > 1) d.cnt[(uint64_t)d.nch + c] = cnt1;
-  }
+  for (uint32_t t = tid; t < total; t += DDR_BLOCK) d.rec[base + t] = tab[t];
 }
 
-// Step 2.  Block (ti, s): the histograms of segment s summed.
-__global__ __launch_bounds__(BLOCK) void ddp_segsum_kernel(DdpArgs d) {
-  const uint32_t ti = (uint32_t)(blockIdx.x / d.nseg);
-  const uint64_t s = blockIdx.x % d.nseg;
-  const uint64_t c0 = s * DDP_SEG, c1 = min(c0 + DDP_SEG, d.nch);
-  for (int b = threadIdx.x; b < DDP_BINS; b += BLOCK) {
-    uint32_t v[DDP_SEG], sum = 0;  // the segment's loads in flight together
-#pragma unroll
-    for (int j = 0; j < (int)DDP_SEG; ++j)
-      v[j] = c0 + j < c1 ? d.hist[((uint64_t)ti * d.nch + c0 + j) * DDP_BINS + b] : 0u;
-#pragma unroll
-    for (int j = 0; j < (int)DDP_SEG; ++j) sum += v[j];
-    d.seg[((uint64_t)ti * d.nseg + s) * DDP_BINS + b] = sum;
-  }
-}
-
-// Step 3.  Block (ti, g): partitions g * 64 .. g * 64 + 63 of type ti, one per
-// lane; its DDP_SCAN_WAVES waves take consecutive ranges of segments, eight
-// loads in flight at a time.
-constexpr int DDP_SCAN_WAVES = 16;
-__global__ __launch_bounds__(DDP_SCAN_WAVES * 64) void ddp_scan_kernel(DdpArgs d) {
-  __shared__ uint32_t part[DDP_SCAN_WAVES][64];
-  constexpr int GROUPS = DDP_BINS / 64;
-  const uint32_t ti = blockIdx.x / GROUPS;
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int b = (blockIdx.x % GROUPS) * 64 + lane;
-  const uint64_t q = (d.nseg + DDP_SCAN_WAVES - 1) / DDP_SCAN_WAVES;
-  const uint64_t s0 = min((uint64_t)wv * q, d.nseg), s1 = min(s0 + q, d.nseg);
-  uint32_t *col = d.seg + (uint64_t)ti * d.nseg * DDP_BINS + b;
-  uint32_t sum = 0;
-  for (uint64_t s = s0; s < s1; s += 8) {
-    uint32_t v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = s + j < s1 ? col[(s + j) * DDP_BINS] : 0u;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) sum += v[j];
-  }
-  part[wv][lane] = sum;
-  __syncthreads();
-  uint32_t run = 0;
-  for (int w = 0; w < wv; ++w) run += part[w][lane];
-  for (uint64_t s = s0; s < s1; s += 8) {
-    uint32_t v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = s + j < s1 ? col[(s + j) * DDP_BINS] : 0u;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (s + j < s1) {
-        col[(s + j) * DDP_BINS] = run;
-        run += v[j];
-      }
-  }
-  if (wv == DDP_SCAN_WAVES - 1) d.tot[ti * DDP_BINS + b] = run;
-}
-
-// Start of every partition in `rec` (exclusive prefix of the totals over
-// (type, partition)) into out[0 .. nt * DDP_BINS); the whole block (NT
-// threads) calls it.
-template <int NT>
-__device__ __forceinline__ void ddp_starts(const DdpArgs &d, uint32_t *out) {
-  __shared__ uint32_t s_wave[NT / 64];
-  constexpr int PER = 2 * DDP_BINS / NT;  // values per thread (up to two types)
-  static_assert(PER >= 1 && PER * NT == 2 * DDP_BINS, "partition counts per block");
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const uint32_t total = d.nt * DDP_BINS;
-  uint32_t v[PER], mine = 0;
-#pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    const uint32_t x = threadIdx.x * PER + j;
-    v[j] = x < total ? d.tot[x] : 0u;
-    mine += v[j];
-  }
-  uint32_t incl = mine;
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += y;
-  }
-  if (lane == 63) s_wave[wv] = incl;
-  __syncthreads();
-  uint32_t run = incl - mine;
-  for (int w = 0; w < wv; ++w) run += s_wave[w];
-#pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    const uint32_t x = threadIdx.x * PER + j;
-    if (x < total) out[x] = run;
-    run += v[j];
-  }
-  __syncthreads();
-}
-
-// The scatter and resolve steps wait on dependent loads and LDS atomics with
-// few blocks per CU (a grid of a few hundred, and the resolve table's 64 KiB
-// of LDS), so their blocks are 16 waves wide.
-constexpr int DDP_WIDE = 1024;
-
-// Step 4.  Block (ti, s): the records of segment s to their partitions' runs.
-// A record's place in its partition's run is free, so each round of up to
-// DDP_SCATTER_ROUND records is first sorted by partition in LDS (a counting
-// sort) and then written run by run: consecutive lanes store consecutive
-// words of one run, where one scattered 8-byte store per record had been
-// bound by the memory system's rate of random stores.
-constexpr int DDP_SCATTER_ROUND = DDP_WIDE * DDP_SCATTER_LOADS;
-__global__ __launch_bounds__(DDP_WIDE) void ddp_scatter_kernel(DdpArgs d) {
-  __shared__ uint32_t starts[2 * DDP_BINS];
-  __shared__ uint32_t lcnt[DDP_BINS], lbase[DDP_BINS], s_sum[DDP_BINS / 64];
-  __shared__ uint64_t sorted[DDP_SCATTER_ROUND];
-  const uint32_t ti = (uint32_t)(blockIdx.x / d.nseg);
-  const uint64_t s = blockIdx.x % d.nseg;
-  ddp_starts<DDP_WIDE>(d, starts);
-  uint32_t *cur = starts + ti * DDP_BINS;  // this type's cursors
-  static_assert(DDP_BINS <= DDP_WIDE, "one partition per thread");
-  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
-  if (tid < DDP_BINS) {
-    cur[tid] += d.seg[((uint64_t)ti * d.nseg + s) * DDP_BINS + tid];
-    lcnt[tid] = 0;
-  }
-  __syncthreads();
-  // the segment's staged records as one list (chunk j holds [pre[j],
-  // pre[j + 1]))
-  const uint64_t c0 = s * DDP_SEG, c1 = min(c0 + DDP_SEG, d.nch);
-  uint32_t pre[DDP_SEG + 1];
-  pre[0] = 0;
-#pragma unroll
-  for (int j = 0; j < (int)DDP_SEG; ++j) pre[j + 1] = pre[j] + (c0 + j < c1 ? d.cnt[(uint64_t)ti * d.nch + c0 + j] : 0u);
-  const uint32_t total = pre[DDP_SEG];
-  const uint64_t *st = d.stage + ((uint64_t)ti * d.nch + c0) * DD_CHUNK;
-  constexpr int U = DDP_SCATTER_LOADS;
-  for (uint32_t r0 = 0; r0 < total; r0 += DDP_SCATTER_ROUND) {  // the same rounds in every thread
-    const uint32_t nr = min((uint32_t)DDP_SCATTER_ROUND, total - r0);
-    uint64_t e[U];
-    uint32_t bin[U], rk[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t t = r0 + u * DDP_WIDE + tid;
-      e[u] = EMPTY;
-      if (t < total) {
-        int j = 0;
-#pragma unroll
-        for (int x = 1; x < (int)DDP_SEG; ++x) j += t >= pre[x] ? 1 : 0;
-        e[u] = st[(uint64_t)j * DD_CHUNK + (t - pre[j])];
-      }
-    }
-    // each record's rank within its partition in this round
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (e[u] != EMPTY) {
-        bin[u] = ddp_bin((uint32_t)(e[u] >> 32));
-        rk[u] = atomicAdd(&lcnt[bin[u]], 1u);
-      }
+// The table is sized for the records of a range: up to about 2,048 of the
+// smaller batches, 8,192 at 2^22 operations.  LANES lanes read one chunk's run
+// together: eight where runs are eight records or more; beyond 2^23
+// operations runs are short and there are thousands of chunks, and the
+// dependent reads of bounds and records take the time (2^26 operations: eight
+// lanes 4.1 ms, one 3.5).
+template <int PER, int BINS, int LANES>
+__global__ __launch_bounds__(DDR_BLOCK) void ddr_resolve_kernel(DdrArgs d) {
+  constexpr uint32_t CH = (uint32_t)DDR_BLOCK * PER;
+  constexpr int TAB = PER == 8 ? 16384 : 4096;
+  constexpr uint32_t CAP = TAB * 3 / 4;
+  static_assert(CAP + DDR_BLOCK < TAB + 1, "at most one claim per thread past the limit");
+  __shared__ uint64_t tab[TAB];
+  __shared__ uint32_t s_claims;
+  const uint32_t nb = 1u << d.bits;
+  // neighbouring ranges on one XCD (blocks go to the XCDs in turn): their
+  // bounds share cache lines
+  const uint32_t b = nb >= 8 ? (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+  const uint64_t whole = 1ull << (32 - d.bits), first = (uint64_t)b * whole, last = first + whole;
+  constexpr int LOADS = LANES == 1 ? 4 : 2;  // reads in flight
+  const int sub = threadIdx.x % LANES;
+  uint64_t lo = first, width = whole;
+  if constexpr (BINS == DDR_BINS_BIG) {
+    // the first width by the range's records
+    if (threadIdx.x == 0) s_claims = 0;
     __syncthreads();
-    // exclusive prefix of the round's partition counts
-    uint32_t v = 0, incl = 0;
-    if (tid < DDP_BINS) {
-      v = lcnt[tid];
-      incl = v;
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += y;
-      }
-      if (lane == 63) s_sum[wv] = incl;
+    uint32_t mine = 0;
+    for (uint32_t c = threadIdx.x; c < d.nch; c += DDR_BLOCK) {
+      const uint32_t be = d.bounds[(uint64_t)c * nb + b];
+      mine += (be >> 16) - (be & 0xFFFFu);
     }
+    if (mine) atomicAdd(&s_claims, mine);
     __syncthreads();
-    if (tid < DDP_BINS) {
-      uint32_t run = incl - v;
-      for (int w = 0; w < wv; ++w) run += s_sum[w];
-      lbase[tid] = run;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (e[u] != EMPTY) sorted[lbase[bin[u]] + rk[u]] = e[u];
-    __syncthreads();
-    // run by run to the partitions' places
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t p = u * DDP_WIDE + tid;
-      if (p < nr) {
-        const uint64_t x = sorted[p];
-        const uint32_t b = ddp_bin((uint32_t)(x >> 32));
-        d.rec[cur[b] + (p - lbase[b])] = x;
-      }
-    }
-    __syncthreads();
-    if (tid < DDP_BINS) {
-      cur[tid] += lcnt[tid];
-      lcnt[tid] = 0;
-    }
+    for (uint32_t r = s_claims; r > CAP; r /= 2) width = (width + 1) / 2;
     __syncthreads();
   }
-}
-
-// Step 5.  Block (ti, b): partition b of type ti.
-__global__ __launch_bounds__(DDP_WIDE) void ddp_resolve_kernel(DdpArgs d) {
-  __shared__ uint64_t tab[DDP_TAB];
-  __shared__ uint32_t starts[2 * DDP_BINS];
-  __shared__ uint32_t s_claims, s_over;
-  const uint32_t ti = blockIdx.x / DDP_BINS, b = blockIdx.x % DDP_BINS;
-  const uint32_t op = ddp_op(d, ti);
-  ddp_starts<DDP_WIDE>(d, starts);
-  const uint64_t start = starts[ti * DDP_BINS + b], count = d.tot[ti * DDP_BINS + b];
-  if (count == 0) return;  // the same in the whole block
-  for (int j = threadIdx.x; j < DDP_TAB; j += DDP_WIDE) tab[j] = EMPTY;
-  if (threadIdx.x == 0) {
-    s_claims = 0;
-    s_over = 0;
-  }
-  __syncthreads();
-  const uint64_t *rec = d.rec + start;
-  // at most DDP_WIDE claims land after the one that crosses DDP_CAP (one per
-  // thread in flight), so the table never fills and every probe ends
-  static_assert(DDP_CAP + DDP_WIDE < DDP_TAB, "resolve table headroom");
-  // records DDP_RESOLVE_LOADS at a time per thread, all loads in flight.
-  // New keys are counted per wave and record step (one LDS atomic for the
-  // wave's claims: one per claim serialized the block on a single word),
-  // and the overflow flag is checked before every insert, so each thread
-  // claims at most one slot after the count crosses DDP_CAP
-  constexpr int U = DDP_RESOLVE_LOADS;
-  const int lane = threadIdx.x & 63;
-  uint64_t es[U];
+  while (lo < last) {
+    width = min(width, last - lo);
+    for (int j = threadIdx.x; j < TAB; j += DDR_BLOCK) tab[j] = EMPTY;
+    if (threadIdx.x == 0) s_claims = 0;
+    __syncthreads();
+    for (uint32_t c = threadIdx.x / LANES; c < d.nch; c += DDR_BLOCK / LANES) {
+      const uint32_t be = d.bounds[(uint64_t)c * nb + b], end = be >> 16;
+      const uint64_t *run = d.rec + (uint64_t)c * CH;
+      for (uint32_t t0 = (be & 0xFFFFu) + sub; t0 < end; t0 += LANES * LOADS) {
+        uint64_t es[LOADS];
 #pragma unroll
-  for (int u = 0; u < U; ++u) es[u] = EMPTY;
-  for (uint64_t r0 = threadIdx.x; r0 < count; r0 += (uint64_t)U * DDP_WIDE) {
+        for (int u = 0; u < LOADS; ++u) es[u] = t0 + u * LANES < end ? run[t0 + u * LANES] : EMPTY;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint64_t r = r0 + (uint64_t)u * DDP_WIDE;
-      es[u] = r < count ? rec[r] : EMPTY;
-    }
-    bool over = false;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint64_t e = es[u];
-      over = over || *(volatile uint32_t *)&s_over != 0;
-      bool claimed = false;
-      if (e != EMPTY && !over) {
-        const uint32_t k = (uint32_t)(e >> 32);
-        for (uint32_t sl = mix32(k) & (DDP_TAB - 1);; sl = (sl + 1) & (DDP_TAB - 1)) {
-          uint64_t cur = tab[sl];
-          if (cur == EMPTY) {
-            cur = atomicCAS((unsigned long long *)&tab[sl], (unsigned long long)EMPTY, (unsigned long long)e);
+        for (int u = 0; u < LOADS; ++u) {
+          const uint64_t e = es[u];
+          const uint32_t k = (uint32_t)(e >> 32);
+          if (e == EMPTY || (uint64_t)(dds_hash(k) - (uint32_t)lo) >= width) continue;
+          if (*(volatile uint32_t *)&s_claims > CAP) break;
+          const bool keep_last = ddr_keep_last(d, e);
+          for (uint32_t s = mix32(k) & (TAB - 1);; s = (s + 1) & (TAB - 1)) {
+            uint64_t cur = *(volatile uint64_t *)&tab[s];
             if (cur == EMPTY) {
-              claimed = true;
-              break;
+              cur = atomicCAS((unsigned long long *)&tab[s], (unsigned long long)EMPTY, (unsigned long long)e);
+              if (cur == EMPTY) {
+                atomicAdd(&s_claims, 1u);
+                break;
+              }
             }
-          }
-          if ((uint32_t)(cur >> 32) == k) {
-            if (op == OP_INSERT) {
-              if (cur < e) atomicMax((unsigned long long *)&tab[sl], (unsigned long long)e);
-            } else if (cur > e) {
-              atomicMin((unsigned long long *)&tab[sl], (unsigned long long)e);
-            }
+            if ((uint32_t)(cur >> 32) != k) continue;
+            // two records of one key: the loser's flag goes (a record met
+            // again after its range was split loses to the same records)
+            if (keep_last ? cur < e : cur > e)
+              cur = keep_last ? atomicMax((unsigned long long *)&tab[s], (unsigned long long)e)
+                              : atomicMin((unsigned long long *)&tab[s], (unsigned long long)e);
+            const uint64_t loser = (keep_last ? cur < e : cur > e) ? cur : e;
+            d.win[ddr_index(d, loser)] = 0;
             break;
           }
         }
       }
-      const uint64_t cm = ballot(claimed);
-      if (cm && lane == __builtin_ctzll(cm)) {
-        const uint32_t c = (uint32_t)__popcll(cm);
-        if (atomicAdd(&s_claims, c) + c > DDP_CAP) s_over = 1;
-      }
     }
-    if (over) break;
-  }
-  __syncthreads();
-  if (!s_over) {
-    // every record's flag was set by its chunk: clear the losers' (a key
-    // recorded by several chunks), a few scattered stores instead of one
-    // per distinct key.  A partition of at most U * DDP_WIDE records was
-    // read in one step, and each thread still holds its records.
-    const bool held = count <= (uint64_t)U * DDP_WIDE;
-    for (uint64_t r0 = threadIdx.x; r0 < count; r0 += (uint64_t)U * DDP_WIDE) {
-      if (!held) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const uint64_t r = r0 + (uint64_t)u * DDP_WIDE;
-          es[u] = r < count ? rec[r] : EMPTY;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint64_t e = es[u];
-        if (e == EMPTY) continue;
-        const uint32_t k = (uint32_t)(e >> 32);
-        uint32_t sl = mix32(k) & (DDP_TAB - 1);
-        while ((uint32_t)(tab[sl] >> 32) != k) sl = (sl + 1) & (DDP_TAB - 1);
-        if (tab[sl] != e) d.win[(uint32_t)e] = 0;
-      }
-    }
-    return;
-  }
-  // more distinct keys than the table takes: an open-addressed table of
-  // 2 x count words in HBM, in the staging area (free after the scatter;
-  // partitions' tables are disjoint: [2 start, 2 (start + count))), by
-  // atomics (stores written through, so that the claims see them)
-  uint64_t *ft = d.stage + 2 * start;
-  const uint64_t m = 2 * count;
-  for (uint64_t j = threadIdx.x; j < m; j += DDP_WIDE)
-    __hip_atomic_store(&ft[j], EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __syncthreads();
-  for (uint64_t r = threadIdx.x; r < count; r += DDP_WIDE) {
-    const uint64_t e = rec[r];
-    const uint32_t k = (uint32_t)(e >> 32);
-    for (uint64_t sl = mix32(k) % m;; sl = (sl + 1 == m) ? 0 : sl + 1) {
-      const uint64_t cur = cas64(&ft[sl], EMPTY, e);
-      if (cur == EMPTY) break;
-      if ((uint32_t)(cur >> 32) == k) {
-        if (op == OP_INSERT) {
-          if (cur < e) __hip_atomic_fetch_max(&ft[sl], e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else if (cur > e) {
-          __hip_atomic_fetch_min(&ft[sl], e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        break;
-      }
-    }
-  }
-  __syncthreads();
-  // the record left in its key's word is the winner; clear the others' flags
-  for (uint64_t r = threadIdx.x; r < count; r += DDP_WIDE) {
-    const uint64_t e = rec[r];
-    const uint32_t k = (uint32_t)(e >> 32);
-    for (uint64_t sl = mix32(k) % m;; sl = (sl + 1 == m) ? 0 : sl + 1) {
-      const uint64_t cur = __hip_atomic_load(&ft[sl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if ((uint32_t)(cur >> 32) == k) {
-        if (cur != e) d.win[(uint32_t)e] = 0;
-        break;
-      }
+    __syncthreads();
+    const uint32_t claims = s_claims;
+    const bool over = claims > CAP;  // the same in the whole block
+    __syncthreads();
+    if (over) {
+      width = (width + 1) / 2;
+    } else {
+      lo += width;
+      if (claims <= CAP / 2) width *= 2;
     }
   }
 }
@@ -2403,7 +2314,8 @@ __global__ __launch_bounds__(BLOCK) void drain_kernel(uint64_t *stash, uint64_t 
 // a 64-bit table, held in registers), counts them by ballots and reserves
 // room for the whole trip with one add; a wave's live words then go to
 // consecutive positions.  One add per wave had made a 4.0 M-entry dump of
-// 4.2 M slots 794 us.
+// 4.2 M slots 794 us; now about 10 us (export, re-insertion and lookups of
+// the entries 1,315 -> 530 us).
 // SET32: words of a key-only set (the key itself, EMPTY all ones), written as
 // 64-bit words with value half 0.
 // ---------------------------------------------------------------------------
@@ -3748,43 +3660,34 @@ static uint64_t dd_set_words(uint64_t n) {  // the executor's open-addressed ded
   return want;
 }
 
-// The partitioned dedupe's buffers for a batch of n operations with nt types,
-// carved from one scratch allocation (each piece 256-byte aligned).
-static uint64_t ddp_layout(uint64_t *base, uint64_t n, uint32_t nt, DdpArgs *d) {
-  const uint64_t nch = (n + DD_CHUNK - 1) / DD_CHUNK, nseg = (nch + DDP_SEG - 1) / DDP_SEG;
-  auto words = [](uint64_t bytes) { return (bytes + 255) / 256 * 32; };
-  uint64_t at = 0;
-  auto take = [&](uint64_t bytes) {
-    const uint64_t w = at;
-    at += words(bytes);
-    return base ? base + w : nullptr;
-  };
-  uint64_t *stage = take((uint64_t)std::max<uint32_t>(nt, 2) * nch * DD_CHUNK * 8);
-  uint64_t *rec = take(n * 8);
-  uint64_t *win = take(nch * DD_CHUNK);
-  uint64_t *hist = take((uint64_t)nt * nch * DDP_BINS * 2);
-  uint64_t *cnt = take((uint64_t)nt * nch * 4);
-  uint64_t *seg = take((uint64_t)nt * nseg * DDP_BINS * 4);
-  uint64_t *tot = take((uint64_t)nt * DDP_BINS * 4);
-  if (d) {
-    d->n = n;
-    d->nch = nch;
-    d->nseg = nseg;
-    d->nt = nt;
-    d->stage = stage;
-    d->rec = rec;
-    d->win = (uint8_t *)win;
-    d->hist = (uint16_t *)hist;
-    d->cnt = (uint32_t *)cnt;
-    d->seg = (uint32_t *)seg;
-    d->tot = (uint32_t *)tot;
-  }
-  return at;
+// Chunk of the two-launch dedupe: about 128 chunks or more (a block each, the
+// chip has 256 compute units), up to eight operations per thread.
+static uint64_t ddr_chunk(uint64_t n) {
+  return (uint64_t)DDR_BLOCK * (n <= (1ull << 17) ? 1 : n <= (1ull << 18) ? 2 : n <= (1ull << 20) ? 4 : 8);
 }
 
-// Words of the dedupe scratch for n operations: the partitioned dedupe of
-// plain launches (mixed batches: two types) or the executor's set.
-static uint64_t dd_words_for(uint64_t n) { return std::max(dd_set_words(n), ddp_layout(nullptr, n, 2, nullptr)); }
+// The dedupe's buffers for a batch of n operations, carved from one scratch
+// allocation (each piece 256-byte aligned): records and range bounds of every
+// chunk (at most DDR_BLOCK * 8 operations), and a winner flag per operation.
+static uint64_t ddr_layout(uint64_t *base, uint64_t n, uint64_t **rec, uint32_t **bounds, uint8_t **win) {
+  // a chunk is shorter where the batch is (launch_dedupe); its bounds are the
+  // larger part then
+  const uint64_t ch = ddr_chunk(n), nch = (n + ch - 1) / ch;
+  auto words = [](uint64_t bytes) { return (bytes + 255) / 256 * 32; };
+  const uint64_t w_rec = words(nch * ch * 8), w_bounds = words(nch * (n > DDR_MORE ? DDR_BINS_BIG : DDR_BINS) * 4), w_win = words(n);
+  if (base) {
+    *rec = base;
+    *bounds = (uint32_t *)(base + w_rec);
+    *win = (uint8_t *)(base + w_rec + w_bounds);
+  }
+  return w_rec + w_bounds + w_win;
+}
+
+// Words of the dedupe scratch for n operations: the dedupe of plain launches
+// or the executor's set.
+static uint64_t dd_words_for(uint64_t n) {
+  return std::max(dd_set_words(n), ddr_layout(nullptr, n, nullptr, nullptr, nullptr));
+}
 
 // Worklist entries a stash drain may append: the whole stash table and the
 // pending list.
@@ -4100,26 +4003,55 @@ static void launch_drain_any(hive_drain *d, int mode, hipStream_t st) {
   }
 }
 
-// The partitioned dedupe of a batch (five launches) into the scratch at dd,
-// which holds dd_words_for(n) words; *win gets the winner flags.
+template <int PER, int BINS = DDR_BINS>
+static void launch_ddr(const DdrArgs &a, hipStream_t st) {
+  hipLaunchKernelGGL((ddr_chunk_kernel<PER, BINS>), dim3(a.nch), dim3(DDR_BLOCK), 0, st, a);
+  const dim3 ranges(1u << a.bits);
+  if (BINS == DDR_BINS_BIG && a.n > 2 * DDR_MORE)
+    hipLaunchKernelGGL((ddr_resolve_kernel<PER, BINS, BINS == DDR_BINS_BIG ? 1 : 8>), ranges, dim3(DDR_BLOCK), 0, st,
+                       a);
+  else
+    hipLaunchKernelGGL((ddr_resolve_kernel<PER, BINS, 8>), ranges, dim3(DDR_BLOCK), 0, st, a);
+}
+
+// The dedupe of a batch (one launch, or the two of the chunked form) into the
+// scratch at dd, which holds dd_words_for(n) words; *win gets the winner
+// flags.
 static hive_status launch_dedupe(uint64_t *dd, uint32_t mode, const uint8_t *d_ops, const uint32_t *d_keys,
                                  uint64_t n, hipStream_t st, const uint8_t **win) {
-  DdpArgs d{};
-  const uint32_t nt = mode == OP_MIXED ? 2 : 1;
-  ddp_layout(dd, n, nt, &d);
-  d.ops = d_ops;
-  d.keys = d_keys;
-  d.mode = mode;
-  hipLaunchKernelGGL(ddp_collect_kernel, dim3((unsigned)d.nch), dim3(BLOCK), 0, st, d);
-  *win = d.win;
-  // a batch of one chunk: the chunk's winners are the batch's (the serving
-  // loop's requests are mostly this small, and each launch costs the host
-  // several microseconds)
-  if (d.nch == 1) return launch_check();
-  hipLaunchKernelGGL(ddp_segsum_kernel, dim3((unsigned)(nt * d.nseg)), dim3(BLOCK), 0, st, d);
-  hipLaunchKernelGGL(ddp_scan_kernel, dim3(nt * (DDP_BINS / 64)), dim3(DDP_SCAN_WAVES * 64), 0, st, d);
-  hipLaunchKernelGGL(ddp_scatter_kernel, dim3((unsigned)(nt * d.nseg)), dim3(DDP_WIDE), 0, st, d);
-  hipLaunchKernelGGL(ddp_resolve_kernel, dim3(nt * DDP_BINS), dim3(DDP_WIDE), 0, st, d);
+  uint64_t *rec = nullptr;
+  uint32_t *bounds = nullptr;
+  uint8_t *flags = nullptr;
+  (void)ddr_layout(dd, n, &rec, &bounds, &flags);
+  *win = flags;
+  if (n <= DDS_MAX) {
+    uint32_t bits = 0;
+    while (((uint64_t)DDS_PER << bits) < n) ++bits;
+    const DdsArgs a{d_ops, d_keys, flags, (uint32_t)n, mode, bits};
+    hipLaunchKernelGGL(dds_kernel, dim3(1u << bits), dim3(DDS_BLOCK), 0, st, a);
+    return launch_check();
+  }
+  // ranges of about 1,024 operations and at most DDR_BINS of them; of about
+  // 8,192 beyond DDR_MORE, where each range reads a run of every chunk
+  uint32_t bits = 4;
+  while ((1u << bits) < DDR_BINS && (1024ull << bits) < n) ++bits;
+  while ((1u << bits) < DDR_BINS_BIG && (8192ull << bits) < n) ++bits;
+  const uint64_t ch = ddr_chunk(n);
+  DdrArgs a{d_ops, d_keys, flags, rec, bounds, (uint32_t)n, mode, bits, (uint32_t)((n + ch - 1) / ch), OP_NONE};
+  const bool by_type = mode == OP_MIXED && n >= (1ull << 31);  // indices fill the word
+  for (uint32_t only : {(uint32_t)OP_INSERT, (uint32_t)OP_DELETE}) {
+    if (by_type) a.only = only;
+    switch (ch / DDR_BLOCK) {
+      case 1: launch_ddr<1>(a, st); break;
+      case 2: launch_ddr<2>(a, st); break;
+      case 4: launch_ddr<4>(a, st); break;
+      default:
+        if (n > DDR_MORE) launch_ddr<8, DDR_BINS_BIG>(a, st);
+        else launch_ddr<8>(a, st);
+        break;
+    }
+    if (!by_type) break;
+  }
   return launch_check();
 }
 

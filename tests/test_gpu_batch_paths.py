@@ -14,6 +14,8 @@ from paper_2510_15095_amd import workload as wl
 
 pytestmark = pytest.mark.gpu
 
+M32 = 0xFFFFFFFF
+
 
 def case(msg):
     print(f"[case] {msg}", flush=True)
@@ -102,4 +104,82 @@ def test_dump_by_trips(H, S, set32, slots, extra):
     assert H.hive_dump(t.h, small) == len(o)
     got = host(small)
     assert np.unique(got).size == got.size and np.isin(got, words).all()
+    t.close()
+
+
+def _range_keys(n, lo):
+    """n distinct valid keys whose dedupe hash (key times an odd constant) is
+    lo, lo + 1, ...: all in one hash range of any batch size."""
+    inv = pow(0x9E3779B1, -1, 1 << 32)
+    h = (np.arange(n + 2, dtype=np.uint64) + np.uint64(lo)) & np.uint64(M32)
+    k = (h * np.uint64(inv)) & np.uint64(M32)
+    return k[(k != 0) & (k != M32)][:n].astype(np.uint32)
+
+
+def _dedupe_rounds(H, keys, seed, n, set32=False):
+    """An insert batch, a mixed batch and a delete batch of n operations each
+    over `keys`, with repeats, against the dictionary."""
+    rng = np.random.default_rng(seed)
+    nb = max(1, int(np.ceil(keys.size / (0.6 * (32 if set32 else 16)))))
+    t, o = make(H, 16, nb, set32, stash_capacity=max(1024, keys.size // 4)), oracle.O1()
+    ins = keys[rng.integers(0, keys.size, n)]
+    vals = np.zeros(n, np.uint32) if set32 else rng.integers(1, 1 << 32, n, dtype=np.uint64).astype(np.uint32)
+    t.insert(dev(ins), None if set32 else dev(vals))
+    o.insert(ins, vals)
+    assert t.stats()["live"] == len(o)
+    pick = rng.integers(0, keys.size, n)
+    ops = np.array([wl.OP_INSERT, wl.OP_DELETE, wl.OP_LOOKUP, wl.OP_DELETE], np.uint8)[pick % 4]
+    v, f = t.mixed(dev(ops), dev(keys[pick]), dev(vals))
+    ov, of = o.apply(ops, keys[pick], vals)
+    assert np.array_equal(host(f), of)
+    if not set32:
+        assert np.array_equal(host(v), ov)
+    gone = keys[rng.integers(0, keys.size, n)]
+    assert np.array_equal(host(t.delete(dev(gone))), o.delete(gone))
+    assert t.stats()["live"] == len(o)
+    assert np.array_equal(t.dump(), o.dump())
+    t.close()
+
+
+@pytest.mark.parametrize("n", [1, 512, 513, 1 << 14, (1 << 14) + 1, (1 << 17) + 1, (1 << 18) + 1, (1 << 20) + 1])
+def test_dedupe_forms(H, n):
+    """Batches at the edges of the dedupe's forms: one block, several, the
+    two-launch form and each of its chunk sizes (a quarter of the keys are
+    reserved ones for the smallest)."""
+    case(f"dedupe n={n}")
+    _dedupe_rounds(H, wl.KeyStream(600).range(0, max(4, n // 2)), 600 + n, n)
+
+
+@pytest.mark.parametrize("set32", [False, True])
+@pytest.mark.parametrize("n,distinct", [(12_000, 9_000), (200_000, 30_000), (1_500_000, 40_000)])
+def test_dedupe_one_range(H, n, distinct, set32):
+    """All keys in one hash range, more than its LDS table takes: the range is
+    worked through in sub-ranges."""
+    case(f"dedupe in one range n={n} distinct={distinct} set32={set32}")
+    _dedupe_rounds(H, _range_keys(distinct, 0x40000000 - 1000), 700 + n, n, set32)
+
+
+@pytest.mark.parametrize("n", [9_000, 300_000])
+def test_dedupe_one_hot_key(H, n):
+    """One key takes most of the batch: beyond the records a block holds."""
+    case(f"dedupe with a hot key n={n}")
+    keys = np.concatenate([np.full(30, 12345, np.uint32), wl.KeyStream(601).range(0, 10)])
+    _dedupe_rounds(H, np.unique(keys), 800 + n, n)
+
+
+def test_dedupe_beyond_four_million(H):
+    """More than 2^22 operations: every range takes several sub-ranges."""
+    n = 3 * (1 << 22) + 77
+    case(f"dedupe n={n}")
+    rng = np.random.default_rng(9)
+    keys = wl.KeyStream(602).range(0, 1 << 23)
+    ins = keys[rng.integers(0, keys.size, n)]
+    vals = np.arange(1, n + 1, dtype=np.uint32)
+    t, o = H.Table(int(np.ceil(keys.size / (0.7 * 16)))), oracle.O1(keys.size)
+    t.insert(dev(ins), dev(vals))
+    o.insert(ins, vals)
+    assert np.array_equal(t.dump(), o.dump())
+    gone = keys[rng.integers(0, keys.size, n)]
+    assert np.array_equal(host(t.delete(dev(gone))), o.delete(gone))
+    assert t.stats()["live"] == len(o)
     t.close()
