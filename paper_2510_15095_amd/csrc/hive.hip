@@ -56,13 +56,13 @@ constexpr int BLOCK = 64 * WAVES;
 #define EVICT_SLOTS_PER_LANE 16  // 16-slot buckets: slots per lane of an eviction group (2, 4, 8, 16)
 #endif
 constexpr int EVICT_GRID = 2048;  // most blocks of the eviction phase (all resident at once)
-constexpr int RESIZE_GRID = 2048; // blocks of a resize pass (grid-stride over pairs)
+constexpr int RESIZE_GRID = 1024; // most blocks of resize_kernel (they stride over buckets and stash words)
+constexpr int MERGE_GRID = 512;   // blocks of merge_kernel
 // Most blocks of a probe launch: larger batches stride over tiles, about
 // eight tiles per block at 2^26 operations (bulk step +4% against one tile
 // per block, measured over 2,048 .. 65,536 blocks: the launch pays less
 // block setup, such as the coherent read of the control line)
 constexpr uint64_t OPS_GRID = 32768;
-constexpr int DRAIN_GRID = 2048;
 constexpr int DRAIN_WORDS = 8;  // stash words per thread and trip of the drain
 #ifndef OPS_WAVES_PER_EU
 #define OPS_WAVES_PER_EU 4  // occupancy target of the probe kernel (waves per SIMD)
@@ -188,15 +188,10 @@ __device__ __forceinline__ uint64_t fold_shards_wave(Ctl *c, bool wl_done) {
   return total_wl;
 }
 
-// After a batch or a resize call (one wave of 64 threads).
+// After a batch without inserts, and while phases are timed (one wave of 64
+// threads).
 __global__ __launch_bounds__(64) void finish_kernel(Ctl *c) {
   (void)fold_shards_wave(c, true);
-}
-
-// The counters folded with the worklist kept (one wave of 64 threads): the
-// key count of a batch whose worklist is placed after its load-factor rule.
-__global__ __launch_bounds__(64) void fold_kernel(Ctl *c) {
-  (void)fold_shards_wave(c, false);
 }
 
 struct OpsArgs {
@@ -1675,19 +1670,28 @@ __device__ __forceinline__ void evict_counters(const EvictArgs &a, bool unreserv
   }
 }
 
+// The end of an eviction launch (every thread calls it): the block that
+// finishes last folds the shards into the totals and empties the worklist;
+// with no items, block 0 does (the other blocks have nothing to write).  A
+// launch of its own for this took 2.9 us and a host call per batch.
+__device__ __forceinline__ void evict_finish(Ctl *c, bool items);
+
 // P3 as a launch: every worklist item through evict_round (step 2 again,
 // then the bounded chain of Algorithm 3, then the stash or the pending list),
 // one item per group of the eviction shape, the grid striding over items.
-// The worklist is emptied afterwards by finish_kernel (it also counts the
-// items and folds unreserved stash placements into the stash count), so this
-// kernel takes no ticket.
+// The last block empties the worklist, counts the items and folds unreserved
+// stash placements into the stash count (evict_finish).  With DEFER, a launch
+// of finish_kernel does, after the stash launch.
 template <int S, int PAIR = PAIR_BITHASH, bool DEFER = false>
 __global__ __launch_bounds__(BLOCK) void evict_kernel(EvictArgs a) {
   using E = EvictShape<S>;
   __shared__ uint64_t pre[NSHARD + 1];
   wl_prefix(a.ctl, pre);
   const uint64_t cnt = pre[NSHARD];
-  if (cnt == 0) return;  // same in every block
+  if (cnt == 0) {  // same in every block
+    if constexpr (!DEFER) evict_finish(a.ctl, false);
+    return;
+  }
   const Geo geo = read_geo(a.ctl);
   // the same in every block: an unreserved launch leaves the count alone
   const bool unreserved = ld_ctl(&a.ctl->stash_count) + cnt <= a.stash_cap;
@@ -1704,6 +1708,7 @@ __global__ __launch_bounds__(BLOCK) void evict_kernel(EvictArgs a) {
                                 n_evict, n_full, n_side, n_fresh);
   }
   evict_counters(a, unreserved, (uint64_t)blockIdx.x * WAVES + wv, n_evict, n_full, n_side, n_fresh, sl);
+  if constexpr (!DEFER) evict_finish(a.ctl, true);
 }
 
 // P3 for 16-slot buckets with two candidates, as a launch whose lanes are
@@ -1732,7 +1737,10 @@ __global__ __launch_bounds__(BLOCK) void evict_lanes_kernel(EvictArgs a) {
   __shared__ uint64_t pre[NSHARD + 1];
   wl_prefix(a.ctl, pre);
   const uint64_t cnt = pre[NSHARD];
-  if (cnt == 0) return;  // same in every block
+  if (cnt == 0) {  // same in every block
+    evict_finish(a.ctl, false);
+    return;
+  }
   const Geo geo = read_geo(a.ctl);
   // the same in every block: an unreserved launch leaves the count alone
   const bool unreserved = ld_ctl(&a.ctl->stash_count) + cnt <= a.stash_cap;
@@ -1858,6 +1866,7 @@ __global__ __launch_bounds__(BLOCK) void evict_lanes_kernel(EvictArgs a) {
     }
   }
   evict_counters(a, unreserved, wid, n_evict, n_full, n_side, n_fresh, 0);
+  evict_finish(a.ctl, true);
 }
 
 // Step 4 as its own launch (after evict_kernel<.., DEFER>): every worklist
@@ -1901,14 +1910,18 @@ __global__ __launch_bounds__(BLOCK) void stash_kernel(EvictArgs a) {
 // ---------------------------------------------------------------------------
 // Linear-hashing resize (Section IV-C), decided on the device.
 //
-// A resize call is planned by resize_plan_kernel (pairs to split or merge),
-// then runs as segments, one per hashing round: pass 1 splits the segment's
-// pairs, or tests each merge pair for room; pass 2 moves the merge pairs that
-// passed, from the top down to the first that did not.  The last block of
-// each pass updates the geometry and plans the next segment, so the host
-// launches a fixed number of segments and never reads the device.
+// resize_kernel plans a call in every block (the plan is a function of the
+// control block, which nobody changes before the last block has finished) and
+// does all of its splits, of however many hashing rounds, in one launch: an
+// entry's way through the rounds depends on the entry and its bucket alone,
+// so each bucket's entries go to their last bucket at once.  merge_kernel
+// does a contraction, whose pairs depend on one another, phase by phase
+// within one launch.  When there is nothing to do, which is the usual batch,
+// each is one idle launch; a plan, one or two passes per hashing round that
+// the host could not rule out, a drain and a fold took 9 to 25 launches of
+// 1 to 5 us each.
 // ---------------------------------------------------------------------------
-enum : uint32_t { PLAN_PRE = 0, PLAN_PRE_MIXED = 1, PLAN_POST = 2, PLAN_SPLIT = 3, PLAN_MERGE = 4 };
+enum : uint32_t { PLAN_PRE = 0, PLAN_PRE_MIXED = 1, PLAN_POST = 2, PLAN_SPLIT = 3, PLAN_MERGE = 4, PLAN_NONE = 5 };
 
 struct ResizeArgs {
   uint64_t *buckets;
@@ -1960,32 +1973,50 @@ __device__ __forceinline__ void plan_next(volatile Ctl *c) {
 // while (live + extra) * 100 > lf_expand * buckets * S, contraction while
 // live * 100 < lf_contract * buckets * S and the table is above its initial
 // size.
-__device__ __forceinline__ void plan_policy(volatile Ctl *c, const ResizeArgs &a, uint64_t extra,
-                                            bool allow_contract) {
-  const uint64_t S = a.S, K = a.K, nb = c->n_buckets, live = c->live;
+struct Plan {
+  int64_t dir;    // +1 split, -1 merge, 0 nothing
+  uint64_t todo;  // pairs
+};
+__device__ __forceinline__ Plan plan_policy(const ResizeArgs &a, uint64_t nb, uint64_t live, uint64_t initial,
+                                            uint64_t extra, bool allow_contract) {
+  const uint64_t S = a.S, K = a.K;
   const uint64_t need = live + extra;
+  Plan p{0, 0};
   if (need * 100 > (uint64_t)a.lf_expand_pct * nb * S) {
     const uint64_t den = (uint64_t)a.lf_expand_pct * S;
     const uint64_t r = (need * 100 + den - 1) / den;  // fewest buckets that satisfy the rule
     const uint64_t steps = (r - nb + K - 1) / K;
-    c->resize_dir = 1;
-    c->resize_todo = steps * K;
-  } else if (allow_contract && live * 100 < (uint64_t)a.lf_contract_pct * nb * S && nb > c->initial_buckets) {
+    p.dir = 1;
+    p.todo = steps * K;
+  } else if (allow_contract && live * 100 < (uint64_t)a.lf_contract_pct * nb * S && nb > initial) {
     const uint64_t q = live * 100 / ((uint64_t)a.lf_contract_pct * S);
-    const uint64_t lim = max(q, c->initial_buckets);
+    const uint64_t lim = max(q, initial);
     if (nb > lim) {
       const uint64_t steps = (nb - lim + K - 1) / K;
-      const uint64_t fin = (nb > steps * K && nb - steps * K > c->initial_buckets) ? nb - steps * K
-                                                                                  : c->initial_buckets;
-      c->resize_dir = -1;
-      c->resize_todo = nb - fin;
+      const uint64_t fin = (nb > steps * K && nb - steps * K > initial) ? nb - steps * K : initial;
+      p.dir = -1;
+      p.todo = nb - fin;
     }
+  }
+  return p;
+}
+
+// The pairs a call asks for.  `amount` is the insert count (PRE), or the pair
+// count (SPLIT, MERGE).
+__device__ __forceinline__ Plan plan_of(const ResizeArgs &a, uint32_t mode, uint64_t amount, uint64_t nb,
+                                        uint64_t live, uint64_t initial) {
+  switch (mode) {
+    case PLAN_PRE:
+    case PLAN_PRE_MIXED: return plan_policy(a, nb, live, initial, amount, false);
+    case PLAN_POST: return plan_policy(a, nb, live, initial, 0, true);
+    case PLAN_SPLIT: return Plan{1, amount};
+    case PLAN_MERGE: return Plan{-1, amount};
+    default: return Plan{0, 0};
   }
 }
 
-// Start a resize call (one thread): the pairs the call asks for, then the
-// first segment.  `amount` is the insert count (PRE), or the pair count
-// (SPLIT, MERGE).
+// Start a resize call of the persistent executor (one thread): the pairs the
+// call asks for, then the first segment.
 __device__ __forceinline__ void plan_start(volatile Ctl *c, const ResizeArgs &a, uint32_t mode, uint64_t amount) {
   c->resize_dir = 0;
   c->resize_todo = 0;
@@ -1994,58 +2025,30 @@ __device__ __forceinline__ void plan_start(volatile Ctl *c, const ResizeArgs &a,
     c->seg = 0;
     return;
   }
-  switch (mode) {
-    case PLAN_PRE:
-    case PLAN_PRE_MIXED: plan_policy(c, a, amount, false); break;
-    case PLAN_POST: plan_policy(c, a, 0, true); break;
-    case PLAN_SPLIT:
-      c->resize_dir = 1;
-      c->resize_todo = amount;
-      break;
-    default:
-      c->resize_dir = -1;
-      c->resize_todo = amount;
-      break;
-  }
+  const Plan p = plan_of(a, mode, amount, c->n_buckets, c->live, c->initial_buckets);
+  c->resize_dir = p.dir;
+  c->resize_todo = p.todo;
   plan_next(c);
 }
 
-// Insert operations of a mixed batch, for its pre-batch plan: one add per
-// block to Ctl::plan_inserts, which the plan kernel reads and clears.
-__global__ __launch_bounds__(BLOCK) void count_inserts_kernel(Ctl *c, const uint8_t *ops, uint64_t n) {
-  __shared__ unsigned long long block_sum;
-  if (threadIdx.x == 0) block_sum = 0;
-  __syncthreads();
-  unsigned long long mine = 0;
-  for (uint64_t i = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (uint64_t)gridDim.x * BLOCK)
-    mine += ops[i] == OP_INSERT;
-  mine = wave_sum64(mine);
-  if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&block_sum, mine);
-  __syncthreads();
-  if (threadIdx.x == 0 && block_sum) add64(&c->plan_inserts, block_sum);
-}
-
-// A mixed batch's insert count and the plan in one block (batches of at most
-// BLOCK * 16 operations: one launch fewer).
-__global__ __launch_bounds__(BLOCK) void count_and_plan_kernel(ResizeArgs a, const uint8_t *ops, uint64_t n) {
-  __shared__ unsigned long long block_sum;
-  if (threadIdx.x == 0) block_sum = 0;
-  __syncthreads();
-  unsigned long long mine = 0;
-  for (uint64_t i = threadIdx.x; i < n; i += BLOCK) mine += ops[i] == OP_INSERT;
-  mine = wave_sum64(mine);
-  if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&block_sum, mine);
-  __syncthreads();
-  if (threadIdx.x == 0) plan_start(a.ctl, a, PLAN_PRE_MIXED, block_sum);
-}
-
-__global__ void resize_plan_kernel(ResizeArgs a, uint32_t mode, uint64_t amount) {
-  uint64_t n = amount;
-  if (mode == PLAN_PRE_MIXED) {
-    n = ld_ctl(&a.ctl->plan_inserts);
-    __hip_atomic_store(&a.ctl->plan_inserts, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Insert operations of a mixed batch, for its pre-batch plan: NSHARD blocks,
+// each leaves its count in its shard (overwritten by the next batch's).
+__global__ __launch_bounds__(1024) void count_inserts_kernel(Ctl *c, const uint8_t *ops, uint64_t n) {
+  __shared__ uint32_t part[16];
+  uint32_t mine = 0;
+  const uint64_t per = (n + NSHARD - 1) / NSHARD, b = (uint64_t)blockIdx.x * per, e = min(b + per, n);
+  for (uint64_t i = b + threadIdx.x; i < e; i += 8 * 1024) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) mine += (i + j * 1024 < e && ops[i + j * 1024] == OP_INSERT) ? 1u : 0u;
   }
-  plan_start(a.ctl, a, mode, n);
+  const uint64_t sum = wave_sum64(mine);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = (uint32_t)sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint64_t total = 0;
+    for (int w = 0; w < 16; ++w) total += part[w];
+    __hip_atomic_store(&shard_of(c, blockIdx.x)->plan_inserts, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
 // Ticket for "the last block of this launch": every block has finished its
@@ -2083,6 +2086,17 @@ __device__ __forceinline__ bool last_block(Ctl *c) {
   return last;
 }
 
+__device__ __forceinline__ void evict_finish(Ctl *c, bool items) {
+  if (items) {
+    // this thread's counter updates are done before its block is counted
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (!last_block(c)) return;
+  } else if (blockIdx.x != 0) {
+    return;
+  }
+  if (threadIdx.x < 64) (void)fold_shards_wave(c, true);
+}
+
 __device__ __forceinline__ uint32_t nth_set_bit(uint64_t m, uint32_t r) {
   for (uint32_t i = 0; i < r; ++i) m &= m - 1;
   return (uint32_t)__builtin_ctzll(m);
@@ -2109,6 +2123,13 @@ __device__ __forceinline__ void split_pair(const ResizeArgs &a, uint64_t im, uin
     a.buckets[dst * S + rank] = w;
     a.buckets[src * S + sl] = EMPTY;
   }
+}
+
+// State word of a merge phase over n pairs (1: test, 2: move; 0: none left):
+// at most two runs of pairs per block of merge_kernel.
+constexpr uint64_t M28 = (1ull << 28) - 1;
+__device__ __forceinline__ uint64_t merge_phase(uint64_t kind, uint64_t n) {
+  return n ? (kind << 56) | (min(n, (uint64_t)(2 * MERGE_GRID)) << 28) : 0;
 }
 
 // Merge pair j of the segment, walked from the top: (lo, lo + 2^m) with
@@ -2162,48 +2183,10 @@ __device__ __forceinline__ void merge_segment_done(volatile Ctl *c, uint64_t sp,
   plan_next(c);
 }
 
-// Pass 1: split the segment's pairs, or test merge pairs.
-template <int S>
-__global__ __launch_bounds__(BLOCK) void resize_pass1_kernel(ResizeArgs a) {
-  using T = Traits<S>;
-  Ctl *c = a.ctl;
-  const uint64_t seg = c->seg;
-  if (seg == 0) return;  // same value in every block: nobody takes a ticket
-  const int64_t dir = c->resize_dir;
-  const uint64_t im = c->im, sp = c->sp;
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int g = lane / S, sl = lane % S;
-  const uint64_t groups = (uint64_t)gridDim.x * WAVES * T::G;
-  for (uint64_t j = ((uint64_t)blockIdx.x * WAVES + wv) * T::G + g; j < seg; j += groups) {
-    if (dir > 0)
-      split_pair<S>(a, im, sp, j, g, sl);
-    else
-      merge_test_pair<S>(a, c, im, sp, j, g, sl);
-  }
-  if (dir > 0 && last_block(c) && threadIdx.x == 0) split_segment_done(c, sp, seg);
-}
-
-// Pass 2: move the merge pairs that fit, top down.
-template <int S>
-__global__ __launch_bounds__(BLOCK) void resize_pass2_kernel(ResizeArgs a) {
-  using T = Traits<S>;
-  Ctl *c = a.ctl;
-  const uint64_t seg = c->seg;
-  if (seg == 0 || c->resize_dir > 0) return;
-  const uint64_t commit = c->merge_commit;
-  const uint64_t im = c->im, sp = c->sp;
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int g = lane / S, sl = lane % S;
-  const uint64_t groups = (uint64_t)gridDim.x * WAVES * T::G;
-  for (uint64_t j = ((uint64_t)blockIdx.x * WAVES + wv) * T::G + g; j < commit; j += groups)
-    merge_move_pair<S>(a, im, sp, j, g, sl);
-  if (last_block(c) && threadIdx.x == 0) merge_segment_done(c, sp, seg, commit);
-}
-
 // After splits: every stash and pending entry moves to the eviction worklist
 // (the eviction phase re-places it under the new geometry) and the hint bits
-// are cleared (Section III-B "Overflow Stash").  One wave-aggregated append
-// per wave and item range; `t` indexes stash words (the whole table, which
+// are cleared (Section III-B "Overflow Stash").  The executor's drain chunks
+// make one wave-aggregated append per wave and item range; `t` indexes stash words (the whole table, which
 // is reset to EMPTY on the way) then pending entries, and the 256-entry tile
 // t / 256 picks the worklist segment.
 __device__ __forceinline__ uint64_t drain_word(uint64_t t, uint64_t n_stash_words, uint64_t total,
@@ -2239,17 +2222,21 @@ __device__ __forceinline__ void drain_done(volatile Ctl *c) {
   c->split_happened = 0;
 }
 
-__global__ __launch_bounds__(BLOCK) void drain_kernel(uint64_t *stash, uint64_t stash_cap, uint64_t *pending,
-                                                      uint64_t pending_cap, uint32_t *hint, uint64_t hint_n,
-                                                      uint64_t *wl, uint64_t seg_cap, Ctl *c) {
-  if (!c->split_happened) return;
-  const uint64_t n_stash = min(c->stash_count, stash_cap) ? stash_slots_for(stash_cap) : 0;
-  const uint64_t n_pend = min(c->pending_count, pending_cap);
+struct DrainArgs {
+  uint64_t *stash, *pending, *wl;
+  uint64_t stash_cap, pending_cap, wl_seg_cap, hint_words;
+};
+
+// The whole grid's drain: hint bits cleared, stash words reset, live entries
+// appended to the worklist.  Every thread calls it.
+__device__ __forceinline__ void drain_all(const DrainArgs &d, uint32_t *hint, Ctl *c) {
+  const uint64_t n_stash = min(ld_ctl(&c->stash_count), d.stash_cap) ? stash_slots_for(d.stash_cap) : 0;
+  const uint64_t n_pend = min(ld_ctl(&c->pending_count), d.pending_cap);
   const uint64_t total = n_stash + n_pend;
   const uint64_t stride = (uint64_t)gridDim.x * BLOCK;
   const uint64_t tid = (uint64_t)blockIdx.x * BLOCK + threadIdx.x;
   if (total) {
-    for (uint64_t t = tid; t < hint_n; t += stride) hint[t] = 0u;
+    for (uint64_t t = tid; t < d.hint_words; t += stride) hint[t] = 0u;
   }
   // A trip of a block takes DRAIN_WORDS tiles of 256 words that share one
   // worklist segment (tiles T, T + NSHARD, ...: word t is in tile t / 256,
@@ -2269,12 +2256,12 @@ __global__ __launch_bounds__(BLOCK) void drain_kernel(uint64_t *stash, uint64_t 
     uint64_t w[DRAIN_WORDS];
 #pragma unroll
     for (int j = 0; j < DRAIN_WORDS; ++j)
-      w[j] = drain_word((tile0 + (uint64_t)j * NSHARD) * BLOCK + threadIdx.x, n_stash, total, stash, pending);
+      w[j] = drain_word((tile0 + (uint64_t)j * NSHARD) * BLOCK + threadIdx.x, n_stash, total, d.stash, d.pending);
     uint32_t mine = 0;
 #pragma unroll
     for (int j = 0; j < DRAIN_WORDS; ++j) {
       const uint64_t t = (tile0 + (uint64_t)j * NSHARD) * BLOCK + threadIdx.x;
-      if (t < n_stash && w[j] != EMPTY) stash[t] = EMPTY;
+      if (t < n_stash && w[j] != EMPTY) d.stash[t] = EMPTY;
       mine += (w[j] != TOMB && w[j] != EMPTY) ? 1u : 0u;
     }
     // block-wide exclusive prefix of the live counts
@@ -2294,14 +2281,225 @@ __global__ __launch_bounds__(BLOCK) void drain_kernel(uint64_t *stash, uint64_t 
     if (threadIdx.x == 0 && sum) s_base = wl_append(c, seg, sum);
     __syncthreads();
     if (sum) {
-      uint64_t pos = seg * seg_cap + s_base + before + incl - mine;
+      uint64_t pos = seg * d.wl_seg_cap + s_base + before + incl - mine;
 #pragma unroll
       for (int j = 0; j < DRAIN_WORDS; ++j)
-        if (w[j] != TOMB && w[j] != EMPTY) wl[pos++] = w[j];
+        if (w[j] != TOMB && w[j] != EMPTY) d.wl[pos++] = w[j];
     }
     __syncthreads();  // s_wave and s_base of the next trip
   }
-  if (last_block(c) && threadIdx.x == 0) drain_done(c);
+}
+
+// One resize call: the plan, every split it asks for and the stash drain, or
+// the first segment of its merges for merge_kernel.
+//
+// `drain`: entries of the stash and the pending list go to the worklist when
+// this call or an earlier one without a drain split buckets; a later eviction
+// launch places them.  Without it (a batch's growth before its probe launch,
+// where the stash has to stay searchable) they stay, and a new bucket takes
+// its ancestor's hint bit: the keys it may be a candidate of had the ancestor
+// as theirs.
+//
+// A split entry's way: in each round whose range holds its bucket, it stays
+// when one of its candidate hashes still addresses the bucket under the
+// round's next mask, otherwise it moves to the bucket's partner (Section
+// IV-C-1).  One round (the usual call) touches the buckets it splits; more
+// rounds, all of them.  Movers take the first slots of their new buckets,
+// which are EMPTY and which no other bucket's entries reach: a bucket b beyond
+// the old count has one ancestor, b without its top bits.
+template <int S>
+__global__ __launch_bounds__(BLOCK) void resize_kernel(ResizeArgs a, DrainArgs d, uint32_t mode, uint64_t amount,
+                                                       const uint8_t *ops, bool drain) {
+  using T = Traits<S>;
+  constexpr int MAX_ROUNDS = 34;
+  __shared__ uint64_t r_im[MAX_ROUNDS], r_sp[MAX_ROUNDS], r_seg[MAX_ROUNDS];
+  __shared__ uint64_t s_todo, s_im, s_sp, s_nb, s_ins;
+  __shared__ int64_t s_dir;
+  __shared__ uint32_t s_rounds, s_split_before;
+  Ctl *c = a.ctl;
+  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+  uint64_t inserts = 0;
+  if (mode == PLAN_PRE_MIXED && ops) {
+    // a small batch's inserts, counted by every block
+    if (tid == 0) s_ins = 0;
+    __syncthreads();
+    uint64_t mine = 0;
+    for (uint64_t i = tid; i < amount; i += BLOCK) mine += ops[i] == OP_INSERT;
+    mine = wave_sum64(mine);
+    if (lane == 0 && mine) atomicAdd((unsigned long long *)&s_ins, (unsigned long long)mine);
+    __syncthreads();
+    inserts = s_ins;
+  }
+  if (tid < NSHARD) {
+    // key-count changes that are still in the shards, and the count of a
+    // larger batch's inserts
+    const Shard *sh = shard_of(c, tid);
+    const uint64_t dl = wave_sum64(ld_ctl(&sh->live));
+    if (mode == PLAN_PRE_MIXED && !ops) inserts = wave_sum64(ld_ctl(&sh->plan_inserts));
+    if (tid == 0) {
+      const uint64_t nb = ld_ctl(&c->n_buckets), max_b = ld_ctl(&c->max_buckets);
+      uint64_t im = ld_ctl(&c->im), sp = ld_ctl(&c->sp);
+      const Plan p = plan_of(a, mode, mode == PLAN_PRE_MIXED ? inserts : amount, nb, ld_ctl(&c->live) + dl,
+                             ld_ctl(&c->initial_buckets));
+      uint64_t todo = p.dir > 0 ? min(p.todo, max_b - nb) : p.todo, left = todo;
+      uint32_t rounds = 0;
+      if (p.dir > 0) {
+        while (left > 0) {
+          if (sp == im + 1) {
+            im = 2 * im + 1;
+            sp = 0;
+          }
+          const uint64_t seg = min(left, im + 1 - sp);
+          r_im[rounds] = im;
+          r_sp[rounds] = sp;
+          r_seg[rounds] = seg;
+          ++rounds;
+          sp += seg;
+          left -= seg;
+        }
+      }
+      s_dir = todo ? p.dir : 0;
+      s_todo = todo;
+      s_im = im;
+      s_sp = sp;
+      s_nb = nb;
+      s_rounds = rounds;
+      s_split_before = ld_ctl(&c->split_happened) != 0;
+    }
+  }
+  __syncthreads();
+  const int64_t dir = s_dir;
+  const uint64_t todo = s_todo, nb = s_nb;
+  const bool draining = drain && (dir > 0 || s_split_before);
+  if (dir == 0 && !draining) return;  // the same in every block: nobody takes a ticket
+  if (dir > 0) {
+    const uint32_t rounds = s_rounds;
+    const int g = lane / S, sl = lane % S;
+    const uint64_t first = rounds == 1 ? r_sp[0] : 0, count = rounds == 1 ? r_seg[0] : nb;
+    const uint64_t groups = (uint64_t)gridDim.x * WAVES * T::G;
+    // a uniform trip count per wave: the shuffles below take every lane
+    for (uint64_t j0 = ((uint64_t)blockIdx.x * WAVES + wv) * T::G; j0 < count; j0 += groups) {
+      const uint64_t src = first + j0 + g;
+      const bool have = j0 + g < count;
+      const uint64_t w = have ? a.buckets[src * S + sl] : EMPTY;
+      uint64_t b = src;
+      if (w != EMPTY) {
+        const uint32_t h1 = bithash1(key_of(w)), h2 = bithash2(key_of(w));
+        for (uint32_t r = 0; r < rounds; ++r) {
+          const uint64_t im = r_im[r], next = 2 * im + 1;
+          if (b - r_sp[r] >= r_seg[r]) continue;  // not split in this round (b below the range wraps)
+          const bool stay = ((h1 & im) == b && (h1 & next) == b) || ((h2 & im) == b && (h2 & next) == b);
+          if (!stay) b += im + 1;
+        }
+      }
+      const bool move = b != src;
+      const uint64_t mm = (ballot(move) >> (g * S)) & T::FULL;
+      uint32_t rank = (uint32_t)__builtin_popcountll(mm & ((1ull << sl) - 1ull));
+      if (rounds > 1 && ballot(move)) {
+        rank = 0;
+        for (int t = 0; t < S; ++t) {
+          const uint32_t o = (uint32_t)__shfl((int)(uint32_t)b, g * S + t, 64);
+          if (t < sl && ((mm >> t) & 1ull) && o == (uint32_t)b) ++rank;
+        }
+      }
+      if (move) {
+        a.buckets[b * S + rank] = w;
+        a.buckets[src * S + sl] = EMPTY;
+      }
+    }
+    if (!draining) {
+      const uint64_t stride = (uint64_t)gridDim.x * BLOCK;
+      for (uint64_t f = nb + (uint64_t)blockIdx.x * BLOCK + tid; f < nb + todo; f += stride) {
+        uint64_t anc = f;
+        while (anc >= nb) anc ^= 1ull << (63 - __builtin_clzll(anc));
+        if ((a.hint[anc >> 5] >> (anc & 31)) & 1u) set_hint(a.hint, (uint32_t)f);
+      }
+    }
+  }
+  if (draining) drain_all(d, a.hint, c);
+  if (last_block(c) && tid == 0) {
+    volatile Ctl *v = c;
+    if (draining) drain_done(v);
+    if (dir > 0) {
+      v->n_buckets = nb + todo;
+      v->im = s_im;
+      v->sp = s_sp;
+      if (!draining) v->split_happened = 1;
+    } else if (dir < 0) {
+      v->resize_dir = -1;
+      v->resize_todo = todo;
+      plan_next(v);
+      v->merge_done = 0;
+      v->merge_state = merge_phase(1, v->seg);
+    }
+  }
+}
+
+// A contraction (Section IV-C-2): per hashing round, every pair of the
+// segment is tested, top down, then the pairs above the first that does not
+// fit are moved.  The phases run within one launch: blocks claim runs of pairs
+// of the current phase by an atomic on one word, and the block that completes
+// a phase publishes the next.  A block waits only for runs that other running
+// blocks have claimed, so the launch ends however few blocks run at a time.
+template <int S>
+__global__ __launch_bounds__(BLOCK) void merge_kernel(ResizeArgs a) {
+  using T = Traits<S>;
+  __shared__ uint64_t s_state, s_mine;
+  Ctl *c = a.ctl;
+  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+  const int g = lane / S, sl = lane % S;
+  for (;;) {
+    if (tid == 0) {
+      uint64_t st = ld_ctl(&c->merge_state);
+      uint64_t mine = ~0ull;
+      if ((st >> 56) != 0 && (st & M28) < ((st >> 28) & M28)) {
+        st = add64(&c->merge_state, 1);
+        if ((st >> 56) != 0 && (st & M28) < ((st >> 28) & M28)) mine = st & M28;
+      }
+      s_state = st;
+      s_mine = mine;
+    }
+    __syncthreads();
+    const uint64_t st = s_state, mine = s_mine;
+    __syncthreads();
+    if ((st >> 56) == 0) return;
+    if (mine == ~0ull) {  // all claimed: other blocks are at work on them
+      __builtin_amdgcn_s_sleep(7);
+      continue;
+    }
+    // the moves of the phase before, made on other XCDs
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    const bool test = (st >> 56) == 1;
+    const uint64_t nch = (st >> 28) & M28, im = ld_ctl(&c->im), sp = ld_ctl(&c->sp);
+    const uint64_t pairs = test ? ld_ctl(&c->seg) : ld_ctl(&c->merge_commit);
+    const uint64_t per = (pairs + nch - 1) / nch, end = min(pairs, (mine + 1) * per);
+    for (uint64_t j = mine * per + (uint64_t)wv * T::G + g; j < end; j += (uint64_t)WAVES * T::G) {
+      if (test)
+        merge_test_pair<S>(a, c, im, sp, j, g, sl);
+      else
+        merge_move_pair<S>(a, im, sp, j, g, sl);
+    }
+    __syncthreads();
+    if (tid == 0) {
+      __threadfence();  // every wave's moves and tests (the barrier waits for them) before the count
+      if (add64(&c->merge_done, 1) + 1 == nch) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        volatile Ctl *v = c;
+        const uint64_t seg = ld_ctl(&c->seg), commit = ld_ctl(&c->merge_commit);
+        v->merge_done = 0;
+        uint64_t next = 0;
+        if (test && commit > 0) {
+          next = merge_phase(2, commit);
+        } else {
+          merge_segment_done(v, sp, seg, commit);
+          if (v->seg > 0) next = merge_phase(1, v->seg);
+        }
+        __threadfence();
+        __hip_atomic_store(&c->merge_state, next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    __syncthreads();
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2473,7 +2671,6 @@ enum : uint32_t {
 constexpr uint64_t FILL_PER_CHUNK = BLOCK * 64;   // words per fill chunk
 constexpr uint64_t COUNT_PER_CHUNK = BLOCK * 16;  // operations per count chunk
 constexpr uint64_t DRAIN_TILES = 16;              // stash tiles of BLOCK words per drain chunk
-constexpr uint64_t M28 = (1ull << 28) - 1;
 constexpr uint32_t DRAIN_WINDOW = 64;             // batches scanned for work
 
 struct TableDesc {
@@ -3403,7 +3600,10 @@ __global__ __launch_bounds__(BLOCK) void set_evict_kernel(SetArgs a) {
   __shared__ uint64_t pre[NSHARD + 1];
   wl_prefix(a.ctl, pre);
   const uint64_t cnt = pre[NSHARD];
-  if (cnt == 0) return;
+  if (cnt == 0) {
+    evict_finish(a.ctl, false);
+    return;
+  }
   const Geo geo = read_geo(a.ctl);
   const bool unreserved = ld_ctl(&a.ctl->stash_count) + cnt <= a.stash_cap;
   const int lane = threadIdx.x & 63;
@@ -3479,6 +3679,7 @@ __global__ __launch_bounds__(BLOCK) void set_evict_kernel(SetArgs a) {
     if (fr && unreserved) add64(&sh->stash_unreserved, fr);
     if (sd >> 32) add64(&sh->pending_inserts, sd >> 32);
   }
+  evict_finish(a.ctl, true);
 }
 
 }  // namespace hive
@@ -3843,28 +4044,10 @@ static void launch_evict(hive_table *h, uint64_t max_items, hipStream_t st, bool
   }
 }
 
-// Fold the shards into the totals and empty the worklist.
+// Fold the shards into the totals (batches without inserts; an eviction
+// launch folds by itself).
 static void launch_finish(hive_table *h, hipStream_t st) {
   hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(64), 0, st, h->d_ctl);
-}
-
-// Upper bound on the hashing rounds one resize call can cross: from the
-// initial bucket count to the arena size, plus the partial rounds at both
-// ends.
-static int resize_rounds(const hive_table *h) {
-  int r = 2;
-  for (uint64_t x = h->initial_buckets; x < h->max_buckets; x *= 2) ++r;
-  return r;
-}
-
-// merges: the call may contract (pass 2 moves merge pairs; a split-only call
-// skips its launches, which would find nothing to do)
-template <int S>
-static void launch_resize_passes(const ResizeArgs &ra, int rounds, bool merges, hipStream_t st) {
-  for (int r = 0; r < rounds; ++r) {
-    hipLaunchKernelGGL(resize_pass1_kernel<S>, dim3(RESIZE_GRID), dim3(BLOCK), 0, st, ra);
-    if (merges) hipLaunchKernelGGL(resize_pass2_kernel<S>, dim3(RESIZE_GRID), dim3(BLOCK), 0, st, ra);
-  }
 }
 
 // Phase timing: close the open span (if any) at an event recorded now on
@@ -3889,36 +4072,49 @@ static void phase_mark(hive_table *h, int kind, hipStream_t st) {
   h->open_ev = e;
 }
 
+// A resize call's launches up to its eviction launch: the plan with its splits
+// and (drain) the stash's entries to the worklist, then the merges where the
+// call may contract.
+static void launch_resize(hive_table *h, uint32_t mode, uint64_t amount, const uint8_t *d_ops, bool drain,
+                          hipStream_t st) {
+  const ResizeArgs ra{h->d_buckets, h->d_hint, h->d_ctl, h->S, h->cfg.resize_k, h->cfg.lf_expand_pct,
+                      h->cfg.lf_contract_pct};
+  const DrainArgs da{h->d_stash, h->d_pending, h->d_wl, h->stash_cap, h->pending_cap, h->wl_seg_cap,
+                     hint_words(h->max_buckets)};
+  if (mode == PLAN_PRE_MIXED && amount > BLOCK * 16ull) {
+    hipLaunchKernelGGL(count_inserts_kernel, dim3(NSHARD), dim3(1024), 0, st, h->d_ctl, d_ops, amount);
+    d_ops = nullptr;  // counted
+  }
+  // blocks for the largest split or drain the table can ask for
+  const uint64_t work = std::max(h->max_buckets * h->S, drain ? drain_words(h) : 0);
+  const dim3 grid(grid_for(work, BLOCK * 4ull, RESIZE_GRID));
+  const bool merges = mode == PLAN_POST || mode == PLAN_MERGE;
+  switch (h->S) {
+    case 16:
+      hipLaunchKernelGGL(resize_kernel<16>, grid, dim3(BLOCK), 0, st, ra, da, mode, amount, d_ops, drain);
+      if (merges) hipLaunchKernelGGL(merge_kernel<16>, dim3(MERGE_GRID), dim3(BLOCK), 0, st, ra);
+      break;
+    case 32:
+      hipLaunchKernelGGL(resize_kernel<32>, grid, dim3(BLOCK), 0, st, ra, da, mode, amount, d_ops, drain);
+      if (merges) hipLaunchKernelGGL(merge_kernel<32>, dim3(MERGE_GRID), dim3(BLOCK), 0, st, ra);
+      break;
+    default:
+      hipLaunchKernelGGL(resize_kernel<64>, grid, dim3(BLOCK), 0, st, ra, da, mode, amount, d_ops, drain);
+      if (merges) hipLaunchKernelGGL(merge_kernel<64>, dim3(MERGE_GRID), dim3(BLOCK), 0, st, ra);
+      break;
+  }
+}
+
 // batch_items > 0: the call follows a batch's probe launch whose eviction
 // worklist (at most batch_items entries) is still to be placed; the
 // drained stash joins it and one eviction launch places both.
 static hive_status resize_sequence(hive_table *h, uint32_t mode, uint64_t amount, const uint8_t *d_ops,
                                    hipStream_t st, uint64_t batch_items = 0) {
-  ResizeArgs ra{h->d_buckets, h->d_hint, h->d_ctl, h->S, h->cfg.resize_k, h->cfg.lf_expand_pct,
-                h->cfg.lf_contract_pct};
   phase_mark(h, HIVE_PHASE_RESIZE, st);
-  if (mode == PLAN_PRE_MIXED && amount <= BLOCK * 16ull) {
-    hipLaunchKernelGGL(count_and_plan_kernel, dim3(1), dim3(BLOCK), 0, st, ra, d_ops, amount);
-  } else {
-    if (mode == PLAN_PRE_MIXED)
-      hipLaunchKernelGGL(count_inserts_kernel, dim3(grid_for(amount, BLOCK * 16ull, 1024)), dim3(BLOCK), 0, st,
-                         h->d_ctl, d_ops, amount);
-    hipLaunchKernelGGL(resize_plan_kernel, dim3(1), dim3(1), 0, st, ra, mode, amount);
-  }
-  const int rounds = resize_rounds(h);
-  // pre-batch growth and explicit splits never merge
-  const bool merges = mode == PLAN_POST || mode == PLAN_MERGE;
-  switch (h->S) {
-    case 16: launch_resize_passes<16>(ra, rounds, merges, st); break;
-    case 32: launch_resize_passes<32>(ra, rounds, merges, st); break;
-    default: launch_resize_passes<64>(ra, rounds, merges, st); break;
-  }
+  launch_resize(h, mode, amount, d_ops, true, st);
   phase_mark(h, HIVE_PHASE_DRAIN, st);
-  hipLaunchKernelGGL(drain_kernel, dim3(DRAIN_GRID), dim3(BLOCK), 0, st, h->d_stash, h->stash_cap, h->d_pending,
-                     h->pending_cap, h->d_hint, hint_words(h->max_buckets), h->d_wl, h->wl_seg_cap, h->d_ctl);
   // live entries of a drain (and the batch's worklist)
   launch_evict(h, batch_items + h->stash_cap + h->pending_cap, st, false, batch_items > 0);
-  launch_finish(h, st);
   return launch_check();
 }
 
@@ -4100,15 +4296,17 @@ static hive_status run_batch(hive_t h, uint32_t mode, const uint8_t *d_ops, cons
   const bool dedupe = !(flags & HIVE_UNIQUE) && mode != OP_LOOKUP;
   const bool linear = h->cfg.addressing == HIVE_LINEAR;
   const bool inserts = mode == OP_INSERT || mode == OP_MIXED;
-  // A batch with inserts on a table with the post-batch rule places its
-  // eviction worklist after the rule: the splits' stash drain joins the
-  // worklist and one eviction launch places both (the re-placement launch
-  // goes).  The worklist then holds the batch's entries and a full drain.
+  // A batch with inserts on a table with a load-factor rule places its
+  // eviction worklist after the rules: the stash that the splits drain (of
+  // the growth before the batch, too) joins the worklist and one eviction
+  // launch places both.  The worklist then holds the batch's entries and a
+  // full drain.
   const uint64_t wl_post = n + drain_words(h) + WL_SLACK;
-  const bool post_after = linear && h->cfg.post_policy && inserts && h->entry_bytes == 8 && !h->timing &&
+  const bool rules = linear && (h->cfg.post_policy || h->cfg.pre_expand);
+  const bool place_last = rules && inserts && h->entry_bytes == 8 && !h->timing &&
                           (!no_alloc || wl_post <= h->wl_cap);
   // only inserts reach the eviction worklist
-  const uint64_t wl_need = inserts ? (post_after ? wl_post : n) : 0;
+  const uint64_t wl_need = inserts ? (place_last ? wl_post : n) : 0;
   uint64_t *dd = nullptr;
   if (no_alloc) {
     if (wl_need > h->wl_cap) {
@@ -4179,17 +4377,18 @@ static hive_status run_batch(hive_t h, uint32_t mode, const uint8_t *d_ops, cons
     if (mode == OP_INSERT || mode == OP_MIXED) {
       phase_mark(h, HIVE_PHASE_EVICT, st);
       hipLaunchKernelGGL(set_evict_kernel, dim3(grid_for(n, BLOCK, EVICT_GRID)), dim3(BLOCK), 0, st, sa);
-    }
-    if (mode != OP_LOOKUP) {
+    } else if (mode != OP_LOOKUP) {
       phase_mark(h, HIVE_PHASE_FINISH, st);
       launch_finish(h, st);
     }
     phase_mark(h, -1, st);
     return launch_check();
   }
-  if (linear && h->cfg.pre_expand && (mode == OP_INSERT || mode == OP_MIXED)) {
+  if (linear && h->cfg.pre_expand && inserts) {
     // grow before the batch so that live + (inserts of the batch) fits
-    if ((s = resize_sequence(h, mode == OP_MIXED ? PLAN_PRE_MIXED : PLAN_PRE, n, d_ops, st)) != HIVE_OK) return s;
+    const uint32_t pre = mode == OP_MIXED ? PLAN_PRE_MIXED : PLAN_PRE;
+    if (place_last) launch_resize(h, pre, n, d_ops, false, st);
+    else if ((s = resize_sequence(h, pre, n, d_ops, st)) != HIVE_OK) return s;
   }
   phase_mark(h, HIVE_PHASE_PROBE, st);
   switch (h->S) {
@@ -4209,24 +4408,23 @@ static hive_status run_batch(hive_t h, uint32_t mode, const uint8_t *d_ops, cons
     default: launch_ops_mode<64, false>(mode, a, h->cfg, st); break;
   }
   if ((s = launch_check()) != HIVE_OK) return s;
-  if (post_after) {
-    hipLaunchKernelGGL(fold_kernel, dim3(1), dim3(64), 0, st, h->d_ctl);
-    if ((s = resize_sequence(h, PLAN_POST, 0, nullptr, st, n)) != HIVE_OK) return s;
+  const bool post = linear && h->cfg.post_policy && mode != OP_LOOKUP;
+  if (place_last) {
+    if ((s = resize_sequence(h, post ? PLAN_POST : PLAN_NONE, 0, nullptr, st, n)) != HIVE_OK) return s;
     phase_mark(h, -1, st);
     return HIVE_OK;
   }
-  if (mode == OP_INSERT || mode == OP_MIXED) {
+  if (inserts) {
     phase_mark(h, HIVE_PHASE_EVICT, st);
     launch_evict(h, n, st, h->timing);
   }
-  if (mode != OP_LOOKUP) {
+  // the eviction launch folds, that of the post-batch rule too
+  if (h->timing ? mode != OP_LOOKUP : (mode == OP_DELETE && !post)) {
     phase_mark(h, HIVE_PHASE_FINISH, st);
     launch_finish(h, st);
   }
   if ((s = launch_check()) != HIVE_OK) return s;
-  if (linear && h->cfg.post_policy && mode != OP_LOOKUP) {
-    if ((s = resize_sequence(h, PLAN_POST, 0, nullptr, st)) != HIVE_OK) return s;
-  }
+  if (post && (s = resize_sequence(h, PLAN_POST, 0, nullptr, st)) != HIVE_OK) return s;
   phase_mark(h, -1, st);
   return HIVE_OK;
 }
@@ -4310,9 +4508,9 @@ hive_status hive_create(const hive_config *cfg_in, uint64_t initial_buckets, voi
   // the worklist must hold a full stash + pending drain (after a split);
   // the drain walks the whole stash table
   const uint64_t min_wl = drain_words(h);
-  // a table with the post-batch rule places a batch's worklist after the
-  // rule, together with the drain (see run_batch)
-  const uint64_t batch_wl = cfg.addressing == HIVE_LINEAR && cfg.post_policy && cfg.max_batch
+  // a table with a load-factor rule places a batch's worklist after the
+  // rules, together with the drain (see run_batch)
+  const uint64_t batch_wl = cfg.addressing == HIVE_LINEAR && (cfg.post_policy || cfg.pre_expand) && cfg.max_batch
                                 ? cfg.max_batch + min_wl + WL_SLACK
                                 : cfg.max_batch;
   if ((s = ensure_scratch(h, std::max<uint64_t>(batch_wl, min_wl), cfg.max_batch, st)) != HIVE_OK) {

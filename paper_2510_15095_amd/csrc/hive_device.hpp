@@ -72,8 +72,9 @@ struct alignas(128) Ctl {
   uint64_t split_happened; // a split ran since the last stash drain
   uint64_t initial_buckets;
   uint64_t max_buckets;
-  uint64_t plan_inserts;   // insert operations of a mixed batch, counted for its pre-batch plan
-  uint64_t pad2_[7];
+  uint64_t merge_state;    // merge_kernel: phase:8 | chunks:28 | claimed:28 (0: nothing to merge)
+  uint64_t merge_done;     // chunks of that phase completed
+  uint64_t pad2_[6];
   // line 3: maintenance kernels (dump, placement census)
   uint64_t dump_count;
   uint64_t place_first;
@@ -101,6 +102,7 @@ struct Shard {
   uint64_t stash_inserts;
   uint64_t pending_inserts;
   uint64_t stash_unreserved;  // stash placements of launches that needed no reservation
+  uint64_t plan_inserts;      // inserts of a mixed batch counted by block s of count_inserts_kernel
 };
 constexpr uint64_t CTL_BYTES = sizeof(Ctl) + NSHARD * SHARD_STRIDE;
 

@@ -183,3 +183,116 @@ def test_dedupe_beyond_four_million(H):
     assert np.array_equal(host(t.delete(dev(gone))), o.delete(gone))
     assert t.stats()["live"] == len(o)
     t.close()
+
+
+def _linear(H, S, nb, mb, **cfg):
+    return H.Table(nb, slots_per_bucket=S, addressing=H.HIVE_LINEAR, max_buckets=mb, **cfg)
+
+
+def _check_linear(t, o, S, nb0, mb, geo):
+    """Contents, key count, geometry (up to the equivalent form sp == im + 1)
+    and every entry in a candidate bucket of the oracle's addressing."""
+    st = t.stats()
+    assert st["n_buckets"] == geo and st["live"] == len(o), st
+    words, where = t.dump(with_where=True)
+    assert np.array_equal(words, o.dump())
+    o2 = oracle.O2(S, 8, 16, oracle.ADDR_LINEAR, nb0, max_buckets=mb)
+    o2.split(geo - nb0)
+    keys = (words & np.uint64(M32)).astype(np.uint32)[where >= 0]
+    c1, c2 = o2.candidates(keys)
+    w = where[where >= 0]
+    assert ((w == c1) | (w == c2)).all()
+    return st
+
+
+@pytest.mark.parametrize("S", [16, 64])
+@pytest.mark.parametrize("nb0,deltas", [(1, (1, 1, 2, 60, 4000)), (5, (3, 100, -70, 3000, -2500, 7)),
+                                        (1000, (24, 2000, -2900, 5000))])
+def test_resize_calls_over_several_rounds(H, S, nb0, deltas):
+    """hive_resize over one hashing round and over many, up and down: with
+    entries in the stash and the pending list, every key stays reachable and
+    in place.  A merge may stop at a pair that does not fit, never beyond
+    its target."""
+    mb = 1 << 13
+    n = nb0 * S + 40
+    case(f"resize rounds S={S} nb0={nb0} deltas={deltas}")
+    ks = wl.KeyStream(900 + nb0)
+    keys = ks.range(0, n)
+    t, o = _linear(H, S, nb0, mb, stash_capacity=16, pending_capacity=4096), oracle.O1()
+    t.insert(dev(keys), dev(wl.values_for(keys)), flags=H.HIVE_UNIQUE)
+    o.insert(keys, wl.values_for(keys))
+    nb = nb0
+    for d in deltas:
+        t.resize(d)
+        got = t.stats()["n_buckets"]
+        if d > 0:
+            assert got == min(mb, nb + d)
+        else:
+            assert max(nb0, nb + d) <= got <= nb
+        nb = got
+        _check_linear(t, o, S, nb0, mb, nb)
+        q = ks.range(0, 2 * n)
+        v, f = t.lookup(dev(q))
+        ov, of = o.lookup(q)
+        assert np.array_equal(host(f), of) and np.array_equal(host(v), ov)
+    t.close()
+
+
+@pytest.mark.parametrize("nb0,K,post", [(1, 1, 0), (8, 64, 0), (8, 5, 1), (100, 1000, 1)])
+def test_growth_before_a_batch_keeps_the_stash_searchable(H, nb0, K, post):
+    """Batches that replace, delete and look up stashed keys and, by their new
+    keys, grow the table first (over one round or several): the stash is
+    drained after the batch, so its entries must be found through the split."""
+    S, mb = 16, 1 << 12
+    case(f"growth with a stash nb0={nb0} K={K} post={post}")
+    ks = wl.KeyStream(950 + nb0 + post)
+    t = _linear(H, S, nb0, mb, pre_expand=1, post_policy=post, resize_k=K, lf_expand_pct=100 if not post else 97,
+                lf_contract_pct=10, max_evictions=0, stash_capacity=4096, pending_capacity=4096)
+    o = oracle.O1()
+    at = nb0 * S  # exactly full by the rule: many entries cannot be in their buckets
+    keys = ks.range(0, at)
+    t.insert(dev(keys), dev(wl.values_for(keys)), flags=H.HIVE_UNIQUE)
+    o.insert(keys, wl.values_for(keys))
+    rng = np.random.default_rng(nb0)
+    for b in range(5):
+        live = np.unique((o.dump() & np.uint64(M32)).astype(np.uint32))
+        perm = rng.permutation(live)
+        a, c = perm.size // 3, 2 * perm.size // 3
+        new = ks.range(at, at + nb0 * S * (1 + b % 2))
+        at += new.size
+        k = np.concatenate([perm[:a], new, perm[a:c], perm[c:]])
+        ops = np.concatenate([np.full(a + new.size, wl.OP_INSERT), np.full(c - a, wl.OP_DELETE),
+                              np.full(perm.size - c, wl.OP_LOOKUP)]).astype(np.uint8)
+        p = rng.permutation(k.size)
+        k, ops = k[p], ops[p]
+        vals = rng.integers(1, 1 << 32, k.size, dtype=np.uint64).astype(np.uint32)
+        v, f = t.mixed(dev(ops), dev(k), dev(vals))
+        ov, of = o.apply(ops, k, vals)
+        assert np.array_equal(host(f), of) and np.array_equal(host(v), ov), b
+        st = t.stats()
+        _check_linear(t, o, S, nb0, mb, st["n_buckets"])
+    t.close()
+
+
+def test_large_mixed_batch_counts_its_inserts(H):
+    """Beyond 4,096 operations a mixed batch's inserts are counted by a launch
+    of their own: growth by the rule on exactly that count, at odd sizes."""
+    S, nb0, mb = 16, 64, 1 << 14
+    ks = wl.KeyStream(970)
+    o2 = oracle.O2(S, 8, 4096, oracle.ADDR_LINEAR, nb0, max_buckets=mb, resize_k=16)
+    t = _linear(H, S, nb0, mb, pre_expand=1, resize_k=16)
+    at = 0
+    for n in (4096, 4097, 9001, 70_001):
+        case(f"mixed growth n={n}")
+        k = ks.range(at, at + n)
+        at += n
+        ops = np.where(np.arange(n) % 3 == 0, wl.OP_LOOKUP, wl.OP_INSERT).astype(np.uint8)
+        live = t.stats()["live"]
+        t.mixed(dev(ops), dev(k), dev(wl.values_for(k)))
+        need, nb = live + int((ops == wl.OP_INSERT).sum()), o2.stats()["n_buckets"]
+        while need * 100 > 90 * nb * S:
+            nb += 16
+        o2.split(nb - o2.stats()["n_buckets"])
+        st = t.stats()
+        assert st["n_buckets"] == nb and st["live"] == need, (n, st, nb)
+    t.close()
