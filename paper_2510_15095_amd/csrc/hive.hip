@@ -57,7 +57,8 @@ constexpr int BLOCK = 64 * WAVES;
 #endif
 constexpr int EVICT_GRID = 2048;  // most blocks of the eviction phase (all resident at once)
 constexpr int RESIZE_GRID = 1024; // most blocks of resize_kernel (they stride over buckets and stash words)
-constexpr int MERGE_GRID = 512;   // blocks of merge_kernel
+constexpr int MERGE_GRID = 256;   // blocks of merge_kernel, one per compute unit
+constexpr int MERGE_BLOCK = 512;
 // Most blocks of a probe launch: larger batches stride over tiles, about
 // eight tiles per block at 2^26 operations (bulk step +4% against one tile
 // per block, measured over 2,048 .. 65,536 blocks: the launch pays less
@@ -2126,21 +2127,27 @@ __device__ __forceinline__ void split_pair(const ResizeArgs &a, uint64_t im, uin
 }
 
 // State word of a merge phase over n pairs (1: test, 2: move; 0: none left):
-// at most two runs of pairs per block of merge_kernel.
+// at most one run of pairs per block of merge_kernel (a claim and a count of
+// each run are atomics on one address, about 64 ns each).
 constexpr uint64_t M28 = (1ull << 28) - 1;
 __device__ __forceinline__ uint64_t merge_phase(uint64_t kind, uint64_t n) {
-  return n ? (kind << 56) | (min(n, (uint64_t)(2 * MERGE_GRID)) << 28) : 0;
+  return n ? (kind << 56) | (min(n, (uint64_t)MERGE_GRID) << 28) : 0;
 }
 
 // Merge pair j of the segment, walked from the top: (lo, lo + 2^m) with
 // lo = sp - 1 - j.  It fits when hi's entries fit lo's EMPTY slots
 // (Section IV-C-2); the first pair that does not fit bounds the commit.
-template <int S>
+// FRESH: agent-scope loads and stores, for phases of one launch that read what
+// blocks of other XCDs wrote in the one before: no L2 write-back and no
+// invalidation is needed then (a fence pair per run of pairs made a
+// contraction take 551 us).
+template <int S, bool FRESH = false>
 __device__ __forceinline__ void merge_test_pair(const ResizeArgs &a, Ctl *c, uint64_t im, uint64_t sp, uint64_t j,
                                                 int g, int sl) {
   using T = Traits<S>;
   const uint64_t lo = sp - 1 - j, hi = lo + im + 1;
-  const uint64_t wl = a.buckets[lo * S + sl], wh = a.buckets[hi * S + sl];
+  const uint64_t wl = FRESH ? load_fresh(a.buckets + lo * S + sl) : a.buckets[lo * S + sl];
+  const uint64_t wh = FRESH ? load_fresh(a.buckets + hi * S + sl) : a.buckets[hi * S + sl];
   const uint64_t fl = (ballot(wl == EMPTY) >> (g * S)) & T::FULL;
   const uint64_t lh = (ballot(wh != EMPTY) >> (g * S)) & T::FULL;
   if (sl == 0 && __builtin_popcountll(lh) > __builtin_popcountll(fl))
@@ -2149,20 +2156,30 @@ __device__ __forceinline__ void merge_test_pair(const ResizeArgs &a, Ctl *c, uin
 
 // Move a merge pair that fits: the r-th live entry of hi goes to the r-th
 // EMPTY slot of lo; stash entries with a candidate in hi now address lo.
-template <int S>
+template <int S, bool FRESH = false>
 __device__ __forceinline__ void merge_move_pair(const ResizeArgs &a, uint64_t im, uint64_t sp, uint64_t j, int g,
                                                 int sl) {
   using T = Traits<S>;
   const uint64_t lo = sp - 1 - j, hi = lo + im + 1;
-  const uint64_t wl = a.buckets[lo * S + sl], wh = a.buckets[hi * S + sl];
+  const uint64_t wl = FRESH ? load_fresh(a.buckets + lo * S + sl) : a.buckets[lo * S + sl];
+  const uint64_t wh = FRESH ? load_fresh(a.buckets + hi * S + sl) : a.buckets[hi * S + sl];
   const uint64_t fl = (ballot(wl == EMPTY) >> (g * S)) & T::FULL;
   const uint64_t lh = (ballot(wh != EMPTY) >> (g * S)) & T::FULL;
   if (wh != EMPTY) {
     const uint32_t r = __builtin_popcountll(lh & ((1ull << sl) - 1ull));
-    a.buckets[lo * S + nth_set_bit(fl, r)] = wh;
-    a.buckets[hi * S + sl] = EMPTY;
+    uint64_t *to = a.buckets + lo * S + nth_set_bit(fl, r), *from = a.buckets + hi * S + sl;
+    if constexpr (FRESH) {
+      __hip_atomic_store(to, wh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(from, EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      *to = wh;
+      *from = EMPTY;
+    }
   }
-  if (sl == 0 && ((a.hint[hi >> 5] >> (hi & 31)) & 1u)) set_hint(a.hint, (uint32_t)lo);
+  if (sl == 0) {
+    const uint32_t word = FRESH ? ld_ctl32(a.hint + (hi >> 5)) : a.hint[hi >> 5];
+    if ((word >> (hi & 31)) & 1u) set_hint(a.hint, (uint32_t)lo);
+  }
 }
 
 // Geometry after a finished segment (run by one thread once every pair of
@@ -2442,7 +2459,7 @@ __global__ __launch_bounds__(BLOCK) void resize_kernel(ResizeArgs a, DrainArgs d
 // a phase publishes the next.  A block waits only for runs that other running
 // blocks have claimed, so the launch ends however few blocks run at a time.
 template <int S>
-__global__ __launch_bounds__(BLOCK) void merge_kernel(ResizeArgs a) {
+__global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(ResizeArgs a) {
   using T = Traits<S>;
   __shared__ uint64_t s_state, s_mine;
   Ctl *c = a.ctl;
@@ -2464,26 +2481,25 @@ __global__ __launch_bounds__(BLOCK) void merge_kernel(ResizeArgs a) {
     __syncthreads();
     if ((st >> 56) == 0) return;
     if (mine == ~0ull) {  // all claimed: other blocks are at work on them
-      __builtin_amdgcn_s_sleep(7);
+      __builtin_amdgcn_s_sleep(15);
       continue;
     }
-    // the moves of the phase before, made on other XCDs
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     const bool test = (st >> 56) == 1;
     const uint64_t nch = (st >> 28) & M28, im = ld_ctl(&c->im), sp = ld_ctl(&c->sp);
     const uint64_t pairs = test ? ld_ctl(&c->seg) : ld_ctl(&c->merge_commit);
     const uint64_t per = (pairs + nch - 1) / nch, end = min(pairs, (mine + 1) * per);
-    for (uint64_t j = mine * per + (uint64_t)wv * T::G + g; j < end; j += (uint64_t)WAVES * T::G) {
+    constexpr uint64_t STEP = (uint64_t)(MERGE_BLOCK / 64) * T::G;
+    for (uint64_t j = mine * per + (uint64_t)wv * T::G + g; j < end; j += STEP) {
       if (test)
-        merge_test_pair<S>(a, c, im, sp, j, g, sl);
+        merge_test_pair<S, true>(a, c, im, sp, j, g, sl);
       else
-        merge_move_pair<S>(a, im, sp, j, g, sl);
+        merge_move_pair<S, true>(a, im, sp, j, g, sl);
     }
+    // every wave's stores and minima are done before the run is counted
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid == 0) {
-      __threadfence();  // every wave's moves and tests (the barrier waits for them) before the count
       if (add64(&c->merge_done, 1) + 1 == nch) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         volatile Ctl *v = c;
         const uint64_t seg = ld_ctl(&c->seg), commit = ld_ctl(&c->merge_commit);
         v->merge_done = 0;
@@ -4092,15 +4108,15 @@ static void launch_resize(hive_table *h, uint32_t mode, uint64_t amount, const u
   switch (h->S) {
     case 16:
       hipLaunchKernelGGL(resize_kernel<16>, grid, dim3(BLOCK), 0, st, ra, da, mode, amount, d_ops, drain);
-      if (merges) hipLaunchKernelGGL(merge_kernel<16>, dim3(MERGE_GRID), dim3(BLOCK), 0, st, ra);
+      if (merges) hipLaunchKernelGGL(merge_kernel<16>, dim3(MERGE_GRID), dim3(MERGE_BLOCK), 0, st, ra);
       break;
     case 32:
       hipLaunchKernelGGL(resize_kernel<32>, grid, dim3(BLOCK), 0, st, ra, da, mode, amount, d_ops, drain);
-      if (merges) hipLaunchKernelGGL(merge_kernel<32>, dim3(MERGE_GRID), dim3(BLOCK), 0, st, ra);
+      if (merges) hipLaunchKernelGGL(merge_kernel<32>, dim3(MERGE_GRID), dim3(MERGE_BLOCK), 0, st, ra);
       break;
     default:
       hipLaunchKernelGGL(resize_kernel<64>, grid, dim3(BLOCK), 0, st, ra, da, mode, amount, d_ops, drain);
-      if (merges) hipLaunchKernelGGL(merge_kernel<64>, dim3(MERGE_GRID), dim3(BLOCK), 0, st, ra);
+      if (merges) hipLaunchKernelGGL(merge_kernel<64>, dim3(MERGE_GRID), dim3(MERGE_BLOCK), 0, st, ra);
       break;
   }
 }

@@ -73,13 +73,14 @@ struct alignas(128) Ctl {
   uint64_t initial_buckets;
   uint64_t max_buckets;
   uint64_t merge_state;    // merge_kernel: phase:8 | chunks:28 | claimed:28 (0: nothing to merge)
-  uint64_t merge_done;     // chunks of that phase completed
-  uint64_t pad2_[6];
-  // line 3: maintenance kernels (dump, placement census)
+  uint64_t pad2_[7];
+  // line 3: maintenance kernels (dump, placement census); runs of the current
+  // phase completed (merge_kernel: not on the line that waiting blocks poll)
   uint64_t dump_count;
   uint64_t place_first;
   uint64_t place_second;
-  uint64_t pad3_[13];
+  uint64_t merge_done;
+  uint64_t pad3_[12];
 };
 static_assert(sizeof(Ctl) == 512, "four lines");
 
