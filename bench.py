@@ -890,12 +890,15 @@ def run_bulk(args):
     ms_step = float(ms.sum(axis=1).mean())
 
     # roofline of the lookup kernel: algorithmic bytes per launch =
-    # hits * 128 * (1 + f_second) + misses * 256 (both candidates) + 9 B of I/O
-    # per operation (key in, value and found flag out)
+    # hits * 128 * (1 + f_second) + misses * 128 + 9 B of I/O per operation
+    # (key in, value and found flag out).  A miss has to touch its first
+    # candidate; the second is read only when its filter bit is set, which
+    # the count leaves out (with probe_both every miss touches both)
     def lookup_bytes(hits):
         misses = n - hits
         io = 5 if set32 else 9  # key in, (value and) found flag out
-        return hits * BUCKET_BYTES * (1 + frac_second) + misses * 2 * BUCKET_BYTES + io * n
+        miss = BUCKET_BYTES * (2 if args.probe_both else 1)
+        return hits * BUCKET_BYTES * (1 + frac_second) + misses * miss + io * n
     lk_ms = (ms[:, 2].mean() + ms[:, 4].mean()) / 2
     lk_bytes = (lookup_bytes(n_present) + lookup_bytes(n_present2)) / 2
     achieved = lk_bytes / (lk_ms * 1e-3) / 1e9

@@ -195,8 +195,72 @@ __global__ __launch_bounds__(64) void finish_kernel(Ctl *c) {
   (void)fold_shards_wave(c, true);
 }
 
+// ---------------------------------------------------------------------------
+// Spill filter and first-candidate placement (FIXED tables of two candidates
+// that are probed one after the other).
+//
+// A probe is bound by the 128-byte lines it reads, and a key that is absent,
+// or sits in its second candidate, costs two.  So a new key goes to its first
+// candidate while that has at least `first_min` EMPTY slots (only then to the
+// emptier of both), and every bucket b has 2^shift filter bits of its own:
+// whenever a key whose first candidate is b is put anywhere else (its second
+// candidate, the stash, the pending list), the bit that the key picks is set.
+// A search that finds nothing in the first candidate and whose bit is clear is
+// over: one line.  Bits are never cleared but with the table (a stale one
+// only costs the second probe that every miss took before).  While no entry
+// was ever deleted, a first candidate with first_min EMPTY slots always had
+// them, so none of its keys is elsewhere and the bits are not even read.
+//
+// Bulk build of 2^26 keys to 95% load, without / with: inserts 3.82 / 3.85 ms,
+// lookups at 50% and 25% hits 2.22 / 2.05 and 2.52 / 2.26, deletes 1.45 / 1.40;
+// 2^24 lookups in a table of 2^24 keys 543 / 425 us.  (A new key in its second
+// candidate costs an atomic on its bit; reading the filter for every insert
+// would add 0.5 ms.)
+//
+// first_min: more packs first candidates less tightly (fewer chains), less
+// leaves more keys in them.  At 16 slots and 95% load, two-choice / 5 / 3:
+// keys in their second candidate 33 / 16 / 14%, inserts that need eviction
+// 0.34 / 0.69 / 1.5%.  Tables with an eviction bound under FIRST_MIN_CHAIN
+// place by two-choice alone: without chains, packed first candidates would
+// send entries to the stash.
+// shift: 8 bits a bucket while the filter stays within FILTER_BYTES, so that
+// it is served by the L2s while bucket lines stream through them; at 95% load
+// a missing key finds its bit set with probability 0.74 / 0.59 / 0.41 / 0.25
+// for 1 / 2 / 4 / 8 bits.
+// LINEAR tables have none: their unsplit buckets are full, so that most bits
+// would be set, and splits would have to hand them on (growth to 12.6 M keys
+// and back 3,500 us without, 3,840 with; mixed batches the same either way).
+// ---------------------------------------------------------------------------
+constexpr uint32_t FIRST_MIN = 5;
+constexpr uint32_t FIRST_MIN_CHAIN = 4;
+constexpr uint64_t FILTER_BYTES = 5ull << 20;
+
+struct Spill {
+  uint32_t *bits;  // null: the table has no filter
+  uint32_t shift;
+  uint32_t first_min;
+};
+
+__device__ __forceinline__ uint64_t spill_bit(const Spill &f, uint32_t c1, uint32_t k) {
+  return ((uint64_t)c1 << f.shift) | (((k * 0x9E3779B1u) >> 29) & ((1u << f.shift) - 1u));
+}
+
+// Whether key k, whose first candidate is c1, may be elsewhere.
+__device__ __forceinline__ bool spill_test(const Spill &f, uint32_t c1, uint32_t k) {
+  const uint64_t t = spill_bit(f, c1, k);
+  return (f.bits[t >> 5] >> (t & 31)) & 1u;
+}
+
+// Key k, whose first candidate is c1, is being put elsewhere.
+__device__ __forceinline__ void spill_mark(const Spill &f, uint32_t c1, uint32_t k) {
+  if (!f.bits) return;
+  const uint64_t t = spill_bit(f, c1, k);
+  or32(&f.bits[t >> 5], 1u << (t & 31));
+}
+
 struct OpsArgs {
   uint64_t *buckets;
+  Spill spill;
   uint32_t *hint;
   uint64_t *stash;
   uint64_t *pending;
@@ -908,6 +972,7 @@ struct OpsShared {
 struct OpsView {
   Geo geo;
   uint64_t n_stash, n_pend;
+  bool removed;  // an entry may have been deleted since the table was empty
 };
 
 __device__ __forceinline__ OpsView read_view(const Ctl *c, uint64_t stash_cap, uint64_t pending_cap) {
@@ -915,6 +980,7 @@ __device__ __forceinline__ OpsView read_view(const Ctl *c, uint64_t stash_cap, u
   v.geo = read_geo(c);
   v.n_stash = min(ld_ctl(&c->stash_count), stash_cap);
   v.n_pend = min(ld_ctl(&c->pending_count), pending_cap);
+  v.removed = ld_ctl32(&c->removed) != 0;
   return v;
 }
 
@@ -928,6 +994,12 @@ __device__ __forceinline__ void ops_counts_add(Ctl *c, uint64_t unit, int64_t li
   }
 }
 
+// Entries may be deleted by this launch: later ones read the filter even where
+// a first candidate has room.
+__device__ __forceinline__ void set_removed(Ctl *c) {
+  __hip_atomic_store(&c->removed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // P1 for one tile of WAVES x 64 operations [tile * 256, tile * 256 + 256).
 // BOTH: probe both candidates in one round for every operation (inserts of
 // new keys always need both; for lookups and deletes it trades bytes for one
@@ -935,7 +1007,11 @@ __device__ __forceinline__ void ops_counts_add(Ctl *c, uint64_t unit, int64_t li
 // PAIR: the table's candidate hashes (HashPair); BitHash1/2 by default.
 // With three candidates (PAIR_TRIPLE) the third is probed in a third round
 // by the operations that found their key in neither of the first two.
-template <int S, uint32_t MODE, bool BOTH, int PAIR = PAIR_BITHASH, int PIPE = Traits<S>::CH>
+// FILTER: the table has a spill filter (FILTER_ASK: it may have one; the
+// executor, whose worker holds one copy of each kind of tile).
+enum : int { FILTER_NONE = 0, FILTER_USE = 1, FILTER_ASK = 2 };
+template <int S, uint32_t MODE, bool BOTH, int PAIR = PAIR_BITHASH, int PIPE = Traits<S>::CH,
+          int FILTER = FILTER_NONE>
 __device__ __forceinline__ void ops_tile(const OpsArgs &a, const OpsView &view, uint64_t tile,
                                          OpsShared<S, PairArity<PAIR>::D> &sh, int64_t &live_acc,
                                          uint64_t &bad_acc) {
@@ -985,10 +1061,15 @@ __device__ __forceinline__ void ops_tile(const OpsArgs &a, const OpsView &view, 
   s_b1[wv][lane] = c1;
   wave_lds_sync();
 
-  // Inserts of new keys need both candidates (absence check and two-choice
-  // placement), so insert batches probe both in one round; lookups and
-  // deletes probe the second candidate only after a miss in the first.
-  constexpr bool kFused = (MODE == OP_INSERT || BOTH) && (S == 16);
+  // The second candidate is probed after a miss in the first, with a filter
+  // by keys that may be there and by new keys whose first candidate is nearly
+  // full alone.  Without one inserts of new keys always need both (absence
+  // and two-choice placement) and take them in one round, as everything does
+  // with BOTH.
+  constexpr bool kFused = (BOTH || (MODE == OP_INSERT && FILTER != FILTER_USE)) && (S == 16);
+  // spilled: the key may be outside its first candidate; marked: its filter
+  // bit is known to be set
+  bool spilled = true, marked = false;
   Mask m1;
   bool need2;
   if constexpr (kFused) {
@@ -1007,6 +1088,19 @@ __device__ __forceinline__ void ops_tile(const OpsArgs &a, const OpsView &view, 
     wave_lds_sync();
     m1 = s_m[0][wv][lane];
     need2 = work && m1 == 0 && c2 != c1;
+    if constexpr (FILTER != FILTER_NONE && !D3) {
+      if (FILTER == FILTER_USE || a.spill.bits) {
+        // the filter is read by the lanes that missed alone, and after the
+        // round: read with it, by every lane, it cost more line reads than
+        // it saved (2^26 lookups at 50% hits 2.21 ms, against 2.05 so and
+        // 2.22 without a filter)
+        const bool near_full = (uint32_t)popc_mask(s_e[0][wv][lane]) < a.spill.first_min;
+        marked = work && m1 == 0 && (near_full || MODE == OP_MIXED || MODE == OP_DELETE || view.removed) &&
+                 spill_test(a.spill, c1, k);
+        spilled = marked;
+        need2 = need2 && (spilled || (op == OP_INSERT && near_full));
+      }
+    }
     const uint64_t need2_mask = ballot(need2);
     const int n2 = __popcll(need2_mask);
     compact_second(need2, need2_mask, n2, k, c2, c1, lane, s_k2[wv], s_b2[wv], s_list[wv]);
@@ -1061,7 +1155,7 @@ __device__ __forceinline__ void ops_tile(const OpsArgs &a, const OpsView &view, 
       slot = a.buckets + (uint64_t)c3 * S + ctz_mask(m3);
       word = s_w[D3 ? 2 : 0][wv][lane];
       in_bucket = true;
-    } else if (overflow_used && (hinted(a.hint, c1, c2) || (D3 && hinted(a.hint, c3, c3)))) {
+    } else if (overflow_used && spilled && (hinted(a.hint, c1, c2) || (D3 && hinted(a.hint, c3, c3)))) {
       slot = overflow_find(a.stash, a.stash_cap, n_stash, a.pending, n_pend, k, &word, false);
     }
     if (op == OP_LOOKUP) {
@@ -1103,14 +1197,17 @@ __device__ __forceinline__ void ops_tile(const OpsArgs &a, const OpsView &view, 
         dl = -1;
       }
     } else if (op == OP_INSERT) {
-      // claim-then-commit (Algorithm 2) in the candidate with more empty
-      // slots first, ties to the first hash: bucketed two-choice placement
-      // (three-choice with three candidates); within a bucket the slots are
-      // tried from one picked by the key (claim_slot)
+      // claim-then-commit (Algorithm 2) in the first candidate while it has
+      // room to spare, else in the candidate with more empty slots, ties to
+      // the first hash: bucketed two-choice placement (three-choice with
+      // three candidates); within a bucket the slots are tried from one
+      // picked by the key (claim_slot).  A first candidate that filled up
+      // meanwhile, with the second not probed, leaves the key to step 3,
+      // which looks at both again
       dl = 1;
       Mask f_first = e1, f_second = (c2 != c1) ? e2 : (Mask)0;
       uint32_t b_first = c1, b_second = c2;
-      if (popc_mask(f_second) > popc_mask(f_first)) {
+      if (popc_mask(f_second) > popc_mask(f_first) && (D3 || (uint32_t)popc_mask(f_first) < a.spill.first_min)) {
         const Mask tm = f_first;
         f_first = f_second;
         f_second = tm;
@@ -1154,6 +1251,9 @@ __device__ __forceinline__ void ops_tile(const OpsArgs &a, const OpsView &view, 
           f_first &= (Mask)~((Mask)1 << s);
       }
       to_wl = !placed;
+      if constexpr (!D3) {
+        if (placed && b_first != c1 && !marked) spill_mark(a.spill, c1, k);
+      }
     }
   }
 
@@ -1188,7 +1288,7 @@ __device__ __forceinline__ void ops_tile(const OpsArgs &a, const OpsView &view, 
 // for; PIPE: loads in flight per probe chunk.  Tuned variants of the
 // 16-slot BitHash kernels are picked per table (hive_config.probe_tuning).
 template <int S, uint32_t MODE, bool BOTH, int PAIR = PAIR_BITHASH, int WPE = OPS_WAVES_PER_EU,
-          int PIPE = Traits<S>::CH>
+          int PIPE = Traits<S>::CH, int FILTER = FILTER_NONE>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE))) void ops_kernel(OpsArgs a) {
   __shared__ OpsShared<S, PairArity<PAIR>::D> sh;
   const OpsView view = read_view(a.ctl, a.stash_cap, a.pending_cap);
@@ -1196,8 +1296,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE))) vo
   int64_t live_acc = 0;
   uint64_t bad_acc = 0;
   for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x)
-    ops_tile<S, MODE, BOTH, PAIR, PIPE>(a, view, tile, sh, live_acc, bad_acc);
+    ops_tile<S, MODE, BOTH, PAIR, PIPE, FILTER>(a, view, tile, sh, live_acc, bad_acc);
   ops_counts_add(a.ctl, (uint64_t)blockIdx.x * WAVES + (threadIdx.x >> 6), live_acc, bad_acc);
+  if constexpr (FILTER != FILTER_NONE && (MODE == OP_MIXED || MODE == OP_DELETE)) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) set_removed(a.ctl);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1205,6 +1308,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE))) vo
 // ---------------------------------------------------------------------------
 struct EvictArgs {
   uint64_t *buckets;
+  Spill spill;
   uint32_t *hint;
   uint64_t *stash;
   uint64_t *pending;
@@ -1258,10 +1362,20 @@ __device__ __forceinline__ int overflow_place(const EvictArgs &a, const Geo &geo
     }
   }
   const uint32_t k = key_of(kv);
+  if constexpr (PairArity<PAIR>::D == 2) spill_mark(a.spill, address(geo, HashPair<PAIR>::h1(k)), k);
   set_hint(a.hint, address(geo, HashPair<PAIR>::h1(k)));
   set_hint(a.hint, address(geo, HashPair<PAIR>::h2(k)));
   if constexpr (PairArity<PAIR>::D == 3) set_hint(a.hint, address(geo, HashPair<PAIR>::h3(k)));
   return where;
+}
+
+// Entry kv was put in bucket b.
+template <int PAIR>
+__device__ __forceinline__ void evict_mark(const EvictArgs &a, const Geo &geo, uint64_t kv, uint32_t b) {
+  if constexpr (PairArity<PAIR>::D == 2) {
+    const uint32_t c1 = address(geo, HashPair<PAIR>::h1(key_of(kv)));
+    if (b != c1) spill_mark(a.spill, c1, key_of(kv));
+  }
 }
 
 // Eviction group shape.  A group of L lanes works on one item and sees a
@@ -1495,12 +1609,11 @@ __device__ __forceinline__ bool evict_chain(const EvictArgs &a, const Geo &geo, 
              group_claim<S>(a.buckets + (uint64_t)c[1] * S, f[1], kv, g, sl) ||
              group_claim<S>(a.buckets + (uint64_t)c[2] * S, f[2], kv, g, sl);
   } else {
-    if (popc_mask(f2) > popc_mask(f1))
-      placed = group_claim<S>(a.buckets + (uint64_t)c2 * S, f2, kv, g, sl) ||
-               group_claim<S>(a.buckets + (uint64_t)c1 * S, f1, kv, g, sl);
-    else
-      placed = group_claim<S>(a.buckets + (uint64_t)c1 * S, f1, kv, g, sl) ||
-               group_claim<S>(a.buckets + (uint64_t)c2 * S, f2, kv, g, sl);
+    const bool swap = popc_mask(f2) > popc_mask(f1) && (uint32_t)popc_mask(f1) < a.spill.first_min;
+    const uint32_t cf = swap ? c2 : c1, cs = swap ? c1 : c2;
+    const bool in_first = group_claim<S>(a.buckets + (uint64_t)cf * S, swap ? f2 : f1, kv, g, sl);
+    placed = in_first || group_claim<S>(a.buckets + (uint64_t)cs * S, swap ? f1 : f2, kv, g, sl);
+    if (placed && sl == 0) evict_mark<PAIR>(a, geo, kv, in_first ? cf : cs);
   }
   uint32_t b = c1;  // chains start at the first candidate
   // look-ahead chains keep the view of the bucket they move to: w holds
@@ -1512,6 +1625,7 @@ __device__ __forceinline__ bool evict_chain(const EvictArgs &a, const Geo &geo, 
     if (!have_view) {
       const Mask fm = load_view<S>(bkt, g, sl, w);
       if (group_claim<S>(bkt, fm, kv, g, sl)) {
+        if (sl == 0) evict_mark<PAIR>(a, geo, kv, b);
         placed = true;
         break;
       }
@@ -1549,6 +1663,7 @@ __device__ __forceinline__ bool evict_chain(const EvictArgs &a, const Geo &geo, 
       const Mask fpick = pick ? fb : fa;
       const uint64_t victim = vw[pick];
       if (cas64(bkt + vs[pick], victim, kv) != victim) continue;  // the slot changed: count the round
+      evict_mark<PAIR>(a, geo, kv, b);
       if (victim == EMPTY) {
         placed = true;  // the slot was empty after all: the CAS claimed it
         break;
@@ -1557,6 +1672,7 @@ __device__ __forceinline__ bool evict_chain(const EvictArgs &a, const Geo &geo, 
       kv = victim;
       b = va[pick];
       if (fpick && group_claim<S>(a.buckets + (uint64_t)b * S, fpick, kv, g, sl)) {
+        evict_mark<PAIR>(a, geo, kv, b);
         placed = true;
         break;
       }
@@ -1579,6 +1695,7 @@ __device__ __forceinline__ bool evict_chain(const EvictArgs &a, const Geo &geo, 
     const bool ok = (ballot(won) >> (g * E::L)) & E::LANES;
     const uint64_t victim = shfl64(ws, g * E::L + s0 / E::P);
     if (!ok) continue;  // the slot changed under us: count the round, keep the item
+    if (sl == 0) evict_mark<PAIR>(a, geo, kv, b);
     if (victim == EMPTY) {
       placed = true;  // the slot was empty after all: the CAS claimed it
       break;
@@ -1828,14 +1945,11 @@ __global__ __launch_bounds__(BLOCK) void evict_lanes_kernel(EvictArgs a) {
     if (st == FRESH) {
       const Mask f1 = (Mask)empty_mask16(w);
       const Mask f2 = (Mask)empty_mask16(w2v) & (Mask)((x2 != x1) ? ~0ull : 0ull);
-      bool placed;
-      if (popc_mask(f2) > popc_mask(f1))
-        placed = group_claim<S>(a.buckets + (uint64_t)x2 * S, f2, kv, lane, 0) ||
-                 group_claim<S>(a.buckets + (uint64_t)x1 * S, f1, kv, lane, 0);
-      else
-        placed = group_claim<S>(a.buckets + (uint64_t)x1 * S, f1, kv, lane, 0) ||
-                 group_claim<S>(a.buckets + (uint64_t)x2 * S, f2, kv, lane, 0);
-      if (placed) {
+      const bool swap = popc_mask(f2) > popc_mask(f1) && (uint32_t)popc_mask(f1) < a.spill.first_min;
+      const uint32_t cf = swap ? x2 : x1, cs = swap ? x1 : x2;
+      const bool in_first = group_claim<S>(a.buckets + (uint64_t)cf * S, swap ? f2 : f1, kv, lane, 0);
+      if (in_first || group_claim<S>(a.buckets + (uint64_t)cs * S, swap ? f1 : f2, kv, lane, 0)) {
+        if ((in_first ? cf : cs) != x1) spill_mark(a.spill, x1, key_of(kv));
         st = IDLE;
       } else if (max_kicks == 0) {
         fail = true;
@@ -1844,7 +1958,9 @@ __global__ __launch_bounds__(BLOCK) void evict_lanes_kernel(EvictArgs a) {
         st = LOOK;
       }
     } else if (st == RELOAD) {
-      st = group_claim<S>(a.buckets + (uint64_t)b * S, (Mask)empty_mask16(w), kv, lane, 0) ? IDLE : LOOK;
+      const bool placed = group_claim<S>(a.buckets + (uint64_t)b * S, (Mask)empty_mask16(w), kv, lane, 0);
+      if (placed) evict_mark<PAIR>(a, geo, kv, b);
+      st = placed ? IDLE : LOOK;
     } else if (st == LOOK) {
       ++kick;
       const Mask fa = (Mask)empty_mask16(w) & (Mask)((x1 != b) ? ~0ull : 0ull);
@@ -1858,12 +1974,15 @@ __global__ __launch_bounds__(BLOCK) void evict_lanes_kernel(EvictArgs a) {
         if (kick < max_kicks) st = RELOAD;
         else fail = true;
       } else if (victim == EMPTY) {
+        evict_mark<PAIR>(a, geo, kv, b);
         st = IDLE;  // the slot was empty after all: the CAS claimed it
       } else {
+        evict_mark<PAIR>(a, geo, kv, b);
         ++n_evict;
         kv = victim;
         b = pick ? x2 : x1;
         if (fpick && group_claim<S>(a.buckets + (uint64_t)b * S, fpick, kv, lane, 0)) {
+          evict_mark<PAIR>(a, geo, kv, b);
           st = IDLE;
         } else if (kick < max_kicks) {
           // the next round works from the view just loaded
@@ -2722,6 +2841,7 @@ constexpr uint32_t DRAIN_WINDOW = 64;             // batches scanned for work
 
 struct TableDesc {
   uint64_t *buckets;
+  Spill spill;
   uint32_t *hint;
   uint64_t *stash;
   uint64_t *pending;
@@ -2789,7 +2909,7 @@ __device__ __forceinline__ ResizeArgs resize_args(const ReqDesc &d) {
 }
 
 __device__ __forceinline__ EvictArgs evict_args(const ReqDesc &d) {
-  return EvictArgs{d.t.buckets, d.t.hint,       d.t.stash,       d.t.pending,      d.t.ctl,
+  return EvictArgs{d.t.buckets, d.t.spill,      d.t.hint,        d.t.stash,        d.t.pending, d.t.ctl,
                    d.t.wl,      d.t.wl_seg_cap, d.t.stash_cap,   d.t.pending_cap,  d.t.max_evictions};
 }
 
@@ -3129,6 +3249,7 @@ __device__ __forceinline__ ReqDesc uniform_desc(const ReqDesc &src) {
   __builtin_memcpy(&d, w, sizeof(ReqDesc));
   d.t.buckets = as_global(d.t.buckets);
   d.t.hint = as_global(d.t.hint);
+  d.t.spill.bits = as_global(d.t.spill.bits);
   d.t.stash = as_global(d.t.stash);
   d.t.pending = as_global(d.t.pending);
   d.t.ctl = as_global(d.t.ctl);
@@ -3222,6 +3343,7 @@ __device__ __forceinline__ void run_chunk(ReqState *r, const ReqDesc &d, uint32_
     case PH_OPS: {
       OpsArgs a{};
       a.buckets = d.t.buckets;
+      a.spill = d.t.spill;
       a.hint = d.t.hint;
       a.stash = d.t.stash;
       a.pending = d.t.pending;
@@ -3244,12 +3366,13 @@ __device__ __forceinline__ void run_chunk(ReqState *r, const ReqDesc &d, uint32_
       int64_t live_acc = 0;
       uint64_t bad_acc = 0;
       switch (d.mode) {
-        case OP_INSERT: ops_tile<S, OP_INSERT, false>(a, view, c, sh, live_acc, bad_acc); break;
-        case OP_DELETE: ops_tile<S, OP_DELETE, false>(a, view, c, sh, live_acc, bad_acc); break;
-        case OP_LOOKUP: ops_tile<S, OP_LOOKUP, false>(a, view, c, sh, live_acc, bad_acc); break;
-        default: ops_tile<S, OP_MIXED, false>(a, view, c, sh, live_acc, bad_acc); break;
+        case OP_INSERT: ops_tile<S, OP_INSERT, false, PAIR_BITHASH, Traits<S>::CH, FILTER_ASK>(a, view, c, sh, live_acc, bad_acc); break;
+        case OP_DELETE: ops_tile<S, OP_DELETE, false, PAIR_BITHASH, Traits<S>::CH, FILTER_ASK>(a, view, c, sh, live_acc, bad_acc); break;
+        case OP_LOOKUP: ops_tile<S, OP_LOOKUP, false, PAIR_BITHASH, Traits<S>::CH, FILTER_ASK>(a, view, c, sh, live_acc, bad_acc); break;
+        default: ops_tile<S, OP_MIXED, false, PAIR_BITHASH, Traits<S>::CH, FILTER_ASK>(a, view, c, sh, live_acc, bad_acc); break;
       }
       ops_counts_add(d.t.ctl, c * WAVES + (threadIdx.x >> 6), live_acc, bad_acc);
+      if (c == 0 && threadIdx.x == 0 && (d.mode == OP_MIXED || d.mode == OP_DELETE)) set_removed(d.t.ctl);
       break;
     }
     default: break;  // PH_START: no data-parallel work
@@ -3395,6 +3518,7 @@ constexpr int SET_CH = 16;       // wave-wide bucket loads in flight
 
 struct SetArgs {
   uint32_t *buckets;
+  Spill spill;
   uint32_t *hint;
   uint32_t *stash;
   uint32_t *pending;
@@ -3473,6 +3597,7 @@ __global__ __launch_bounds__(BLOCK) void set_ops_kernel(SetArgs a) {
   const uint64_t n_stash = min(ld_ctl(&a.ctl->stash_count), a.stash_cap);
   const uint64_t n_pend = min(ld_ctl(&a.ctl->pending_count), a.pending_cap);
   const bool overflow_used = (n_stash | n_pend) != 0;
+  const bool removed = ld_ctl32(&a.ctl->removed) != 0;
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int g = lane >> 5, sl = lane & 31;
   const uint64_t ntiles = (a.n + BLOCK - 1) / BLOCK;
@@ -3503,7 +3628,15 @@ __global__ __launch_bounds__(BLOCK) void set_ops_kernel(SetArgs a) {
     set_probe_round(a.buckets, s_key[wv], s_b1[wv], nullptr, 64, s_m[0][wv], s_e[0][wv], g, sl);
     wave_lds_sync();
     const uint32_t m1 = s_m[0][wv][lane], e1 = s_e[0][wv][lane];
-    const bool need2 = work && m1 == 0 && c2 != c1;
+    // filter and placement as for 64-bit entries (ops_tile)
+    const bool near_full = (uint32_t)__builtin_popcount(e1) < a.spill.first_min;
+    bool spilled = true, marked = false;
+    if (a.spill.bits) {
+      marked = work && m1 == 0 && (near_full || MODE == OP_MIXED || MODE == OP_DELETE || removed) &&
+               spill_test(a.spill, c1, k);
+      spilled = marked;
+    }
+    const bool need2 = work && m1 == 0 && c2 != c1 && (spilled || (op == OP_INSERT && near_full));
     const uint64_t need2_mask = ballot(need2);
     const int n2 = __popcll(need2_mask);
     compact_second(need2, need2_mask, n2, k, c2, c1, lane, s_k2[wv], s_b2[wv], s_list[wv]);
@@ -3524,7 +3657,7 @@ __global__ __launch_bounds__(BLOCK) void set_ops_kernel(SetArgs a) {
       } else if (m2) {
         slot = a.buckets + (uint64_t)c2 * SET_S + __builtin_ctz(m2);
         in_bucket = true;
-      } else if (overflow_used && hinted(a.hint, c1, c2)) {
+      } else if (overflow_used && spilled && hinted(a.hint, c1, c2)) {
         slot = set_overflow_find(a, n_stash, n_pend, k);
       }
       if (op == OP_LOOKUP) {
@@ -3541,10 +3674,12 @@ __global__ __launch_bounds__(BLOCK) void set_ops_kernel(SetArgs a) {
           dl = -1;
         }
       } else if (!slot) {
-        // a new key: claim-then-commit in the emptier candidate first
+        // a new key: claim-then-commit in the first candidate while it has
+        // room to spare, else in the emptier one first
         dl = 1;
         uint32_t f_first = e1, f_second = (c2 != c1) ? e2 : 0u, b_first = c1, b_second = c2;
-        if (__builtin_popcount(f_second) > __builtin_popcount(f_first)) {
+        if (__builtin_popcount(f_second) > __builtin_popcount(f_first) &&
+            (uint32_t)__builtin_popcount(f_first) < a.spill.first_min) {
           const uint32_t tf = f_first;
           f_first = f_second;
           f_second = tf;
@@ -3565,6 +3700,7 @@ __global__ __launch_bounds__(BLOCK) void set_ops_kernel(SetArgs a) {
             f_first &= ~(1u << s);
         }
         to_wl = !placed;
+        if (placed && b_first != c1 && !marked) spill_mark(a.spill, c1, k);
       }
     }
     const uint64_t wl_mask = ballot(to_wl);
@@ -3584,6 +3720,7 @@ __global__ __launch_bounds__(BLOCK) void set_ops_kernel(SetArgs a) {
     }
     if (active && MODE != OP_INSERT && a.flags_out) __builtin_nontemporal_store(out_f, &a.flags_out[i]);
   }
+  if ((MODE == OP_MIXED || MODE == OP_DELETE) && blockIdx.x == 0 && threadIdx.x == 0) set_removed(a.ctl);
 }
 
 // A lane's fresh copy of a whole 32-slot bucket (128 bytes).
@@ -3636,6 +3773,7 @@ __device__ __forceinline__ int set_overflow_place(const SetArgs &a, const Geo &g
       where = 2;
     }
   }
+  spill_mark(a.spill, fastmod(bithash1(k), geo.magic, (uint32_t)geo.n_buckets), k);
   set_hint(a.hint, fastmod(bithash1(k), geo.magic, (uint32_t)geo.n_buckets));
   set_hint(a.hint, fastmod(bithash2(k), geo.magic, (uint32_t)geo.n_buckets));
   return where;
@@ -3667,17 +3805,18 @@ __global__ __launch_bounds__(BLOCK) void set_evict_kernel(SetArgs a) {
       uint32_t w[SET_S];
       const uint32_t f1 = load_set_bucket(a.buckets + (uint64_t)c1 * SET_S, w);
       const uint32_t f2 = c2 != c1 ? load_set_bucket(a.buckets + (uint64_t)c2 * SET_S, w) : 0u;
-      if (__builtin_popcount(f2) > __builtin_popcount(f1))
-        placed = set_claim(a.buckets + (uint64_t)c2 * SET_S, f2, k) ||
-                 set_claim(a.buckets + (uint64_t)c1 * SET_S, f1, k);
-      else
-        placed = set_claim(a.buckets + (uint64_t)c1 * SET_S, f1, k) ||
-                 set_claim(a.buckets + (uint64_t)c2 * SET_S, f2, k);
+      const bool swap = __builtin_popcount(f2) > __builtin_popcount(f1) &&
+                        (uint32_t)__builtin_popcount(f1) < a.spill.first_min;
+      const uint32_t cf = swap ? c2 : c1, cs = swap ? c1 : c2;
+      const bool in_first = set_claim(a.buckets + (uint64_t)cf * SET_S, swap ? f2 : f1, k);
+      placed = in_first || set_claim(a.buckets + (uint64_t)cs * SET_S, swap ? f1 : f2, k);
+      if (placed && (in_first ? cf : cs) != c1) spill_mark(a.spill, c1, k);
       uint32_t b = c1;
       for (uint32_t kick = 1; kick <= a.max_evictions && !placed; ++kick) {
         uint32_t *bkt = a.buckets + (uint64_t)b * SET_S;
-        const uint32_t fm = load_set_bucket(bkt, w);
+        const uint32_t fm = load_set_bucket(bkt, w), k1 = fastmod(bithash1(k), geo.magic, nb);
         if (set_claim(bkt, fm, k)) {
+          if (b != k1) spill_mark(a.spill, k1, k);
           placed = true;
           break;
         }
@@ -3687,6 +3826,7 @@ __global__ __launch_bounds__(BLOCK) void set_evict_kernel(SetArgs a) {
         for (int j = 0; j < SET_S; ++j)
           if (j == s0) ws = w[j];
         if (cas32(bkt + s0, ws, k) != ws) continue;  // the slot changed: count the round, keep the key
+        if (b != k1) spill_mark(a.spill, k1, k);
         if (ws == EMPTY32) {
           placed = true;
           break;
@@ -3745,6 +3885,7 @@ struct hive_table {
   uint64_t stash_cap, pending_cap;
   uint64_t *d_buckets = nullptr;
   uint32_t *d_hint = nullptr;
+  Spill spill{nullptr, 0, 0};  // its bits follow the hint bits, in one allocation
   uint64_t *d_stash = nullptr;
   uint64_t *d_pending = nullptr;
   Ctl *d_ctl = nullptr;
@@ -3853,10 +3994,16 @@ static hive_status fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t st)
 
 static uint64_t hint_words(uint64_t buckets) { return (buckets + 31) / 32; }
 
+// Words of the hint bits and, from a 256-byte boundary on, the filter's.
+static uint64_t hint_span(const hive_table *h) { return (hint_words(h->max_buckets) + 63) / 64 * 64; }
+static uint64_t bit_words(const hive_table *h, bool filter) {
+  return filter ? hint_span(h) + ((h->max_buckets << h->spill.shift) + 31) / 32 : hint_words(h->max_buckets);
+}
+
 static hive_status reset_table(hive_table *h, hipStream_t st) {
   hive_status s;
   if ((s = fill_u64(h->d_buckets, h->max_buckets * h->S * h->entry_bytes / 8, EMPTY, st)) != HIVE_OK) return s;
-  if ((s = fill_u32(h->d_hint, hint_words(h->max_buckets), 0u, st)) != HIVE_OK) return s;
+  if ((s = fill_u32(h->d_hint, bit_words(h, h->spill.bits != nullptr), 0u, st)) != HIVE_OK) return s;
   if ((s = fill_u64(h->d_stash, stash_slots_for(h->stash_cap) * h->entry_bytes / 8, EMPTY, st)) != HIVE_OK) return s;
   if ((s = fill_u64((uint64_t *)shard_of(h->d_ctl, 0), NSHARD * SHARD_STRIDE / 8, 0, st)) != HIVE_OK) return s;
   hipLaunchKernelGGL(ctl_reset_kernel, dim3(1), dim3(1), 0, st, h->d_ctl, initial_ctl(h));
@@ -3994,6 +4141,13 @@ template <int S, uint32_t MODE, bool BOTH, int PAIR = PAIR_BITHASH, int V = 0>
 static void launch_ops(const OpsArgs &a, uint32_t grid_cap, hipStream_t st) {
   constexpr ProbeTuning t = kProbeTunings[V];
   const uint64_t blocks = std::min<uint64_t>((a.n + BLOCK - 1) / BLOCK, grid_cap ? grid_cap : OPS_GRID);
+  if constexpr (!BOTH && PairArity<PAIR>::D == 2) {
+    if (a.spill.bits) {
+      hipLaunchKernelGGL((ops_kernel<S, MODE, BOTH, PAIR, t.waves_per_simd, t.loads_in_flight, FILTER_USE>),
+                         dim3((unsigned)blocks), dim3(BLOCK), 0, st, a);
+      return;
+    }
+  }
   hipLaunchKernelGGL((ops_kernel<S, MODE, BOTH, PAIR, t.waves_per_simd, t.loads_in_flight>),
                      dim3((unsigned)blocks), dim3(BLOCK), 0, st, a);
 }
@@ -4055,7 +4209,7 @@ static unsigned evict_lanes_grid(uint64_t max_items) {
 // start a chain at once, keeps one item per lane (evict_kernel).
 static void launch_evict(hive_table *h, uint64_t max_items, hipStream_t st, bool split_steps = false,
                          bool refill = true) {
-  EvictArgs e{h->d_buckets, h->d_hint,       h->d_stash,   h->d_pending,   h->d_ctl,
+  EvictArgs e{h->d_buckets, h->spill,        h->d_hint,    h->d_stash,   h->d_pending,   h->d_ctl,
               h->d_wl,      h->wl_seg_cap,   h->stash_cap, h->pending_cap, h->cfg.max_evictions};
   const dim3 grid(grid_for(max_items, (uint64_t)WAVES * evict_groups_per_wave(h->S), EVICT_GRID));
   if (split_steps && h->S == 16 && h->cfg.hash_pair == PAIR_BITHASH) {
@@ -4388,6 +4542,7 @@ static hive_status run_batch(hive_t h, uint32_t mode, const uint8_t *d_ops, cons
   if (no_alloc) h->timing = false;
   OpsArgs a{};
   a.buckets = h->d_buckets;
+  a.spill = h->spill;
   a.hint = h->d_hint;
   a.stash = h->d_stash;
   a.pending = h->d_pending;
@@ -4409,7 +4564,7 @@ static hive_status run_batch(hive_t h, uint32_t mode, const uint8_t *d_ops, cons
     if ((s = launch_dedupe(dd, mode, d_ops, d_keys, n, st, &a.win)) != HIVE_OK) return s;
   }
   if (h->entry_bytes == 4) {
-    SetArgs sa{(uint32_t *)h->d_buckets, h->d_hint, (uint32_t *)h->d_stash, (uint32_t *)h->d_pending, h->d_ctl,
+    SetArgs sa{(uint32_t *)h->d_buckets, h->spill, h->d_hint, (uint32_t *)h->d_stash, (uint32_t *)h->d_pending, h->d_ctl,
                h->d_wl, h->wl_seg_cap, a.dd, a.dd_mask, d_ops, d_keys, d_flags_out, n, h->stash_cap, h->pending_cap,
                h->cfg.max_evictions, a.win};
     phase_mark(h, HIVE_PHASE_PROBE, st);
@@ -4541,15 +4696,21 @@ hive_status hive_create(const hive_config *cfg_in, uint64_t initial_buckets, voi
   cfg.pending_capacity = h->pending_cap;
   cfg.max_buckets = max_b;
   h->cfg = cfg;
+  const bool filter = cfg.addressing == HIVE_FIXED && cfg.hash_pair != HIVE_PAIR_TRIPLE && !cfg.probe_both &&
+                      cfg.max_evictions >= FIRST_MIN_CHAIN;
+  h->spill.first_min = filter ? FIRST_MIN : S + 1;  // S + 1: by two-choice alone
+  h->spill.shift = 3;
+  while (h->spill.shift > 0 && (max_b << h->spill.shift) / 8 > FILTER_BYTES) --h->spill.shift;
   hive_status s = HIVE_OK;
   if ((s = alloc((void **)&h->d_buckets, max_b * S * h->entry_bytes, &h->bytes)) != HIVE_OK ||
-      (s = alloc((void **)&h->d_hint, hint_words(max_b) * 4, &h->bytes)) != HIVE_OK ||
+      (s = alloc((void **)&h->d_hint, bit_words(h, filter) * 4, &h->bytes)) != HIVE_OK ||
       (s = alloc((void **)&h->d_stash, stash_slots_for(h->stash_cap) * h->entry_bytes, &h->bytes)) != HIVE_OK ||
       (s = alloc((void **)&h->d_pending, h->pending_cap * h->entry_bytes, &h->bytes)) != HIVE_OK ||
       (s = alloc((void **)&h->d_ctl, CTL_BYTES, &h->bytes)) != HIVE_OK) {
     free_table(h);
     return s;
   }
+  if (filter) h->spill.bits = h->d_hint + hint_span(h);
   hipStream_t st = (hipStream_t)stream;
   h->last = st;
   // the worklist must hold a full stash + pending drain (after a split);
@@ -4889,7 +5050,7 @@ hive_status hive_drain_submit(hive_drain_t d, hive_t h, const hive_batch_desc *b
   if (wl_need > h->wl_cap || dd_size > h->dd_cap) return HIVE_ERR_OOM;  // cannot happen after a good grow
   ReqDesc r;
   memset(&r, 0, sizeof(r));
-  r.t = TableDesc{h->d_buckets,    h->d_hint,  h->d_stash,   h->d_pending, h->d_ctl, h->d_wl, h->d_dd,
+  r.t = TableDesc{h->d_buckets,    h->spill, h->d_hint,  h->d_stash,   h->d_pending, h->d_ctl, h->d_wl, h->d_dd,
                   h->wl_seg_cap,  h->stash_cap,
                   h->pending_cap, hint_words(h->max_buckets), h->S, h->cfg.max_evictions, h->cfg.resize_k,
                   h->cfg.lf_expand_pct, h->cfg.lf_contract_pct, h->cfg.pre_expand, h->cfg.post_policy,

@@ -48,7 +48,7 @@ struct alignas(128) Ctl {
   uint64_t im;             // LINEAR: index mask 2^m - 1
   uint64_t sp;             // LINEAR: split pointer
   uint32_t mode;           // ADDR_FIXED / ADDR_LINEAR
-  uint32_t pad_mode_;
+  uint32_t removed;        // a batch that may delete ran since the table was empty
   uint64_t stash_count;    // stash slots used (including TOMB)
   uint64_t pending_count;  // pending slots used (including TOMB; may pass capacity on loss)
   uint64_t pad0_[9];

@@ -296,3 +296,70 @@ def test_large_mixed_batch_counts_its_inserts(H):
         st = t.stats()
         assert st["n_buckets"] == nb and st["live"] == need, (n, st, nb)
     t.close()
+
+
+@pytest.mark.parametrize("S,set32,cfg", [(16, False, {}), (64, False, {}), (32, True, {}), (16, False, {"hash_pair": 1}),
+                                         (16, False, {"hash_pair": 2}), (16, False, {"max_evictions": 3}),
+                                         (16, False, {"probe_both": 1}), (16, False, {"probe_tuning": 0x4444})])
+def test_spilled_keys_stay_reachable(H, S, set32, cfg):
+    """Tables with a spill filter (and the kinds without one) at 96% load,
+    through rounds of deletes and inserts: keys in their second candidate and
+    in the stash are found, replaced and deleted, before and after the first
+    deletion, and the same batches through the executor."""
+    nb = 257 if S == 16 else 65
+    case(f"spilled keys S={S} set32={set32} {cfg}")
+    n = int(nb * S * 0.96)
+    ks = wl.KeyStream(1200 + S)
+    t, o = make(H, S, nb, set32, stash_capacity=2048, pending_capacity=4096, **cfg), oracle.O1()
+    rng = np.random.default_rng(1200)
+    keys = ks.range(0, n)
+    for part in np.array_split(keys, 5):  # the later parts meet full buckets
+        t.insert(dev(part), dev(values(part, set32)), flags=H.HIVE_UNIQUE)
+        o.insert(part, values(part, set32))
+    q = ks.range(0, 3 * n)
+
+    def check():
+        v, f = t.lookup(dev(q))
+        ov, of = o.lookup(q)
+        assert np.array_equal(host(f), of)
+        if not set32:
+            assert np.array_equal(host(v), ov)
+        assert np.array_equal(t.dump(), o.dump())
+
+    check()
+    at = n
+    for r in range(4):
+        again = rng.permutation(keys)[: n // 3]  # replaced where they are
+        t.insert(dev(again), dev(values(again, set32) ^ np.uint32(0 if set32 else r + 1)))
+        o.insert(again, values(again, set32) ^ np.uint32(0 if set32 else r + 1))
+        gone = rng.permutation(keys)[: n // 4]
+        assert np.array_equal(host(t.delete(dev(gone))), o.delete(gone))
+        new = ks.range(at, at + n // 4)
+        at += new.size
+        keys = np.concatenate([np.setdiff1d(keys, gone), new])
+        t.insert(dev(new), dev(values(new, set32)))
+        o.insert(new, values(new, set32))
+        check()
+    if not set32 and "hash_pair" not in cfg:
+        d = H.hive_drain_create(S, 0, 64, 1, 10_000_000)
+        keep = []
+        for r in range(6):
+            pick = rng.permutation(q)[:900]
+            ops = np.array([wl.OP_INSERT, wl.OP_DELETE, wl.OP_LOOKUP], np.uint8)[pick % 3]
+            vals = rng.integers(1, 1 << 32, pick.size, dtype=np.uint64).astype(np.uint32)
+            room = len(o) < n  # no growth past the table
+            ops[(ops == wl.OP_INSERT) & (not room)] = wl.OP_LOOKUP
+            import torch
+            vo = torch.zeros(pick.size, dtype=torch.int32, device="cuda").view(torch.uint32)
+            fo = torch.zeros(pick.size, dtype=torch.uint8, device="cuda")
+            b = (dev(ops), dev(pick), dev(vals), vo, fo)
+            keep.append((b, o.apply(ops, pick, vals)))
+            assert H.hive_drain_submit(d, t.h, H.HIVE_OP_MIXED, b[1], b[2], b[0], vo, fo) is not None
+        H.hive_drain_launch(d, 0)
+        import torch
+        torch.cuda.synchronize()
+        for (_, _, _, vo, fo), (ov, of) in keep:
+            assert np.array_equal(host(fo), of) and np.array_equal(host(vo), ov)
+        H.hive_drain_destroy(d)
+        check()
+    t.close()
