@@ -376,11 +376,13 @@ constexpr int DDS_BLOCK = 1024;
 constexpr uint64_t DDS_MAX = 1ull << 14;
 constexpr uint32_t DDS_PER = 512;     // operations per range aimed at
 constexpr int DDS_TAB = 4096;         // table entries (32 KiB)
-constexpr uint32_t DDS_CAP = DDS_TAB * 5 / 8;
 constexpr int DDS_LIST = 8192;        // records held (64 KiB)
+// the executor's blocks
+constexpr uint64_t DDS_EXEC_MAX = 1ull << 14;
+constexpr int DDS_EXEC_TAB = 2048;
+constexpr int DDS_EXEC_LIST = 1024;
 constexpr int DDS_LOADS = 8;          // keys in flight per thread
 static_assert(DDS_MAX < (1ull << 31), "an index shares a word with the type bit");
-static_assert(DDS_CAP + DDS_BLOCK < DDS_TAB, "one claim per thread past the limit still leaves EMPTY words");
 
 struct DdsArgs {
   const uint8_t *ops;
@@ -396,10 +398,18 @@ __device__ __forceinline__ uint32_t dds_range(uint32_t k, uint32_t bits) {
   return bits ? dds_hash(k) >> (32 - bits) : 0u;
 }
 
+template <int TAB, int LIST>
+struct DdsShared {
+  uint64_t tab[TAB];
+  uint64_t list[LIST];
+  uint32_t count, claims;
+};
+
 // Record e (key << 32 | type << 31 | index) into the table.
+template <int TAB>
 __device__ __forceinline__ void dds_settle(uint64_t *tab, uint64_t e, bool keep_last, uint32_t *claims) {
   const uint32_t k = (uint32_t)(e >> 32);
-  for (uint32_t s = mix32(k) & (DDS_TAB - 1);; s = (s + 1) & (DDS_TAB - 1)) {
+  for (uint32_t s = mix32(k) & (TAB - 1);; s = (s + 1) & (TAB - 1)) {
     uint64_t cur = *(volatile uint64_t *)&tab[s];
     if (cur == EMPTY) {
       cur = atomicCAS((unsigned long long *)&tab[s], (unsigned long long)EMPTY, (unsigned long long)e);
@@ -422,26 +432,28 @@ __device__ __forceinline__ void dds_settle(uint64_t *tab, uint64_t e, bool keep_
 }
 
 // Whether record e is the one its key's table word kept.
+template <int TAB>
 __device__ __forceinline__ bool dds_kept(const uint64_t *tab, uint64_t e) {
   const uint32_t k = (uint32_t)(e >> 32);
-  uint32_t s = mix32(k) & (DDS_TAB - 1);
-  while ((uint32_t)(tab[s] >> 32) != k) s = (s + 1) & (DDS_TAB - 1);
+  uint32_t s = mix32(k) & (TAB - 1);
+  while ((uint32_t)(tab[s] >> 32) != k) s = (s + 1) & (TAB - 1);
   return tab[s] == e;
 }
 
-// Operations base + j * DDS_BLOCK + thread of the batch as records, EMPTY
+// Operations base + j * NT + thread of the batch as records, EMPTY
 // where there is none to record or its key is outside [lo, lo + width).
+template <int NT>
 __device__ __forceinline__ void dds_read(const DdsArgs &d, uint32_t base, uint32_t lo, uint64_t width, uint64_t *e) {
   uint32_t k[DDS_LOADS], o[DDS_LOADS];
 #pragma unroll
   for (int j = 0; j < DDS_LOADS; ++j) {
-    const uint32_t i = base + j * DDS_BLOCK + threadIdx.x;
+    const uint32_t i = base + j * NT + threadIdx.x;
     k[j] = i < d.n ? d.keys[i] : 0u;
     o[j] = (d.mode == OP_MIXED && i < d.n) ? d.ops[i] : d.mode;
   }
 #pragma unroll
   for (int j = 0; j < DDS_LOADS; ++j) {
-    const uint32_t i = base + j * DDS_BLOCK + threadIdx.x;
+    const uint32_t i = base + j * NT + threadIdx.x;
     // a mixed batch's deletes carry the type bit: the key sets of the types are
     // disjoint by contract, so one table takes both
     const uint32_t ty = (d.mode == OP_MIXED && o[j] == OP_DELETE) ? 1u : 0u;
@@ -451,23 +463,25 @@ __device__ __forceinline__ void dds_read(const DdsArgs &d, uint32_t base, uint32
   }
 }
 
-__global__ __launch_bounds__(DDS_BLOCK) void dds_kernel(DdsArgs d) {
-  __shared__ uint64_t tab[DDS_TAB];
-  __shared__ uint64_t list[DDS_LIST];
-  __shared__ uint32_t s_count, s_claims;
+// Range `range` of the batch, by a block of NT threads (every one calls it).
+template <int NT, int TAB, int LIST>
+__device__ __forceinline__ void dds_range_of(const DdsArgs &d, uint32_t range, DdsShared<TAB, LIST> &sh) {
+  constexpr uint32_t CAP = TAB * 5 / 8;
+  static_assert(CAP + NT < TAB, "one claim per thread past the limit still leaves EMPTY words");
+  uint64_t *tab = sh.tab, *list = sh.list;
   const int lane = threadIdx.x & 63;
   // inserts keep the last occurrence (type 0 of a mixed batch), deletes the first
   const auto keep_last = [&](uint64_t e) { return d.mode == OP_MIXED ? ((uint32_t)e >> 31) == 0 : d.mode == OP_INSERT; };
-  const uint64_t whole = 1ull << (32 - d.bits), first = (uint64_t)blockIdx.x * whole, last = first + whole;
+  const uint64_t whole = 1ull << (32 - d.bits), first = (uint64_t)range * whole, last = first + whole;
   uint64_t lo = first, width = whole;
   while (lo < last) {
     width = min(width, last - lo);
-    for (int j = threadIdx.x; j < DDS_TAB; j += DDS_BLOCK) tab[j] = EMPTY;
-    if (threadIdx.x == 0) s_count = s_claims = 0;
+    for (int j = threadIdx.x; j < TAB; j += NT) tab[j] = EMPTY;
+    if (threadIdx.x == 0) sh.count = sh.claims = 0;
     __syncthreads();
-    for (uint32_t base = 0; base < d.n; base += DDS_LOADS * DDS_BLOCK) {
+    for (uint32_t base = 0; base < d.n; base += DDS_LOADS * NT) {
       uint64_t e[DDS_LOADS], m[DDS_LOADS];
-      dds_read(d, base, (uint32_t)lo, width, e);
+      dds_read<NT>(d, base, (uint32_t)lo, width, e);
       uint32_t c = 0;
 #pragma unroll
       for (int j = 0; j < DDS_LOADS; ++j) {
@@ -476,40 +490,40 @@ __global__ __launch_bounds__(DDS_BLOCK) void dds_kernel(DdsArgs d) {
       }
       if (c == 0) continue;
       uint32_t at = 0;
-      if (lane == 0) at = atomicAdd(&s_count, c);
+      if (lane == 0) at = atomicAdd(&sh.count, c);
       at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
 #pragma unroll
       for (int j = 0; j < DDS_LOADS; ++j) {
         if (e[j] != EMPTY) {
           const uint32_t pos = at + rank_below(m[j]);
-          if (pos < DDS_LIST)
+          if (pos < LIST)
             list[pos] = e[j];
-          else if (*(volatile uint32_t *)&s_claims <= DDS_CAP)
-            dds_settle(tab, e[j], keep_last(e[j]), &s_claims);
+          else if (*(volatile uint32_t *)&sh.claims <= CAP)
+            dds_settle<TAB>(tab, e[j], keep_last(e[j]), &sh.claims);
         }
         at += (uint32_t)__popcll(m[j]);
       }
     }
     __syncthreads();
-    const uint32_t held = min(s_count, (uint32_t)DDS_LIST);
-    const bool spilled = s_count > DDS_LIST;
-    for (uint32_t t = threadIdx.x; t < held; t += DDS_BLOCK)
-      if (*(volatile uint32_t *)&s_claims <= DDS_CAP) dds_settle(tab, list[t], keep_last(list[t]), &s_claims);
+    const uint32_t held = min(sh.count, (uint32_t)LIST);
+    const bool spilled = sh.count > LIST;
+    for (uint32_t t = threadIdx.x; t < held; t += NT)
+      if (*(volatile uint32_t *)&sh.claims <= CAP) dds_settle<TAB>(tab, list[t], keep_last(list[t]), &sh.claims);
     __syncthreads();
-    const uint32_t claims = s_claims;
-    const bool over = claims > DDS_CAP;  // the same in the whole block
+    const uint32_t claims = sh.claims;
+    const bool over = claims > CAP;  // the same in the whole block
     if (!over) {
-      for (uint32_t t = threadIdx.x; t < held; t += DDS_BLOCK) {
+      for (uint32_t t = threadIdx.x; t < held; t += NT) {
         const uint64_t e = list[t];
-        d.win[(uint32_t)e & 0x7FFFFFFFu] = dds_kept(tab, e);
+        d.win[(uint32_t)e & 0x7FFFFFFFu] = dds_kept<TAB>(tab, e);
       }
       if (spilled) {
-        for (uint32_t base = 0; base < d.n; base += DDS_LOADS * DDS_BLOCK) {
+        for (uint32_t base = 0; base < d.n; base += DDS_LOADS * NT) {
           uint64_t e[DDS_LOADS];
-          dds_read(d, base, (uint32_t)lo, width, e);
+          dds_read<NT>(d, base, (uint32_t)lo, width, e);
 #pragma unroll
           for (int j = 0; j < DDS_LOADS; ++j)
-            if (e[j] != EMPTY) d.win[(uint32_t)e[j] & 0x7FFFFFFFu] = dds_kept(tab, e[j]);
+            if (e[j] != EMPTY) d.win[(uint32_t)e[j] & 0x7FFFFFFFu] = dds_kept<TAB>(tab, e[j]);
         }
       }
     }
@@ -518,9 +532,14 @@ __global__ __launch_bounds__(DDS_BLOCK) void dds_kernel(DdsArgs d) {
       width = (width + 1) / 2;
     } else {
       lo += width;
-      if (claims <= DDS_CAP / 2) width *= 2;
+      if (claims <= CAP / 2) width *= 2;
     }
   }
+}
+
+__global__ __launch_bounds__(DDS_BLOCK) void dds_kernel(DdsArgs d) {
+  __shared__ DdsShared<DDS_TAB, DDS_LIST> sh;
+  dds_range_of<DDS_BLOCK>(d, blockIdx.x, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -2861,7 +2880,9 @@ struct ReqDesc {  // written by the host
   uint8_t *flags_out;
   uint64_t n;
   uint32_t mode, flags;
-  uint64_t seq, table_slot, ticket, dd_size;
+  uint64_t seq, table_slot, ticket;
+  uint64_t dd_size;  // dedupe by a set in HBM of this many words (0: not so)
+  uint64_t dds;      // dedupe by hash ranges in LDS: 1 + log2 of their number (0: not so)
 };
 static_assert(sizeof(ReqDesc) % 8 == 0, "descriptor copied as 64-bit words");
 
@@ -2969,8 +2990,9 @@ __device__ __forceinline__ uint64_t enter(volatile ReqState *r, const ReqDesc &d
   const uint64_t gpb = (uint64_t)WAVES * (64 / d.t.S);  // groups per block
   switch (ph) {
     case PH_FILL: return d.dd_size ? ceil_div(d.dd_size, FILL_PER_CHUNK) : 0;
-    case PH_DEDUPE: return d.dd_size ? ceil_div(d.n, BLOCK) : 0;
+    case PH_DEDUPE: return d.dds ? 1ull << (d.dds - 1) : d.dd_size ? ceil_div(d.n, BLOCK) : 0;
     case PH_COUNT:
+      if (d.dds) return 0;  // counted with the dedupe
       r->aux = 0;
       return (d.t.addressing == ADDR_LINEAR && d.t.pre_expand && d.mode == OP_MIXED) ? ceil_div(d.n, COUNT_PER_CHUNK)
                                                                                      : 0;
@@ -3031,14 +3053,18 @@ __device__ __forceinline__ void phase_fold(ReqState *rs, const ReqDesc &d, uint3
 // and without the acquires (L2 invalidations) of a handoff, since no other
 // block writes its data meanwhile.  Each such phase starts with an L1
 // invalidation instead (invalidate_l1: the block's own atomics of the last
-// phase are not in its L1).  The release before publishing stays (later
-// phases read buckets with coherent loads, which must see this block's plain
-// stores), and so does the full release when the batch is done.
-constexpr uint64_t SOLO_CHUNKS = 4;
+// phase are not in its L1).  The release before publishing (an L2 write-back)
+// stays after the phases whose plain stores later ones read with coherent
+// loads (splits, merges, the stash drain); winner flags and worklist entries
+// are read with plain loads, through the L2 that holds them, and buckets
+// change by atomics.  The full release stays when the batch is done.
+constexpr uint64_t SOLO_CHUNKS = 8;
 __device__ uint64_t advance(DrainQueue *q, ReqState *rs, const ReqDesc &d, uint32_t ph, bool own) {
   if (!own) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   volatile ReqState *r = rs;
   uint64_t nch = 0;
+  // a phase whose plain stores other phases read coherently
+  const bool stored = ph == PH_SEG_A || ph == PH_SEG_B || ph == PH_DRAIN;
   epilogue(r, d, ph);
   for (;;) {
     ph = successor(r, d, ph);
@@ -3059,9 +3085,14 @@ __device__ uint64_t advance(DrainQueue *q, ReqState *rs, const ReqDesc &d, uint3
     add64(&q->completed, 1);
     return 0;
   }
-  const uint64_t published = make_state(ph, nch) + (own && nch <= SOLO_CHUNKS ? nch : 0);
-  __threadfence();
-  __hip_atomic_store(&rs->state, published, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  const bool solo = own && nch <= SOLO_CHUNKS;
+  const uint64_t published = make_state(ph, nch) + (solo ? nch : 0);
+  if (solo && !stored) {
+    __hip_atomic_store(&rs->state, published, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+    __threadfence();
+    __hip_atomic_store(&rs->state, published, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  }
   return published;
 }
 
@@ -3265,7 +3296,14 @@ __device__ __forceinline__ ReqDesc uniform_desc(const ReqDesc &src) {
 
 
 template <int S>
-__device__ __forceinline__ void run_chunk(ReqState *r, const ReqDesc &d, uint32_t ph, uint64_t c, OpsShared<S> &sh) {
+union DrainShared {
+  OpsShared<S> ops;
+  DdsShared<DDS_EXEC_TAB, DDS_EXEC_LIST> dds;
+};
+
+template <int S>
+__device__ __forceinline__ void run_chunk(ReqState *r, const ReqDesc &d, uint32_t ph, uint64_t c,
+                                          DrainShared<S> &sh) {
   using T = Traits<S>;
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int g = lane / S, sl = lane % S;
@@ -3277,20 +3315,30 @@ __device__ __forceinline__ void run_chunk(ReqState *r, const ReqDesc &d, uint32_
       for (uint64_t t = b + threadIdx.x; t < e; t += BLOCK) d.t.dd[t] = EMPTY;
       break;
     }
-    case PH_DEDUPE: {
-      dedupe_thread(d.t.dd, d.dd_size - 1, d.mode, d.ops, d.keys, d.n, c * BLOCK + threadIdx.x);
-      break;
-    }
+    case PH_DEDUPE:
     case PH_COUNT: {
-      __shared__ unsigned long long cnt;
-      if (threadIdx.x == 0) cnt = 0;
-      __syncthreads();
-      unsigned long long mine = 0;
-      const uint64_t b = c * COUNT_PER_CHUNK, e = min(b + COUNT_PER_CHUNK, d.n);
-      for (uint64_t t = b + threadIdx.x; t < e; t += BLOCK) mine += d.ops[t] == OP_INSERT;
-      atomicAdd(&cnt, mine);
-      __syncthreads();
-      if (threadIdx.x == 0 && cnt) add64(&r->aux, cnt);
+      // the inserts of a mixed batch, for its growth rule: with the first
+      // range of a dedupe in LDS, else in chunks of their own
+      const bool ranges = ph == PH_DEDUPE && d.dds;
+      const bool counts = d.mode == OP_MIXED && d.t.addressing == ADDR_LINEAR && d.t.pre_expand;
+      if (ph == PH_COUNT || (ranges && c == 0 && counts)) {
+        __shared__ unsigned long long cnt;
+        if (threadIdx.x == 0) cnt = 0;
+        __syncthreads();
+        unsigned long long mine = 0;
+        const uint64_t b = ranges ? 0 : c * COUNT_PER_CHUNK, e = ranges ? d.n : min(b + COUNT_PER_CHUNK, d.n);
+        for (uint64_t t = b + threadIdx.x; t < e; t += BLOCK) mine += d.ops[t] == OP_INSERT;
+        mine = wave_sum64(mine);
+        if (lane == 0 && mine) atomicAdd(&cnt, mine);
+        __syncthreads();
+        if (threadIdx.x == 0 && cnt) add64(&r->aux, cnt);
+      }
+      if (ranges) {
+        const DdsArgs a{d.ops, d.keys, (uint8_t *)d.t.dd, (uint32_t)d.n, d.mode, (uint32_t)(d.dds - 1)};
+        dds_range_of<BLOCK>(a, (uint32_t)c, sh.dds);
+      } else if (ph == PH_DEDUPE) {
+        dedupe_thread(d.t.dd, d.dd_size - 1, d.mode, d.ops, d.keys, d.n, c * BLOCK + threadIdx.x);
+      }
       break;
     }
     case PH_SEG_A: {
@@ -3352,6 +3400,7 @@ __device__ __forceinline__ void run_chunk(ReqState *r, const ReqDesc &d, uint32_
       a.wl_seg_cap = d.t.wl_seg_cap;
       a.dd = d.dd_size ? d.t.dd : nullptr;
       a.dd_mask = d.dd_size ? d.dd_size - 1 : 0;
+      a.win = d.dds ? (const uint8_t *)d.t.dd : nullptr;
       a.ops = d.ops;
       a.keys = d.keys;
       a.vals = d.vals;
@@ -3366,10 +3415,10 @@ __device__ __forceinline__ void run_chunk(ReqState *r, const ReqDesc &d, uint32_
       int64_t live_acc = 0;
       uint64_t bad_acc = 0;
       switch (d.mode) {
-        case OP_INSERT: ops_tile<S, OP_INSERT, false, PAIR_BITHASH, Traits<S>::CH, FILTER_ASK>(a, view, c, sh, live_acc, bad_acc); break;
-        case OP_DELETE: ops_tile<S, OP_DELETE, false, PAIR_BITHASH, Traits<S>::CH, FILTER_ASK>(a, view, c, sh, live_acc, bad_acc); break;
-        case OP_LOOKUP: ops_tile<S, OP_LOOKUP, false, PAIR_BITHASH, Traits<S>::CH, FILTER_ASK>(a, view, c, sh, live_acc, bad_acc); break;
-        default: ops_tile<S, OP_MIXED, false, PAIR_BITHASH, Traits<S>::CH, FILTER_ASK>(a, view, c, sh, live_acc, bad_acc); break;
+        case OP_INSERT: ops_tile<S, OP_INSERT, false, PAIR_BITHASH, Traits<S>::CH, FILTER_ASK>(a, view, c, sh.ops, live_acc, bad_acc); break;
+        case OP_DELETE: ops_tile<S, OP_DELETE, false, PAIR_BITHASH, Traits<S>::CH, FILTER_ASK>(a, view, c, sh.ops, live_acc, bad_acc); break;
+        case OP_LOOKUP: ops_tile<S, OP_LOOKUP, false, PAIR_BITHASH, Traits<S>::CH, FILTER_ASK>(a, view, c, sh.ops, live_acc, bad_acc); break;
+        default: ops_tile<S, OP_MIXED, false, PAIR_BITHASH, Traits<S>::CH, FILTER_ASK>(a, view, c, sh.ops, live_acc, bad_acc); break;
       }
       ops_counts_add(d.t.ctl, c * WAVES + (threadIdx.x >> 6), live_acc, bad_acc);
       if (c == 0 && threadIdx.x == 0 && (d.mode == OP_MIXED || d.mode == OP_DELETE)) set_removed(d.t.ctl);
@@ -3399,7 +3448,7 @@ __device__ __forceinline__ void invalidate_l1() { asm volatile("buffer_inv sc0" 
 // 128 (4 waves) spills inside the phases and runs slower.
 template <int S>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void drain_worker_kernel(DrainQueue *q) {
-  __shared__ OpsShared<S> sh;
+  __shared__ DrainShared<S> sh;
   __shared__ ReqDesc desc;
   __shared__ uint64_t s_req, s_chunk, s_cnt, s_nch;
   __shared__ uint32_t s_phase, s_cmd;
@@ -3460,6 +3509,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
       run_chunk<S>(r, d, phase, chunk + k, sh);
       __syncthreads();
     }
+    // this wave's stores and atomics are done before the block goes on
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
     const bool own = cnt == uniform64(s_nch);  // every chunk of the phase ran here
     if (threadIdx.x == 0) {
       if (s_solo) {
@@ -5038,7 +5090,7 @@ hive_status hive_drain_submit(hive_drain_t d, hive_t h, const hive_batch_desc *b
     d->n_tables++;
   }
   const bool dedupe = !(b->flags & HIVE_UNIQUE) && b->op_mode != HIVE_OP_LOOKUP;
-  const uint64_t dd_size = (dedupe && b->n > 0) ? dd_set_words(b->n) : 0;
+  uint64_t dd_size = (dedupe && b->n > 0) ? dd_set_words(b->n) : 0;
   // scratch is never reallocated under a running executor; only inserts
   // reach the eviction worklist, while the dedupe set holds every operation
   const uint64_t wl_need = (b->op_mode == HIVE_OP_INSERT || b->op_mode == HIVE_OP_MIXED) ? b->n : 0;
@@ -5066,6 +5118,13 @@ hive_status hive_drain_submit(hive_drain_t d, hive_t h, const hive_batch_desc *b
   r.seq = d->next_seq[slot]++;
   r.table_slot = slot;
   r.ticket = t;
+  if (dd_size && b->n <= DDS_EXEC_MAX) {
+    // by hash ranges in LDS; the scratch (checked above for either form) holds
+    // the winner flags
+    r.dds = 1;
+    while (((uint64_t)DDS_PER << (r.dds - 1)) < b->n) ++r.dds;
+    dd_size = 0;
+  }
   r.dd_size = dd_size;
   memcpy(&d->h_ring[t % d->cap], &r, sizeof(r));
   __atomic_thread_fence(__ATOMIC_RELEASE);
