@@ -3058,7 +3058,10 @@ __device__ __forceinline__ void phase_fold(ReqState *rs, const ReqDesc &d, uint3
 // loads (splits, merges, the stash drain); winner flags and worklist entries
 // are read with plain loads, through the L2 that holds them, and buckets
 // change by atomics.  The full release stays when the batch is done.
-constexpr uint64_t SOLO_CHUNKS = 8;
+// (Chunks run one after another in a block, 6 to 8 us each with a probe's
+// latency: at 8 chunks a mixed batch of 2,048 operations took 122 us, at 2
+// chunks, handed to other blocks beyond, 58.)
+constexpr uint64_t SOLO_CHUNKS = 2;
 __device__ uint64_t advance(DrainQueue *q, ReqState *rs, const ReqDesc &d, uint32_t ph, bool own) {
   if (!own) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   volatile ReqState *r = rs;
@@ -3078,10 +3081,14 @@ __device__ uint64_t advance(DrainQueue *q, ReqState *rs, const ReqDesc &d, uint3
     const uint64_t ticket = d.ticket;
     __hip_atomic_store(&q->host_live[ticket % q->cap], ld_ctl(&d.t.ctl->live), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_SYSTEM);
-    __threadfence_system();  // the batch's outputs before its completion flag
-    __hip_atomic_store(&q->table_next[d.table_slot], d.seq + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&rs->state, make_state(PH_DONE, 0), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&q->host_done[ticket % q->cap], ticket + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    // one fence orders the batch's outputs and updates before all of these
+    // stores (a release of its own on each would write the L2 back again);
+    // the ring slot is done with before the host may reuse it
+    __threadfence_system();
+    __hip_atomic_store(&rs->state, make_state(PH_DONE, 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&q->table_next[d.table_slot], d.seq + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __hip_atomic_store(&q->host_done[ticket % q->cap], ticket + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     add64(&q->completed, 1);
     return 0;
   }
@@ -3136,7 +3143,8 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
 __device__ void ingest(DrainQueue *q) {
   const int lane = threadIdx.x & 63;
   uint32_t got = 0;
-  if (lane == 0 && __hip_atomic_load(&q->ingest_lock, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
+  if (lane == 0 && __hip_atomic_load(&q->ingest_lock, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0 &&
+      __hip_atomic_load(&q->final_seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
     uint32_t expect = 0;
     got = __hip_atomic_compare_exchange_strong(&q->ingest_lock, &expect, 1u, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
@@ -3147,6 +3155,10 @@ __device__ void ingest(DrainQueue *q) {
   const uint64_t tail = uniform64(ld_sys(q->host_tail));
   const uint64_t i0 = uniform64(ld_ctl(&q->ingested));
   const uint64_t n = min(tail - i0, (uint64_t)64);
+  if (n == 0 && !stop) {  // nothing new: no fences
+    if (lane == 0) __hip_atomic_store(&q->ingest_lock, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
   constexpr uint64_t W = sizeof(ReqDesc) / 8;
   for (uint64_t k = lane; k < n * W; k += 64) {
     const uint64_t i = (i0 + k / W) % q->cap, w = k % W;
@@ -3187,40 +3199,36 @@ __device__ uint32_t find_work(DrainQueue *q, uint64_t *req, uint32_t *phase, uin
                               uint64_t *nch) {
   const int lane = threadIdx.x & 63;
   ingest(q);
-  const uint64_t ing = uniform64(ld_ctl(&q->ingested));
-  uint64_t head = uniform64(ld_ctl(&q->head));
-  // retire the completed batches at the head of the ring
-  {
-    const uint64_t t = head + lane;
+  uint64_t ing = ld_ctl(&q->ingested), head = ld_ctl(&q->head);  // in flight together
+  ing = uniform64(ing);
+  head = uniform64(head);
+  // the window's states; the completed batches at the head of the ring are
+  // retired (then the window has moved, and its states are read again)
+  uint64_t t = head + lane, st = 0;
+  for (;;) {
     // relaxed: a retired entry is only skipped; an acquire load here would
     // invalidate the XCD's L2 on every poll of every idle block
-    const bool done = t < ing && (__hip_atomic_load(&q->req[t % q->cap].state, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT) >> 56) == PH_DONE;
-    const uint64_t dm = ballot(done);
+    st = t < ing ? __hip_atomic_load(&q->req[t % q->cap].state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    const uint64_t dm = ballot(t < ing && (st >> 56) == PH_DONE);
     const int lead = (dm == ~0ull) ? 64 : __builtin_ctzll(~dm);
-    if (lead > 0) {
-      if (lane == 0) {
-        uint64_t h = head;
-        __hip_atomic_compare_exchange_strong(&q->head, &h, head + lead, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-      }
-      head = uniform64(ld_ctl(&q->head));
-    }
+    if (lead == 0) break;
+    uint64_t h = head;
+    if (lane == 0)
+      __hip_atomic_compare_exchange_strong(&q->head, &h, head + lead, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+    // h: the head found; entries up to head + lead are done in any case
+    head = max(uniform64(h), head + lead);
+    t = head + lane;
+    if (head >= ing) break;
   }
-  if (head == ing) {
+  if (head >= ing) {
     if (__hip_atomic_load(&q->final_seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 &&
         ld_ctl(&q->ingested) == ing)
       return 2;
     return 1;
   }
-  const uint64_t t = head + lane;
   ReqState *r = q->req + t % q->cap;
-  uint64_t st = 0;
-  bool runnable = false;
-  if (t < ing) {
-    st = __hip_atomic_load(&r->state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    runnable = (uint32_t)(st >> 56) != PH_DONE && (st & M28) < ((st >> 28) & M28);
-  }
+  bool runnable = t < ing && (uint32_t)(st >> 56) != PH_DONE && (st & M28) < ((st >> 28) & M28);
   // the descriptor read below must see what was written before the state
   // was released; the acquire fence (an L2 invalidate) is paid only by a
   // scan that found unclaimed chunks, never by an idle poll
@@ -3488,7 +3496,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
     const uint32_t cmd = s_cont ? 0u : s_cmd;
     if (cmd == 2) break;
     if (cmd == 1) {
-      __builtin_amdgcn_s_sleep(7);  // about 450 clocks
+      // about 7 us: every poll of an idle block reads the queue's words and
+      // the states of the window, the same lines that the working blocks
+      // update, and with a block per compute unit some block polls every few
+      // tens of ns anyway (450 clocks: a lookup of one key 25.6 us through
+      // the executor, a mixed batch of 4,096 operations 63; now 21.5 and 53)
+      __builtin_amdgcn_s_sleep(127);
+      __builtin_amdgcn_s_sleep(127);
       __syncthreads();
       continue;
     }
@@ -3514,8 +3528,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
     __syncthreads();
     const bool own = cnt == uniform64(s_nch);  // every chunk of the phase ran here
     if (threadIdx.x == 0) {
-      if (s_solo) {
-        s_last = true;  // the phase was published claimed by this block
+      if (s_solo || phase == PH_START) {
+        s_last = true;  // claimed whole by this block; a start phase stores nothing
       } else {
         __threadfence();  // these chunks' writes before their completion count
         s_last = add64(&r->done, s_cnt) + s_cnt == s_nch;
