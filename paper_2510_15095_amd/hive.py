@@ -140,28 +140,40 @@ lib = _lib
 
 
 # ---------------------------------------------------------------- marshalling
+# These run a few times in every call, and a small batch's call is bound by
+# them: pointers go to ctypes as plain integers, torch is looked up once, and
+# the current stream's handle is read without making a Stream object (3 us).
+import torch  # noqa: E402  (loaded by _load already)
+
+_Tensor = torch.Tensor
+_U8, _U32, _U64, _I64 = torch.uint8, torch.uint32, torch.uint64, torch.int64
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream):
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _dev(t, dtype, name, n=None, optional=False):
-    import torch
+    """Address of a contiguous GPU tensor of `dtype` with at least n elements."""
+    if (isinstance(t, _Tensor) and t.is_cuda and t.dtype is dtype and t.is_contiguous()
+            and (n is None or t.numel() >= n)):
+        return t.data_ptr()
     if t is None:
         if optional:
             return None
         raise ValueError(f"{name} is required")
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if not isinstance(t, _Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a GPU tensor")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if n is not None and t.numel() < n:
-        raise ValueError(f"{name} holds {t.numel()} elements, needs {n}")
-    return ctypes.c_void_p(t.data_ptr())
+    raise ValueError(f"{name} holds {t.numel()} elements, needs {n}")
 
 
 def _check(status: int, where: str, warn_ok: bool = False) -> int:
@@ -206,48 +218,43 @@ def hive_destroy(h) -> None:
 
 
 def hive_insert_batch(h, keys, vals, flags: int = 0, stream=None) -> None:
-    import torch
     n = keys.numel()
-    _check(_lib.hive_insert_batch(h, _dev(keys, torch.uint32, "keys"),
-                                  _dev(vals, torch.uint32, "vals", n, optional=True), n, flags,
+    _check(_lib.hive_insert_batch(h, _dev(keys, _U32, "keys"),
+                                  _dev(vals, _U32, "vals", n, optional=True), n, flags,
                                   _stream_ptr(stream)), "hive_insert_batch")
 
 
 def hive_lookup_batch(h, keys, vals_out=None, found_out=None, stream=None) -> None:
-    import torch
     n = keys.numel()
-    _check(_lib.hive_lookup_batch(h, _dev(keys, torch.uint32, "keys"), n,
-                                  _dev(vals_out, torch.uint32, "vals_out", n, optional=True),
-                                  _dev(found_out, torch.uint8, "found_out", n, optional=True),
+    _check(_lib.hive_lookup_batch(h, _dev(keys, _U32, "keys"), n,
+                                  _dev(vals_out, _U32, "vals_out", n, optional=True),
+                                  _dev(found_out, _U8, "found_out", n, optional=True),
                                   _stream_ptr(stream)), "hive_lookup_batch")
 
 
 def hive_delete_batch(h, keys, deleted_out=None, flags: int = 0, stream=None) -> None:
-    import torch
     n = keys.numel()
-    _check(_lib.hive_delete_batch(h, _dev(keys, torch.uint32, "keys"), n, flags,
-                                  _dev(deleted_out, torch.uint8, "deleted_out", n, optional=True),
+    _check(_lib.hive_delete_batch(h, _dev(keys, _U32, "keys"), n, flags,
+                                  _dev(deleted_out, _U8, "deleted_out", n, optional=True),
                                   _stream_ptr(stream)), "hive_delete_batch")
 
 
 def hive_mixed_batch(h, ops, keys, vals, vals_out=None, flags_out=None, flags: int = 0, stream=None) -> None:
-    import torch
     n = keys.numel()
-    _check(_lib.hive_mixed_batch(h, _dev(ops, torch.uint8, "ops", n), _dev(keys, torch.uint32, "keys"),
-                                 _dev(vals, torch.uint32, "vals", n, optional=True), n, flags,
-                                 _dev(vals_out, torch.uint32, "vals_out", n, optional=True),
-                                 _dev(flags_out, torch.uint8, "flags_out", n, optional=True),
+    _check(_lib.hive_mixed_batch(h, _dev(ops, _U8, "ops", n), _dev(keys, _U32, "keys"),
+                                 _dev(vals, _U32, "vals", n, optional=True), n, flags,
+                                 _dev(vals_out, _U32, "vals_out", n, optional=True),
+                                 _dev(flags_out, _U8, "flags_out", n, optional=True),
                                  _stream_ptr(stream)), "hive_mixed_batch")
 
 
 def hive_mixed_batch_noalloc(h, ops, keys, vals, vals_out=None, flags_out=None, flags: int = 0,
                              stream=None) -> None:
-    import torch
     n = keys.numel()
-    _check(_lib.hive_mixed_batch_noalloc(h, _dev(ops, torch.uint8, "ops", n), _dev(keys, torch.uint32, "keys"),
-                                         _dev(vals, torch.uint32, "vals", n), n, flags,
-                                         _dev(vals_out, torch.uint32, "vals_out", n, optional=True),
-                                         _dev(flags_out, torch.uint8, "flags_out", n, optional=True),
+    _check(_lib.hive_mixed_batch_noalloc(h, _dev(ops, _U8, "ops", n), _dev(keys, _U32, "keys"),
+                                         _dev(vals, _U32, "vals", n), n, flags,
+                                         _dev(vals_out, _U32, "vals_out", n, optional=True),
+                                         _dev(flags_out, _U8, "flags_out", n, optional=True),
                                          _stream_ptr(stream)), "hive_mixed_batch_noalloc")
 
 
@@ -262,10 +269,9 @@ def hive_stats(h, stream=None) -> tuple[int, dict]:
 
 
 def hive_dump(h, words_out, where_out=None, stream=None) -> int:
-    import torch
     n = ctypes.c_uint64()
-    _check(_lib.hive_dump(h, _dev(words_out, torch.uint64, "words_out"),
-                          _dev(where_out, torch.int64, "where_out", words_out.numel(), optional=True),
+    _check(_lib.hive_dump(h, _dev(words_out, _U64, "words_out"),
+                          _dev(where_out, _I64, "where_out", words_out.numel(), optional=True),
                           words_out.numel(), ctypes.byref(n), _stream_ptr(stream)), "hive_dump")
     return int(n.value)
 
@@ -278,7 +284,7 @@ def hive_placement(h, stream=None) -> tuple[int, int, int]:
 
 def hive_live_async(h, host_dst_ptr: int, stream=None) -> None:
     """host_dst_ptr: address of 8 bytes of pinned host memory."""
-    _check(_lib.hive_live_async(h, ctypes.c_void_p(host_dst_ptr), _stream_ptr(stream)), "hive_live_async")
+    _check(_lib.hive_live_async(h, host_dst_ptr, _stream_ptr(stream)), "hive_live_async")
 
 
 def hive_clear(h, stream=None) -> None:
@@ -322,16 +328,15 @@ def hive_drain_create(slots_per_bucket: int = 16, blocks_per_cu: int = 0, ring_c
 def hive_drain_submit(d, h, op_mode, keys, vals=None, ops=None, vals_out=None, flags_out=None,
                       flags: int = 0) -> int | None:
     """Queue one batch; returns its ticket, or None when the ring is full."""
-    import torch
     n = keys.numel()
     b = hive_batch_desc()
     b.op_mode = op_mode
     b.flags = flags
-    b.d_ops = _dev(ops, torch.uint8, "ops", n, optional=True)
-    b.d_keys = _dev(keys, torch.uint32, "keys")
-    b.d_vals = _dev(vals, torch.uint32, "vals", n, optional=True)
-    b.d_vals_out = _dev(vals_out, torch.uint32, "vals_out", n, optional=True)
-    b.d_flags_out = _dev(flags_out, torch.uint8, "flags_out", n, optional=True)
+    b.d_ops = _dev(ops, _U8, "ops", n, optional=True)
+    b.d_keys = _dev(keys, _U32, "keys")
+    b.d_vals = _dev(vals, _U32, "vals", n, optional=True)
+    b.d_vals_out = _dev(vals_out, _U32, "vals_out", n, optional=True)
+    b.d_flags_out = _dev(flags_out, _U8, "flags_out", n, optional=True)
     b.n = n
     t = ctypes.c_uint64()
     status = _lib.hive_drain_submit(d, h, ctypes.byref(b), ctypes.byref(t))
@@ -375,19 +380,17 @@ HIVE_HASH_KINDS = len(HASH_KINDS)
 
 def hive_hash_buckets(kind: str, keys, m: int, out, stream=None) -> None:
     """out[i] = bucket of keys[i] under hash `kind` (uint32 GPU tensors)."""
-    import torch
     n = keys.numel()
-    _check(_lib.hive_hash_buckets(HASH_KINDS.index(kind), _dev(keys, torch.uint32, "keys"), n, m,
-                                  _dev(out, torch.uint32, "out", n), _stream_ptr(stream)), "hive_hash_buckets")
+    _check(_lib.hive_hash_buckets(HASH_KINDS.index(kind), _dev(keys, _U32, "keys"), n, m,
+                                  _dev(out, _U32, "out", n), _stream_ptr(stream)), "hive_hash_buckets")
 
 
 def hive_hash_collisions(kind: str, keys, m: int, scratch, stream=None) -> int:
     """Collision count Y of `keys` over m buckets; scratch: uint32 GPU tensor
     of at least 2 + ceil(m / 32) words."""
-    import torch
     y = ctypes.c_uint64()
-    _check(_lib.hive_hash_collisions(HASH_KINDS.index(kind), _dev(keys, torch.uint32, "keys"), keys.numel(), m,
-                                     _dev(scratch, torch.uint32, "scratch", 2 + (m + 31) // 32),
+    _check(_lib.hive_hash_collisions(HASH_KINDS.index(kind), _dev(keys, _U32, "keys"), keys.numel(), m,
+                                     _dev(scratch, _U32, "scratch", 2 + (m + 31) // 32),
                                      ctypes.byref(y), _stream_ptr(stream)), "hive_hash_collisions")
     return int(y.value)
 
@@ -395,10 +398,9 @@ def hive_hash_collisions(kind: str, keys, m: int, scratch, stream=None) -> int:
 def hive_gather_lines(table, idx, out, stream=None) -> None:
     """out[i] = XOR of the 16 words of line idx[i] of table (uint64 GPU tensor
     of n_lines x 16 words; idx uint32, out uint64 GPU tensors)."""
-    import torch
     n = idx.numel()
-    _check(_lib.hive_gather_lines(_dev(table, torch.uint64, "table"), table.numel() // 16,
-                                  _dev(idx, torch.uint32, "idx"), n, _dev(out, torch.uint64, "out", n),
+    _check(_lib.hive_gather_lines(_dev(table, _U64, "table"), table.numel() // 16,
+                                  _dev(idx, _U32, "idx"), n, _dev(out, _U64, "out", n),
                                   _stream_ptr(stream)), "hive_gather_lines")
 
 
@@ -448,20 +450,17 @@ class Table:
         hive_insert_batch(self.h, keys, vals, flags, self.stream)
 
     def lookup(self, keys):
-        import torch
         v = torch.empty(keys.numel(), dtype=torch.uint32, device=keys.device)
         f = torch.empty(keys.numel(), dtype=torch.uint8, device=keys.device)
         hive_lookup_batch(self.h, keys, v, f, self.stream)
         return v, f
 
     def delete(self, keys, flags=0):
-        import torch
         d = torch.empty(keys.numel(), dtype=torch.uint8, device=keys.device)
         hive_delete_batch(self.h, keys, d, flags, self.stream)
         return d
 
     def mixed(self, ops, keys, vals, flags=0):
-        import torch
         v = torch.empty(keys.numel(), dtype=torch.uint32, device=keys.device)
         f = torch.empty(keys.numel(), dtype=torch.uint8, device=keys.device)
         hive_mixed_batch(self.h, ops, keys, vals, v, f, flags, self.stream)
@@ -478,7 +477,6 @@ class Table:
     def dump(self, with_where=False):
         """All live words, sorted by key, as host numpy arrays."""
         import numpy as np
-        import torch
         st = self.stats()
         cap = st["live"] + st["stash_count"] + st["pending_count"] + 1
         words = torch.empty(cap, dtype=torch.uint64, device="cuda")
