@@ -286,14 +286,6 @@ struct OpsArgs {
 // Entries are (key << 32 | index); EMPTY never collides since key
 // 0xFFFFFFFF is reserved.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void fill_u64_kernel(uint64_t *p, uint64_t n, uint64_t v) {
-  for (uint64_t t = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; t < n; t += (uint64_t)gridDim.x * BLOCK) p[t] = v;
-}
-
-__global__ __launch_bounds__(BLOCK) void fill_u32_kernel(uint32_t *p, uint64_t n, uint32_t v) {
-  for (uint64_t t = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; t < n; t += (uint64_t)gridDim.x * BLOCK) p[t] = v;
-}
-
 // Record entry e = (k << 32 | index) of an operation of type `op` in the
 // set.  Plain loads come first: a key already present costs no CAS, and an
 // index that cannot win costs no max/min atomic (a stale load is only ever
@@ -1054,19 +1046,20 @@ __device__ __forceinline__ void ops_tile(const OpsArgs &a, const OpsView &view, 
   const uint64_t n_stash = view.n_stash, n_pend = view.n_pend;
   const bool overflow_used = (n_stash | n_pend) != 0;
 
-  uint32_t op = OP_NONE, k = 0, v = 0;
+  uint32_t op = OP_NONE, k = 0, v = 0, won = 0;
   if (active) {
     // the batch's inputs and outputs are touched once: non-temporal, so they
     // do not displace bucket lines from the caches (bulk step +0.7%)
     op = (MODE == OP_MIXED) ? (uint32_t)__builtin_nontemporal_load(&a.ops[i]) : MODE;
     k = __builtin_nontemporal_load(&a.keys[i]);
+    if (MODE != OP_LOOKUP && a.win) won = __builtin_nontemporal_load(&a.win[i]);  // not written for lookups, nor used
     if (op == OP_INSERT) v = __builtin_nontemporal_load(&a.vals[i]);
   }
   const bool valid = active && op <= OP_LOOKUP && valid_key(k);
   bool work = valid;
   if (work && op != OP_LOOKUP) {
     if (a.win)
-      work = __builtin_nontemporal_load(&a.win[i]) != 0;
+      work = won != 0;
     else if (a.dd)
       work = dedupe_winner(a.dd, a.dd_mask, k, (uint32_t)i);
   }
@@ -2824,7 +2817,27 @@ __global__ void ctl_zero_placement_kernel(Ctl *ctl) {
   ctl->place_second = 0;
 }
 
-__global__ void ctl_reset_kernel(Ctl *ctl, Ctl init) { *ctl = init; }
+// Empties a table: every word of its buckets and stash EMPTY, hint and filter
+// bits and shards cleared, the control block as at creation.  One launch: a
+// small table's clear is bound by launches (five before, 2 to 3 us each).
+struct ResetArgs {
+  uint64_t *buckets, *stash, *shards;  // word counts even, 16-byte aligned
+  uint32_t *bits;
+  uint64_t n_buckets, n_stash, n_shards, n_bits;
+  Ctl *ctl;
+};
+__global__ __launch_bounds__(BLOCK) void reset_kernel(ResetArgs a, Ctl init) {
+  const uint64_t first = (uint64_t)blockIdx.x * BLOCK + threadIdx.x, stride = (uint64_t)gridDim.x * BLOCK;
+  const auto fill = [&](uint64_t *p, uint64_t n, uint64_t v) {
+    for (uint64_t t = first; t < n / 2; t += stride) *(ulonglong2 *)(p + 2 * t) = ulonglong2{v, v};
+  };
+  fill(a.buckets, a.n_buckets, EMPTY);
+  fill(a.stash, a.n_stash, EMPTY);
+  fill(a.shards, a.n_shards, 0);
+  for (uint64_t t = first; t < a.n_bits; t += stride) a.bits[t] = 0u;
+  if (first == 0) *a.ctl = init;
+}
+
 __global__ void ctl_zero_dump_kernel(Ctl *ctl) { ctl->dump_count = 0; }
 
 
@@ -4046,18 +4059,6 @@ static Ctl initial_ctl(const hive_table *h) {
   return c;
 }
 
-static hive_status fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t st) {
-  if (n == 0) return HIVE_OK;
-  hipLaunchKernelGGL(fill_u64_kernel, dim3(grid_for(n, BLOCK * 8ull, 65535)), dim3(BLOCK), 0, st, p, n, v);
-  return launch_check();
-}
-
-static hive_status fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t st) {
-  if (n == 0) return HIVE_OK;
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(n, BLOCK * 8ull, 65535)), dim3(BLOCK), 0, st, p, n, v);
-  return launch_check();
-}
-
 static uint64_t hint_words(uint64_t buckets) { return (buckets + 31) / 32; }
 
 // Words of the hint bits and, from a 256-byte boundary on, the filter's.
@@ -4067,12 +4068,18 @@ static uint64_t bit_words(const hive_table *h, bool filter) {
 }
 
 static hive_status reset_table(hive_table *h, hipStream_t st) {
-  hive_status s;
-  if ((s = fill_u64(h->d_buckets, h->max_buckets * h->S * h->entry_bytes / 8, EMPTY, st)) != HIVE_OK) return s;
-  if ((s = fill_u32(h->d_hint, bit_words(h, h->spill.bits != nullptr), 0u, st)) != HIVE_OK) return s;
-  if ((s = fill_u64(h->d_stash, stash_slots_for(h->stash_cap) * h->entry_bytes / 8, EMPTY, st)) != HIVE_OK) return s;
-  if ((s = fill_u64((uint64_t *)shard_of(h->d_ctl, 0), NSHARD * SHARD_STRIDE / 8, 0, st)) != HIVE_OK) return s;
-  hipLaunchKernelGGL(ctl_reset_kernel, dim3(1), dim3(1), 0, st, h->d_ctl, initial_ctl(h));
+  ResetArgs a{};
+  a.buckets = h->d_buckets;
+  a.n_buckets = h->max_buckets * h->S * h->entry_bytes / 8;
+  a.stash = h->d_stash;
+  a.n_stash = stash_slots_for(h->stash_cap) * h->entry_bytes / 8;
+  a.shards = (uint64_t *)shard_of(h->d_ctl, 0);
+  a.n_shards = NSHARD * SHARD_STRIDE / 8;
+  a.bits = h->d_hint;
+  a.n_bits = bit_words(h, h->spill.bits != nullptr);
+  a.ctl = h->d_ctl;
+  hipLaunchKernelGGL(reset_kernel, dim3(grid_for(a.n_buckets + a.n_stash + a.n_shards, BLOCK * 8ull, 65535)),
+                     dim3(BLOCK), 0, st, a, initial_ctl(h));
   return launch_check();
 }
 
