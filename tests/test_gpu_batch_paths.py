@@ -141,11 +141,10 @@ def _dedupe_rounds(H, keys, seed, n, set32=False):
     t.close()
 
 
-@pytest.mark.parametrize("n", [1, 512, 513, 1 << 14, (1 << 14) + 1, (1 << 17) + 1, (1 << 18) + 1, (1 << 20) + 1])
+@pytest.mark.parametrize("n", [1, 255, 1023, 1024, 1025, 1 << 14, (1 << 14) + 1, (1 << 17) + 1, (1 << 18) + 1, (1 << 20) + 1])
 def test_dedupe_forms(H, n):
-    """Batches at the edges of the dedupe's forms: one block, several, the
-    two-launch form and each of its chunk sizes (a quarter of the keys are
-    reserved ones for the smallest)."""
+    """Batches at the edges of the dedupe's forms: with the probe in one block,
+    one launch of several blocks, two launches and each of their chunk sizes."""
     case(f"dedupe n={n}")
     _dedupe_rounds(H, wl.KeyStream(600).range(0, max(4, n // 2)), 600 + n, n)
 
