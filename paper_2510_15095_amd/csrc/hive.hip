@@ -1499,25 +1499,29 @@ __device__ __forceinline__ Mask interleave_slots(const uint64_t *m) {
 }
 
 // One lane's fresh copy of a whole 16-slot bucket (128 bytes, 128-byte
-// aligned) in eight 16-byte loads with the cache policy of an agent-scope
-// relaxed atomic load (sc1: served coherently, not from a stale vector-cache
-// line).  Atomic loads are at most 8 bytes wide; in the one-lane-per-item
-// shape sixteen of them cost each wave instruction 64 scattered lines, eight
-// wide ones half the instructions (bulk eviction 205 -> 162 us).  The block
-// ends in its own wait for the loads, so the registers are complete when it
-// returns.
+// aligned) in eight 16-byte loads.  The compute unit's L1 is invalidated
+// first, so that the bucket comes from the L2, as an agent-scope load's word
+// would; the first of the eight brings the line into the L1 and the others
+// find it there.  Marked as agent-scope loads (sc1) all eight went to the L2,
+// whose request rate bound the eviction launches: 112 -> 91 us in the batches
+// of a growing table, 270 -> 213 us after a 2^26-key build to 95%.  (Atomic
+// loads are at most 8 bytes wide: sixteen scattered lines of requests.)  A
+// view that is older all the same costs a failed CAS and a reload, no more.
+// The block ends in its own wait for the loads, so the registers are complete
+// when it returns.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void load_bucket16_fresh(const uint64_t *b, uint64_t *w) {
   u32x4 x0, x1, x2, x3, x4, x5, x6, x7;
   asm volatile(
-      "global_load_dwordx4 %0, %8, off sc1\n"
-      "global_load_dwordx4 %1, %8, off offset:16 sc1\n"
-      "global_load_dwordx4 %2, %8, off offset:32 sc1\n"
-      "global_load_dwordx4 %3, %8, off offset:48 sc1\n"
-      "global_load_dwordx4 %4, %8, off offset:64 sc1\n"
-      "global_load_dwordx4 %5, %8, off offset:80 sc1\n"
-      "global_load_dwordx4 %6, %8, off offset:96 sc1\n"
-      "global_load_dwordx4 %7, %8, off offset:112 sc1\n"
+      "buffer_inv sc0\n"
+      "global_load_dwordx4 %0, %8, off\n"
+      "global_load_dwordx4 %1, %8, off offset:16\n"
+      "global_load_dwordx4 %2, %8, off offset:32\n"
+      "global_load_dwordx4 %3, %8, off offset:48\n"
+      "global_load_dwordx4 %4, %8, off offset:64\n"
+      "global_load_dwordx4 %5, %8, off offset:80\n"
+      "global_load_dwordx4 %6, %8, off offset:96\n"
+      "global_load_dwordx4 %7, %8, off offset:112\n"
       "s_waitcnt vmcnt(0)\n"
       : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3), "=&v"(x4), "=&v"(x5), "=&v"(x6), "=&v"(x7)
       : "v"(b)
@@ -1536,22 +1540,23 @@ __device__ __forceinline__ void load_bucket16x2_fresh(const uint64_t *b1, const 
                                                       uint64_t *w2) {
   u32x4 x0, x1, x2, x3, x4, x5, x6, x7, y0, y1, y2, y3, y4, y5, y6, y7;
   asm volatile(
-      "global_load_dwordx4 %0, %16, off sc1\n"
-      "global_load_dwordx4 %1, %16, off offset:16 sc1\n"
-      "global_load_dwordx4 %2, %16, off offset:32 sc1\n"
-      "global_load_dwordx4 %3, %16, off offset:48 sc1\n"
-      "global_load_dwordx4 %4, %16, off offset:64 sc1\n"
-      "global_load_dwordx4 %5, %16, off offset:80 sc1\n"
-      "global_load_dwordx4 %6, %16, off offset:96 sc1\n"
-      "global_load_dwordx4 %7, %16, off offset:112 sc1\n"
-      "global_load_dwordx4 %8, %17, off sc1\n"
-      "global_load_dwordx4 %9, %17, off offset:16 sc1\n"
-      "global_load_dwordx4 %10, %17, off offset:32 sc1\n"
-      "global_load_dwordx4 %11, %17, off offset:48 sc1\n"
-      "global_load_dwordx4 %12, %17, off offset:64 sc1\n"
-      "global_load_dwordx4 %13, %17, off offset:80 sc1\n"
-      "global_load_dwordx4 %14, %17, off offset:96 sc1\n"
-      "global_load_dwordx4 %15, %17, off offset:112 sc1\n"
+      "buffer_inv sc0\n"
+      "global_load_dwordx4 %0, %16, off\n"
+      "global_load_dwordx4 %1, %16, off offset:16\n"
+      "global_load_dwordx4 %2, %16, off offset:32\n"
+      "global_load_dwordx4 %3, %16, off offset:48\n"
+      "global_load_dwordx4 %4, %16, off offset:64\n"
+      "global_load_dwordx4 %5, %16, off offset:80\n"
+      "global_load_dwordx4 %6, %16, off offset:96\n"
+      "global_load_dwordx4 %7, %16, off offset:112\n"
+      "global_load_dwordx4 %8, %17, off\n"
+      "global_load_dwordx4 %9, %17, off offset:16\n"
+      "global_load_dwordx4 %10, %17, off offset:32\n"
+      "global_load_dwordx4 %11, %17, off offset:48\n"
+      "global_load_dwordx4 %12, %17, off offset:64\n"
+      "global_load_dwordx4 %13, %17, off offset:80\n"
+      "global_load_dwordx4 %14, %17, off offset:96\n"
+      "global_load_dwordx4 %15, %17, off offset:112\n"
       "s_waitcnt vmcnt(0)\n"
       : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3), "=&v"(x4), "=&v"(x5), "=&v"(x6), "=&v"(x7), "=&v"(y0),
         "=&v"(y1), "=&v"(y2), "=&v"(y3), "=&v"(y4), "=&v"(y5), "=&v"(y6), "=&v"(y7)
