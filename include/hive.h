@@ -84,7 +84,7 @@ typedef struct {
                                  growth headroom; 0 = initial buckets) */
   uint64_t max_batch;         /* scratch preallocated for batches of this many
                                  operations (0 = grow on demand).  LINEAR
-                                 tables with post_policy also hold a full
+                                 tables with a load-factor rule also hold a full
                                  stash drain beside a batch's eviction
                                  worklist: a batch with inserts is evicted
                                  once, after the post-batch rule */
@@ -243,8 +243,8 @@ hive_status hive_dump(hive_t h, uint64_t *d_words, int64_t *d_where, uint64_t ca
 
 /* Placement census: out[0] = live bucket entries in their first candidate
  * bucket, out[1] = in their second (different) candidate, out[2] = stash and
- * pending slots in use (including deleted ones).  With two-choice placement
- * a successful lookup touches one bucket for out[0] entries and two for
+ * pending slots in use (including deleted ones).  A successful lookup of a
+ * bucket entry touches one bucket for out[0] entries and two for
  * out[1] entries.  Synchronizes `stream`. */
 hive_status hive_placement(hive_t h, uint64_t *out, void *stream);
 
@@ -271,14 +271,17 @@ const char *hive_status_string(hive_status s);
  * own stream only.  HIVE_ERR_HIP if waiting for the events failed. */
 enum {
   HIVE_PHASE_DEDUPE = 0,  /* dedupe of the batch's repeated keys (by hash
-                             partitions: collect, sums, scan, scatter, resolve) */
+                             ranges: one launch, or chunk and resolve) */
   HIVE_PHASE_PROBE = 1,   /* probe launch: replace, claim (steps 1-2), lookup, delete */
   HIVE_PHASE_EVICT = 2,   /* eviction chains (step 3); with 16-slot buckets and
                              the BitHash pair, step 4 is timed apart below,
                              otherwise it is included here */
   HIVE_PHASE_RESIZE = 3,  /* load-factor plans and split/merge passes */
   HIVE_PHASE_DRAIN = 4,   /* stash drain after splits and its re-placement */
-  HIVE_PHASE_FINISH = 5,  /* counter folds after a batch */
+  HIVE_PHASE_FINISH = 5,  /* counter folds after a batch (a launch of their
+                             own while timing is on; without it eviction
+                             launches fold, and small batches take dedupe
+                             and probe in one launch) */
   HIVE_PHASE_STASH = 6,   /* stash or pending placement of entries whose chain ran
                              out (step 4; 16-slot BitHash tables) */
   HIVE_PHASE_KINDS = 7

@@ -1,10 +1,10 @@
 // Hive hash table on MI355X (gfx950): kernels and the C ABI of include/hive.h.
 //
 // A batch runs as stream-ordered phases (launches):
-//   dedupe  (optional) a scratch open-addressing set keeps, per key, the last
-//           insert and the first delete of the batch; the others become
-//           no-ops, so repeated keys cannot leave two copies (the paper does
-//           not say what happens to repeats inside one batch);
+//   dedupe  (optional) by hash ranges in LDS: per key, the last insert and the
+//           first delete of the batch stand; the others become no-ops, so
+//           repeated keys cannot leave two copies (the paper does not say what
+//           happens to repeats inside one batch);
 //   P1      every operation: hash, match-and-elect over the first and then
 //           the second candidate bucket (Section III-F), then replace
 //           (Algorithm 1), lookup, delete (Algorithm 4) or claim-then-commit
@@ -3638,7 +3638,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
 // buckets per wave-wide load), the second after a miss, then looks up,
 // deletes (one agent-scope atomic store of EMPTY) or inserts: a key already
 // present is left as it is (there is no value to replace), a new one claims
-// the lowest EMPTY slot of the emptier candidate by a 32-bit CAS; P3 runs
+// an EMPTY slot of its first candidate while that has room to spare, else of
+// the emptier one, by a 32-bit CAS; P3 runs
 // the bounded cuckoo chains one lane per item on fresh copies of whole
 // buckets, then the stash or the pending list.  FIXED addressing, BitHash1/2,
 // plain launches.
@@ -4645,8 +4646,10 @@ static hive_status run_batch(hive_t h, uint32_t mode, const uint8_t *d_ops, cons
   // full drain.
   const uint64_t wl_post = n + drain_words(h) + WL_SLACK;
   const bool rules = linear && (h->cfg.post_policy || h->cfg.pre_expand);
+  // (a table without the post-batch rule does not grow its worklist for this
+  // alone: a call that needed no allocation before needs none)
   const bool place_last = rules && inserts && h->entry_bytes == 8 && !h->timing &&
-                          (!no_alloc || wl_post <= h->wl_cap);
+                          (wl_post <= h->wl_cap || (!no_alloc && (n > h->wl_cap || h->cfg.post_policy)));
   // only inserts reach the eviction worklist
   const uint64_t wl_need = inserts ? (place_last ? wl_post : n) : 0;
   uint64_t *dd = nullptr;
@@ -4864,8 +4867,9 @@ hive_status hive_create(const hive_config *cfg_in, uint64_t initial_buckets, voi
   const uint64_t min_wl = drain_words(h);
   // a table with a load-factor rule places a batch's worklist after the
   // rules, together with the drain (see run_batch)
-  const uint64_t batch_wl = cfg.addressing == HIVE_LINEAR && (cfg.post_policy || cfg.pre_expand) && cfg.max_batch
-                                ? cfg.max_batch + min_wl + WL_SLACK
+  // (of at least min_wl operations)
+  const uint64_t batch_wl = cfg.addressing == HIVE_LINEAR && (cfg.post_policy || cfg.pre_expand)
+                                ? std::max(cfg.max_batch, min_wl) + min_wl + WL_SLACK
                                 : cfg.max_batch;
   if ((s = ensure_scratch(h, std::max<uint64_t>(batch_wl, min_wl), cfg.max_batch, st)) != HIVE_OK) {
     free_table(h);
