@@ -4252,8 +4252,9 @@ static hive_status ensure_scratch(hive_table *h, uint64_t n, uint64_t n_dd, hipS
 
 // Probe-kernel variants a table may select per operation kind
 // (hive_config.probe_tuning): occupancy target in waves per SIMD and loads
-// in flight per probe chunk.  Variant 0 is the default; the others exist
-// for 16-slot BitHash tables probing the second candidate after a miss
+// in flight per probe chunk.  Variant 0 is the default, which
+// launch_ops_mode may replace by variant 4; the others exist for
+// 16-slot BitHash tables probing the second candidate after a miss
 // (probe_both = 0).  The insert kernel's fused round holds twice the loads,
 // so variants 1 and 2 would spill registers there and are refused for
 // inserts (kInsertTunings).
@@ -4264,11 +4265,30 @@ static constexpr ProbeTuning kProbeTunings[] = {{OPS_WAVES_PER_EU, 16}, {6, 16},
 static constexpr int kNumProbeTunings = sizeof(kProbeTunings) / sizeof(kProbeTunings[0]);
 static constexpr uint32_t kInsertTunings = (1u << 0) | (1u << 3) | (1u << 4);
 
+// By default, a 16-slot BitHash table with a spill filter takes variant 4
+// (8 waves per SIMD, 4 loads in flight).  The filter ends nearly every miss
+// at its first bucket, so an operation is one dependent load or two and
+// more waves hide it better than more loads per wave: lookups of 2^22 keys
+// in us at 4 waves and 16 loads, then at 8 and 4: tables of 2^20 keys at
+// load 0.9 34.7 and 27.6, 2^22 110.6 and 90.4, 2^26 148 and 133; deletes of
+// 2^22 keys at 2^26 291 and 283, replacements 290 and 281, inserts equal.
+// The exception is a lookup of more than WIDE_LOOKUP_MAX keys in buckets
+// larger than the last-level cache: there memory is the bound and the 16
+// loads a wave keeps in flight use it better (2^26 keys in 2^26: 2.05 ms,
+// against 2.08 with 8 and 4; equal at 2^24 keys, 533 and 530 us).  Tables
+// without a filter stay at variant 0: 2^22 lookups at load 0.6 127 us
+// against 131, deletes within 4 % of each other, first inserts into 2^18
+// buckets' worth of keys 112 against 97 but later ones 48 against 55.
+static constexpr uint64_t LAST_LEVEL_CACHE = 256ull << 20;
+static constexpr uint64_t WIDE_LOOKUP_MAX = 1ull << 24;
+
 template <int S, uint32_t MODE, bool BOTH, int PAIR = PAIR_BITHASH, int V = 0>
 static void launch_ops(const OpsArgs &a, uint32_t grid_cap, hipStream_t st) {
   constexpr ProbeTuning t = kProbeTunings[V];
+  // where launch_ops_mode leaves variant 0 to lookups
+  constexpr bool kReplaced = S == 16 && PAIR == PAIR_BITHASH && V == 0 && MODE != OP_LOOKUP;
   const uint64_t blocks = std::min<uint64_t>((a.n + BLOCK - 1) / BLOCK, grid_cap ? grid_cap : OPS_GRID);
-  if constexpr (!BOTH && PairArity<PAIR>::D == 2) {
+  if constexpr (!BOTH && PairArity<PAIR>::D == 2 && !kReplaced) {
     if (a.spill.bits) {
       hipLaunchKernelGGL((ops_kernel<S, MODE, BOTH, PAIR, t.waves_per_simd, t.loads_in_flight, FILTER_USE>),
                          dim3((unsigned)blocks), dim3(BLOCK), 0, st, a);
@@ -4282,7 +4302,7 @@ static void launch_ops(const OpsArgs &a, uint32_t grid_cap, hipStream_t st) {
 template <int S, bool BOTH, int PAIR = PAIR_BITHASH, int V = 0>
 static void launch_ops_mode_v(uint32_t mode, const OpsArgs &a, uint32_t grid_cap, hipStream_t st) {
   // inserts never take the variants hive_create refuses for them
-  constexpr int VI = ((kInsertTunings >> V) & 1u) ? V : 0;
+  constexpr int VI = ((kInsertTunings >> V) & 1u) ? V : 4;
   switch (mode) {
     case OP_INSERT: launch_ops<S, OP_INSERT, BOTH, PAIR, VI>(a, grid_cap, st); break;
     case OP_DELETE: launch_ops<S, OP_DELETE, BOTH, PAIR, V>(a, grid_cap, st); break;
@@ -4294,7 +4314,11 @@ static void launch_ops_mode_v(uint32_t mode, const OpsArgs &a, uint32_t grid_cap
 template <int S, bool BOTH, int PAIR = PAIR_BITHASH>
 static void launch_ops_mode(uint32_t mode, const OpsArgs &a, const hive_config &cfg, hipStream_t st) {
   if constexpr (S == 16 && !BOTH && PAIR == PAIR_BITHASH) {
-    switch ((cfg.probe_tuning >> (4 * std::min<uint32_t>(mode, OP_MIXED))) & 15u) {
+    uint32_t v = (cfg.probe_tuning >> (4 * std::min<uint32_t>(mode, OP_MIXED))) & 15u;
+    if (v == 0 && a.spill.bits &&
+        !(mode == OP_LOOKUP && a.n > WIDE_LOOKUP_MAX && cfg.max_buckets * (S * 8) > LAST_LEVEL_CACHE))
+      v = 4;
+    switch (v) {
       case 1: launch_ops_mode_v<S, BOTH, PAIR, 1>(mode, a, cfg.probe_grid, st); return;
       case 2: launch_ops_mode_v<S, BOTH, PAIR, 2>(mode, a, cfg.probe_grid, st); return;
       case 3: launch_ops_mode_v<S, BOTH, PAIR, 3>(mode, a, cfg.probe_grid, st); return;

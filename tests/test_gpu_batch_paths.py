@@ -362,3 +362,26 @@ def test_spilled_keys_stay_reachable(H, S, set32, cfg):
         H.hive_drain_destroy(d)
         check()
     t.close()
+
+
+@pytest.mark.parametrize("nb", [1 << 21, (1 << 21) + 1])
+@pytest.mark.parametrize("n", [1 << 24, (1 << 24) + 1])
+def test_large_lookups_on_both_sides_of_the_variant_rule(H, nb, n):
+    """Buckets of 256 MiB and just beyond, looked up by 2^24 keys and one
+    more, with keys that were never there and keys in either bucket."""
+    case(f"large lookups nb={nb} n={n}")
+    import torch
+    keys = wl.KeyStream(31).range(0, 1 << 16)
+    t = make(H, 16, nb)
+    t.insert(dev(keys), dev(wl.values_for(keys)))
+    gone = keys[::5]
+    assert host(t.delete(dev(gone))).all()
+    q = np.resize(np.concatenate([keys, wl.KeyStream(31).range(1 << 16, (1 << 16) + 7919)]), n)
+    v, f = t.lookup(dev(q))
+    there = np.ones(keys.size + 7919, bool)
+    there[keys.size:] = False
+    there[: keys.size : 5] = False
+    there = np.resize(there, n)
+    assert np.array_equal(host(f).astype(bool), there)
+    assert np.array_equal(host(v), np.where(there, wl.values_for(q), np.uint32(M32)))
+    t.close()
