@@ -211,11 +211,14 @@ __global__ __launch_bounds__(64) void finish_kernel(Ctl *c) {
 // was ever deleted, a first candidate with first_min EMPTY slots always had
 // them, so none of its keys is elsewhere and the bits are not even read.
 //
-// Bulk build of 2^26 keys to 95% load, without / with: inserts 3.82 / 3.85 ms,
+// Bulk build of 2^26 keys to 95% load, without / with: inserts 3.82 / 3.36 ms,
 // lookups at 50% and 25% hits 2.22 / 2.05 and 2.52 / 2.26, deletes 1.45 / 1.40;
-// 2^24 lookups in a table of 2^24 keys 543 / 425 us.  (A new key in its second
-// candidate costs an atomic on its bit; reading the filter for every insert
-// would add 0.5 ms.)
+// 2^24 lookups in a table of 2^24 keys 543 / 425 us.  What it costs is an
+// atomic on its bit for each new key in its second candidate, so builds gain
+// while the table is mostly empty and batches of new keys into a loaded one
+// pay: 2^26-key table, HIVE_UNIQUE slices 0-55-65-75-85-90-95% without
+// 2,200, 435, 430, 439, 247, 311 us, with 1,617, 382, 420, 465, 276, 418 (the
+// last also runs twice the chains; first_min 8: 351, and 1,735 for the first).
 //
 // first_min: more packs first candidates less tightly (fewer chains), less
 // leaves more keys in them.  At 16 slots and 95% load, two-choice / 5 / 3:
@@ -1107,10 +1110,18 @@ __device__ __forceinline__ void ops_tile(const OpsArgs &a, const OpsView &view, 
         // it saved (2^26 lookups at 50% hits 2.21 ms, against 2.05 so and
         // 2.22 without a filter)
         const bool near_full = (uint32_t)popc_mask(s_e[0][wv][lane]) < a.spill.first_min;
-        marked = work && m1 == 0 && (near_full || MODE == OP_MIXED || MODE == OP_DELETE || view.removed) &&
+        // An insert that finds its first candidate near full reads the
+        // second whatever the filter says, and skips the filter's own line
+        // unless the overflow may hold the key; it may then set a bit that
+        // is set.  The line and its wait before the second round cost more
+        // than those atomics: a build of 2^26 keys to 95% takes 3.36 ms
+        // against 3.74, 7.1 M new keys at 55-65% load 0.38 ms against 0.42
+        const bool both = op == OP_INSERT && near_full;
+        marked = work && m1 == 0 &&
+                 (both ? overflow_used : near_full || MODE == OP_MIXED || MODE == OP_DELETE || view.removed) &&
                  spill_test(a.spill, c1, k);
         spilled = marked;
-        need2 = need2 && (spilled || (op == OP_INSERT && near_full));
+        need2 = need2 && (spilled || both);
       }
     }
     const uint64_t need2_mask = ballot(need2);
@@ -3763,13 +3774,15 @@ __global__ __launch_bounds__(BLOCK) void set_ops_kernel(SetArgs a) {
     const uint32_t m1 = s_m[0][wv][lane], e1 = s_e[0][wv][lane];
     // filter and placement as for 64-bit entries (ops_tile)
     const bool near_full = (uint32_t)__builtin_popcount(e1) < a.spill.first_min;
+    const bool both = op == OP_INSERT && near_full;
     bool spilled = true, marked = false;
     if (a.spill.bits) {
-      marked = work && m1 == 0 && (near_full || MODE == OP_MIXED || MODE == OP_DELETE || removed) &&
+      marked = work && m1 == 0 &&
+               (both ? overflow_used : near_full || MODE == OP_MIXED || MODE == OP_DELETE || removed) &&
                spill_test(a.spill, c1, k);
       spilled = marked;
     }
-    const bool need2 = work && m1 == 0 && c2 != c1 && (spilled || (op == OP_INSERT && near_full));
+    const bool need2 = work && m1 == 0 && c2 != c1 && (spilled || both);
     const uint64_t need2_mask = ballot(need2);
     const int n2 = __popcll(need2_mask);
     compact_second(need2, need2_mask, n2, k, c2, c1, lane, s_k2[wv], s_b2[wv], s_list[wv]);
