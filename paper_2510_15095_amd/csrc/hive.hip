@@ -1992,7 +1992,11 @@ __global__ __launch_bounds__(BLOCK) void evict_lanes_kernel(EvictArgs a) {
         uint32_t good = 0;
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-          const uint32_t k = key_of(odd ? w[2 * q + 1] : w[2 * q]);
+          // both words by value: `odd ? w[i] : w[j]` selects an address, which
+          // put w into scratch memory, written by every load of a bucket (new
+          // keys into a 2^26-key table at 90-95 and 95-97% load 313 and 273
+          // us; so 285 and 203)
+          const uint32_t k0 = key_of(w[2 * q]), k1 = key_of(w[2 * q + 1]), k = odd ? k1 : k0;
           const uint32_t a1 = address(geo, HashPair<PAIR>::h1(k)), a2 = address(geo, HashPair<PAIR>::h2(k));
           const uint32_t alt = b == a1 ? a2 : a1;
           good |= (alt != b && (alt < geo.sp || alt > geo.im) ? 1u : 0u) << (2 * q);
