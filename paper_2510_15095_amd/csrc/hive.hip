@@ -220,12 +220,19 @@ __global__ __launch_bounds__(64) void finish_kernel(Ctl *c) {
 // 2,200, 435, 430, 439, 247, 311 us, with 1,617, 382, 420, 465, 276, 418 (the
 // last also runs twice the chains; first_min 8: 351, and 1,735 for the first).
 //
-// first_min: more packs first candidates less tightly (fewer chains), less
-// leaves more keys in them.  At 16 slots and 95% load, two-choice / 5 / 3:
-// keys in their second candidate 33 / 16 / 14%, inserts that need eviction
-// 0.34 / 0.69 / 1.5%.  Tables with an eviction bound under FIRST_MIN_CHAIN
-// place by two-choice alone: without chains, packed first candidates would
-// send entries to the stash.
+// first_min, a share of the slots: less leaves more keys in their first
+// candidate, and costs chains and stash entries once the table is nearly full,
+// since buckets that few keys have first stay emptier than two-choice would
+// leave them.  2^22 keys built to 95% load in 16-slot buckets, two-choice /
+// 8 / 6 / 5 sixteenths: stash entries 1 / 12 / 28 / 89, and of 2^26 keys 0 / 2 /
+// 43 / 158; the build, two sets of lookups and a delete of 2^26 keys 9,950 /
+// 9,480 / 9,210 / 9,090 us.  (A fixed 5 slots is less than a sixth of a 32-slot
+// bucket: 637 stash entries of 2^21 keys in a key-only set where two-choice has
+// none.)
+// Two-choice alone, and no filter, where chains or the stash have little room:
+// tables with an eviction bound under FIRST_MIN_CHAIN, and those whose stash
+// holds less than the default 1% of the slots (a stash sized for two-choice
+// placement may not hold the entries above).
 // shift: 8 bits a bucket while the filter stays within FILTER_BYTES, so that
 // it is served by the L2s while bucket lines stream through them; at 95% load
 // a missing key finds its bit set with probability 0.74 / 0.59 / 0.41 / 0.25
@@ -234,7 +241,7 @@ __global__ __launch_bounds__(64) void finish_kernel(Ctl *c) {
 // would be set, and splits would have to hand them on (growth to 12.6 M keys
 // and back 3,500 us without, 3,840 with; mixed batches the same either way).
 // ---------------------------------------------------------------------------
-constexpr uint32_t FIRST_MIN = 5;
+constexpr uint32_t FIRST_MIN_16THS = 6;
 constexpr uint32_t FIRST_MIN_CHAIN = 4;
 constexpr uint64_t FILTER_BYTES = 5ull << 20;
 
@@ -4887,8 +4894,8 @@ hive_status hive_create(const hive_config *cfg_in, uint64_t initial_buckets, voi
   cfg.max_buckets = max_b;
   h->cfg = cfg;
   const bool filter = cfg.addressing == HIVE_FIXED && cfg.hash_pair != HIVE_PAIR_TRIPLE && !cfg.probe_both &&
-                      cfg.max_evictions >= FIRST_MIN_CHAIN;
-  h->spill.first_min = filter ? FIRST_MIN : S + 1;  // S + 1: by two-choice alone
+                      cfg.max_evictions >= FIRST_MIN_CHAIN && h->stash_cap >= max_b * S / 100;
+  h->spill.first_min = filter ? S * FIRST_MIN_16THS / 16 : S + 1;  // S + 1: by two-choice alone
   h->spill.shift = 3;
   while (h->spill.shift > 0 && (max_b << h->spill.shift) / 8 > FILTER_BYTES) --h->spill.shift;
   hive_status s = HIVE_OK;
