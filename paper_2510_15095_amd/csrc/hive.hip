@@ -223,12 +223,11 @@ __global__ __launch_bounds__(64) void finish_kernel(Ctl *c) {
 // first_min, a share of the slots: less leaves more keys in their first
 // candidate, and costs chains and stash entries once the table is nearly full,
 // since buckets that few keys have first stay emptier than two-choice would
-// leave them.  2^22 keys built to 95% load in 16-slot buckets, two-choice /
-// 8 / 6 / 5 sixteenths: stash entries 1 / 12 / 28 / 89, and of 2^26 keys 0 / 2 /
-// 43 / 158; the build, two sets of lookups and a delete of 2^26 keys 9,950 /
-// 9,480 / 9,210 / 9,090 us.  (A fixed 5 slots is less than a sixth of a 32-slot
-// bucket: 637 stash entries of 2^21 keys in a key-only set where two-choice has
-// none.)
+// leave them.  2^21 keys built to 95% load in 16-slot buckets, two-choice /
+// 7 / 6 / 5 sixteenths: stash entries 3 / 32 / 59 / 139; the build, two sets of
+// lookups and a delete of 2^26 keys 9,950 / 9,340 / 9,210 / 9,090 us.  (A fixed
+// 5 slots is less than a sixth of a 32-slot bucket: 637 stash entries of 2^21
+// keys in a key-only set where two-choice has none.)
 // Two-choice alone, and no filter, where chains or the stash have little room:
 // tables with an eviction bound under FIRST_MIN_CHAIN, and those whose stash
 // holds less than the default 1% of the slots (a stash sized for two-choice
@@ -241,7 +240,7 @@ __global__ __launch_bounds__(64) void finish_kernel(Ctl *c) {
 // would be set, and splits would have to hand them on (growth to 12.6 M keys
 // and back 3,500 us without, 3,840 with; mixed batches the same either way).
 // ---------------------------------------------------------------------------
-constexpr uint32_t FIRST_MIN_16THS = 6;
+constexpr uint32_t FIRST_MIN_16THS = 7;
 constexpr uint32_t FIRST_MIN_CHAIN = 4;
 constexpr uint64_t FILTER_BYTES = 5ull << 20;
 
