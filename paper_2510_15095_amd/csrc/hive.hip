@@ -158,8 +158,9 @@ __device__ __forceinline__ uint64_t wl_slot(const uint64_t *pre, uint64_t k, uin
 
 // Fold the shards into the totals of Ctl line 1 (one full wave; nothing else
 // may update this table's shards meanwhile).  With wl_done the worklist's
-// items are counted and its segments emptied.  Returns the worklist size.
-__device__ __forceinline__ uint64_t fold_shards_wave(Ctl *c, bool wl_done) {
+// items are counted and its segments emptied.  `inserts`: operations of the
+// batch that may have inserted (Ctl::inserted).  Returns the worklist size.
+__device__ __forceinline__ uint64_t fold_shards_wave(Ctl *c, bool wl_done, uint64_t inserts = 0) {
   const int lane = threadIdx.x & 63;
   Shard *sh = shard_of(c, lane);
   // the last pair: stash placements made without a reservation join the
@@ -185,14 +186,15 @@ __device__ __forceinline__ uint64_t fold_shards_wave(Ctl *c, bool wl_done) {
     for (int f = 0; f < NF; ++f)
       if (v[f]) add64(dst[f], v[f]);
     if (wl_done && total_wl) add64(&c->evict_items, total_wl);
+    if (inserts) add64(&c->inserted, inserts);
   }
   return total_wl;
 }
 
 // After a batch without inserts, and while phases are timed (one wave of 64
 // threads).
-__global__ __launch_bounds__(64) void finish_kernel(Ctl *c) {
-  (void)fold_shards_wave(c, true);
+__global__ __launch_bounds__(64) void finish_kernel(Ctl *c, uint64_t inserts) {
+  (void)fold_shards_wave(c, true, inserts);
 }
 
 // ---------------------------------------------------------------------------
@@ -206,19 +208,33 @@ __global__ __launch_bounds__(64) void finish_kernel(Ctl *c) {
 // whenever a key whose first candidate is b is put anywhere else (its second
 // candidate, the stash, the pending list), the bit that the key picks is set.
 // A search that finds nothing in the first candidate and whose bit is clear is
-// over: one line.  Bits are never cleared but with the table (a stale one
-// only costs the second probe that every miss took before).  While no entry
-// was ever deleted, a first candidate with first_min EMPTY slots always had
-// them, so none of its keys is elsewhere and the bits are not even read.
+// over: one line, and the filter's.  While no entry was ever deleted, a first
+// candidate with first_min EMPTY slots always had them, so none of its keys is
+// elsewhere and the bits are not even read.
 //
-// Bulk build of 2^26 keys to 95% load, without / with: inserts 3.82 / 3.36 ms,
-// lookups at 50% and 25% hits 2.22 / 2.05 and 2.52 / 2.26, deletes 1.45 / 1.40;
-// 2^24 lookups in a table of 2^24 keys 543 / 425 us.  What it costs is an
-// atomic on its bit for each new key in its second candidate, so builds gain
-// while the table is mostly empty and batches of new keys into a loaded one
-// pay: 2^26-key table, HIVE_UNIQUE slices 0-55-65-75-85-90-95% without
-// 2,200, 435, 430, 439, 247, 311 us, with 1,617, 382, 420, 465, 276, 418 (the
-// last also runs twice the chains; first_min 8: 351, and 1,735 for the first).
+// It serves a table's first fill.  Bits are only cleared with the table: under
+// inserts and deletes more and more are set, and a search whose bit is set
+// takes three accesses where it would take two (2^24 keys at 90% load, lookups
+// with no hits, before and after six turnovers of the contents 109 and 174 us,
+// without a filter 165 throughout); and new keys for a loaded table mostly go
+// to their second candidate, each with an atomic on its bit and after a second
+// dependent round.  So a batch that starts when FILTER_START_PCT of the slots'
+// number was inserted, or ends beyond FILTER_END_PCT, is `plain`: placed by
+// two-choice, both candidates in one round, and the filter is dropped until the
+// table is cleared.  (One batch of 2^21 keys to 97 / 99% load: two-choice 200 /
+// 240 us and 94 / 3,858 stash entries, packed 217 / 267 us and 624 / 7,301.
+// Wider buckets gain at any load: 2^25 keys in 32 slots to 99%, 3,237 us, packed
+// 2,638.)  The host counts
+// along (hive_table::inserted) and launches the kernels built without a filter
+// then; the device's own count and flag decide what the bits are worth, for
+// replays of captured launches and for the executor.
+// Slices of new keys into a 2^26-key table, 0-55-65-75-85-90-95-97%, without a
+// filter: 2,083, 428, 426, 440, 251, 320, 261 us, so: 1,609, 423, 427, 436, 244,
+// 288, 212; with the filter kept up throughout: 1,539, 373, 410, 452, 273, 412,
+// 392 (the last two with the buckets of chains in scratch memory).  A limit of
+// 75% was slower between 55 and 75% (2^22 keys: 65 and 73 us a slice against 49
+// and 51).  One batch to 95% of 2^26 keys 3,610 / 3,229 us, lookups at 50% hits
+// after it 2,080 / 1,920; 2^24 lookups in a table of 2^24 keys 504 / 424 us.
 //
 // first_min, a share of the slots: less leaves more keys in their first
 // candidate, and costs chains and stash entries once the table is nearly full,
@@ -241,6 +257,8 @@ __global__ __launch_bounds__(64) void finish_kernel(Ctl *c) {
 // and back 3,500 us without, 3,840 with; mixed batches the same either way).
 // ---------------------------------------------------------------------------
 constexpr uint32_t FIRST_MIN_16THS = 7;
+constexpr uint64_t FILTER_START_PCT = 55;
+constexpr uint64_t FILTER_END_PCT = 96;  // 16-slot buckets
 constexpr uint32_t FIRST_MIN_CHAIN = 4;
 constexpr uint64_t FILTER_BYTES = 5ull << 20;
 
@@ -248,7 +266,32 @@ struct Spill {
   uint32_t *bits;  // null: the table has no filter
   uint32_t shift;
   uint32_t first_min;
+  uint64_t start, end;  // a batch keeps it up that starts below and ends within these numbers of inserts
 };
+
+// The filter as a batch meets it: `plain`, when the batch places by two-choice
+// alone and sets no bits; `dropped`, when a plain batch ran since the table was
+// empty and the bits mean nothing any more.  Both stay as they are while the
+// batch's launches run (Ctl::inserted moves at their end), but for `dropped`,
+// which its probe launch sets when it is plain.
+struct SpillState {
+  bool plain, dropped;
+};
+__device__ __forceinline__ SpillState spill_state(const Spill &f, const Ctl *c, uint64_t n) {
+  SpillState s;
+  const uint64_t inserted = ld_ctl(&c->inserted);
+  s.dropped = ld_ctl32(&c->dropped) != 0;
+  s.plain = s.dropped || inserted >= f.start || inserted + n > f.end;
+  return s;
+}
+
+// No filter, two-choice placement.
+__host__ __device__ __forceinline__ Spill spill_none(uint32_t S) { return Spill{nullptr, 0, S + 1, 0, 0}; }
+
+// The filter that a placement phase keeps up.
+__device__ __forceinline__ Spill spill_placing(const Spill &f, const Ctl *c, uint64_t n, uint32_t S) {
+  return f.bits && !spill_state(f, c, n).plain ? f : spill_none(S);
+}
 
 __device__ __forceinline__ uint64_t spill_bit(const Spill &f, uint32_t c1, uint32_t k) {
   return ((uint64_t)c1 << f.shift) | (((k * 0x9E3779B1u) >> 29) & ((1u << f.shift) - 1u));
@@ -993,14 +1036,17 @@ struct OpsView {
   Geo geo;
   uint64_t n_stash, n_pend;
   bool removed;  // an entry may have been deleted since the table was empty
+  SpillState spill;
 };
 
-__device__ __forceinline__ OpsView read_view(const Ctl *c, uint64_t stash_cap, uint64_t pending_cap) {
+__device__ __forceinline__ OpsView read_view(const Ctl *c, uint64_t stash_cap, uint64_t pending_cap,
+                                             const Spill &spill, uint64_t n) {
   OpsView v;
   v.geo = read_geo(c);
   v.n_stash = min(ld_ctl(&c->stash_count), stash_cap);
   v.n_pend = min(ld_ctl(&c->pending_count), pending_cap);
   v.removed = ld_ctl32(&c->removed) != 0;
+  v.spill = spill_state(spill, c, n);
   return v;
 }
 
@@ -1018,6 +1064,17 @@ __device__ __forceinline__ void ops_counts_add(Ctl *c, uint64_t unit, int64_t li
 // a first candidate has room.
 __device__ __forceinline__ void set_removed(Ctl *c) {
   __hip_atomic_store(&c->removed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The end of a probe launch or phase, by one thread: what it did to the filter
+// (`filter`: it was given one).  Deletes are noted without one, too: replayed
+// launches may have cleared the table and filled it with a filter again since
+// the host dropped it.
+template <uint32_t MODE>
+__device__ __forceinline__ void ops_done(Ctl *c, const OpsView &view, bool filter) {
+  if ((MODE == OP_MIXED || MODE == OP_DELETE) && !view.removed) set_removed(c);
+  if ((MODE == OP_MIXED || MODE == OP_INSERT) && (!filter || view.spill.plain) && !view.spill.dropped)
+    __hip_atomic_store(&c->dropped, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // P1 for one tile of WAVES x 64 operations [tile * 256, tile * 256 + 256).
@@ -1091,6 +1148,9 @@ __device__ __forceinline__ void ops_tile(const OpsArgs &a, const OpsView &view, 
   // spilled: the key may be outside its first candidate; marked: its filter
   // bit is known to be set
   bool spilled = true, marked = false;
+  // a plain batch, or one after it, goes without the filter
+  const bool filtered = (MODE == OP_LOOKUP || MODE == OP_DELETE) ? !view.spill.dropped : !view.spill.plain;
+  const uint32_t first_min = FILTER == FILTER_NONE || filtered ? a.spill.first_min : (uint32_t)S + 1;
   Mask m1;
   bool need2;
   if constexpr (kFused) {
@@ -1110,12 +1170,12 @@ __device__ __forceinline__ void ops_tile(const OpsArgs &a, const OpsView &view, 
     m1 = s_m[0][wv][lane];
     need2 = work && m1 == 0 && c2 != c1;
     if constexpr (FILTER != FILTER_NONE && !D3) {
-      if (FILTER == FILTER_USE || a.spill.bits) {
+      if ((FILTER == FILTER_USE || a.spill.bits) && filtered) {
         // the filter is read by the lanes that missed alone, and after the
         // round: read with it, by every lane, it cost more line reads than
         // it saved (2^26 lookups at 50% hits 2.21 ms, against 2.05 so and
         // 2.22 without a filter)
-        const bool near_full = (uint32_t)popc_mask(s_e[0][wv][lane]) < a.spill.first_min;
+        const bool near_full = (uint32_t)popc_mask(s_e[0][wv][lane]) < first_min;
         // An insert that finds its first candidate near full reads the
         // second whatever the filter says, and skips the filter's own line
         // unless the overflow may hold the key; it may then set a bit that
@@ -1236,7 +1296,7 @@ __device__ __forceinline__ void ops_tile(const OpsArgs &a, const OpsView &view, 
       dl = 1;
       Mask f_first = e1, f_second = (c2 != c1) ? e2 : (Mask)0;
       uint32_t b_first = c1, b_second = c2;
-      if (popc_mask(f_second) > popc_mask(f_first) && (D3 || (uint32_t)popc_mask(f_first) < a.spill.first_min)) {
+      if (popc_mask(f_second) > popc_mask(f_first) && (D3 || (uint32_t)popc_mask(f_first) < first_min)) {
         const Mask tm = f_first;
         f_first = f_second;
         f_second = tm;
@@ -1280,8 +1340,8 @@ __device__ __forceinline__ void ops_tile(const OpsArgs &a, const OpsView &view, 
           f_first &= (Mask)~((Mask)1 << s);
       }
       to_wl = !placed;
-      if constexpr (!D3) {
-        if (placed && b_first != c1 && !marked) spill_mark(a.spill, c1, k);
+      if constexpr (!D3 && FILTER != FILTER_NONE) {
+        if (filtered && placed && b_first != c1 && !marked) spill_mark(a.spill, c1, k);
       }
     }
   }
@@ -1320,16 +1380,14 @@ template <int S, uint32_t MODE, bool BOTH, int PAIR = PAIR_BITHASH, int WPE = OP
           int PIPE = Traits<S>::CH, int FILTER = FILTER_NONE>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE))) void ops_kernel(OpsArgs a) {
   __shared__ OpsShared<S, PairArity<PAIR>::D> sh;
-  const OpsView view = read_view(a.ctl, a.stash_cap, a.pending_cap);
+  const OpsView view = read_view(a.ctl, a.stash_cap, a.pending_cap, a.spill, a.n);
   const uint64_t ntiles = (a.n + BLOCK - 1) / BLOCK;
   int64_t live_acc = 0;
   uint64_t bad_acc = 0;
   for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x)
     ops_tile<S, MODE, BOTH, PAIR, PIPE, FILTER>(a, view, tile, sh, live_acc, bad_acc);
   ops_counts_add(a.ctl, (uint64_t)blockIdx.x * WAVES + (threadIdx.x >> 6), live_acc, bad_acc);
-  if constexpr (FILTER != FILTER_NONE && (MODE == OP_MIXED || MODE == OP_DELETE)) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) set_removed(a.ctl);
-  }
+  if (MODE != OP_LOOKUP && blockIdx.x == 0 && threadIdx.x == 0) ops_done<MODE>(a.ctl, view, FILTER != FILTER_NONE);
 }
 
 // ---------------------------------------------------------------------------
@@ -1358,7 +1416,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void small_batch_kernel(OpsArgs a, uin
   const DdsArgs d{a.ops, a.keys, win, (uint32_t)a.n, MODE, 0};
   uint64_t e[1];
   dds_read<SMALL_BLOCK, 1>(d, 0, 0, 1ull << 32, e);
-  const OpsView view = read_view(a.ctl, a.stash_cap, a.pending_cap);
+  const OpsView view = read_view(a.ctl, a.stash_cap, a.pending_cap, a.spill, a.n);
   __syncthreads();
   const bool keep_last = MODE == OP_MIXED ? ((uint32_t)e[0] >> 31) == 0 : MODE == OP_INSERT;
   if (e[0] != EMPTY) dds_settle<SMALL_TAB>(sh.tab, e[0], keep_last, nullptr);
@@ -1375,9 +1433,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void small_batch_kernel(OpsArgs a, uin
                                                                  bad_acc);
     ops_counts_add(a.ctl, tile * WAVES + (tid >> 6) % WAVES, live_acc, bad_acc);
   }
-  if constexpr (FILTER != FILTER_NONE && MODE != OP_INSERT) {
-    if (tid == 0) set_removed(a.ctl);
-  }
+  if (tid == 0) ops_done<MODE>(a.ctl, view, FILTER != FILTER_NONE);
 }
 
 // ---------------------------------------------------------------------------
@@ -1395,6 +1451,7 @@ struct EvictArgs {
   uint64_t stash_cap;
   uint64_t pending_cap;
   uint32_t max_evictions;
+  uint64_t inserts;  // operations of the batch that may have inserted
 };
 
 __device__ __forceinline__ void set_hint(uint32_t *hint, uint32_t b) { or32(&hint[b >> 5], 1u << (b & 31)); }
@@ -1450,6 +1507,7 @@ __device__ __forceinline__ int overflow_place(const EvictArgs &a, const Geo &geo
 template <int PAIR>
 __device__ __forceinline__ void evict_mark(const EvictArgs &a, const Geo &geo, uint64_t kv, uint32_t b) {
   if constexpr (PairArity<PAIR>::D == 2) {
+    if (!a.spill.bits) return;  // without a filter the hash is not computed either
     const uint32_t c1 = address(geo, HashPair<PAIR>::h1(key_of(kv)));
     if (b != c1) spill_mark(a.spill, c1, key_of(kv));
   }
@@ -1874,7 +1932,7 @@ __device__ __forceinline__ void evict_counters(const EvictArgs &a, bool unreserv
 // finishes last folds the shards into the totals and empties the worklist;
 // with no items, block 0 does (the other blocks have nothing to write).  A
 // launch of its own for this took 2.9 us and a host call per batch.
-__device__ __forceinline__ void evict_finish(Ctl *c, bool items);
+__device__ __forceinline__ void evict_finish(Ctl *c, bool items, uint64_t inserts);
 
 // P3 as a launch: every worklist item through evict_round (step 2 again,
 // then the bounded chain of Algorithm 3, then the stash or the pending list),
@@ -1889,9 +1947,10 @@ __global__ __launch_bounds__(BLOCK) void evict_kernel(EvictArgs a) {
   wl_prefix(a.ctl, pre);
   const uint64_t cnt = pre[NSHARD];
   if (cnt == 0) {  // same in every block
-    if constexpr (!DEFER) evict_finish(a.ctl, false);
+    if constexpr (!DEFER) evict_finish(a.ctl, false, a.inserts);
     return;
   }
+  a.spill = spill_placing(a.spill, a.ctl, a.inserts, S);
   const Geo geo = read_geo(a.ctl);
   // the same in every block: an unreserved launch leaves the count alone
   const bool unreserved = ld_ctl(&a.ctl->stash_count) + cnt <= a.stash_cap;
@@ -1908,7 +1967,7 @@ __global__ __launch_bounds__(BLOCK) void evict_kernel(EvictArgs a) {
                                 n_evict, n_full, n_side, n_fresh);
   }
   evict_counters(a, unreserved, (uint64_t)blockIdx.x * WAVES + wv, n_evict, n_full, n_side, n_fresh, sl);
-  if constexpr (!DEFER) evict_finish(a.ctl, true);
+  if constexpr (!DEFER) evict_finish(a.ctl, true, a.inserts);
 }
 
 // P3 for 16-slot buckets with two candidates, as a launch whose lanes are
@@ -1938,9 +1997,10 @@ __global__ __launch_bounds__(BLOCK) void evict_lanes_kernel(EvictArgs a) {
   wl_prefix(a.ctl, pre);
   const uint64_t cnt = pre[NSHARD];
   if (cnt == 0) {  // same in every block
-    evict_finish(a.ctl, false);
+    evict_finish(a.ctl, false, a.inserts);
     return;
   }
+  a.spill = spill_placing(a.spill, a.ctl, a.inserts, S);
   const Geo geo = read_geo(a.ctl);
   // the same in every block: an unreserved launch leaves the count alone
   const bool unreserved = ld_ctl(&a.ctl->stash_count) + cnt <= a.stash_cap;
@@ -2103,7 +2163,7 @@ __global__ __launch_bounds__(BLOCK) void evict_lanes_kernel(EvictArgs a) {
     }
   }
   evict_counters(a, unreserved, wid, n_evict, n_full, n_side, n_fresh, 0);
-  evict_finish(a.ctl, true);
+  evict_finish(a.ctl, true, a.inserts);
 }
 
 // Step 4 as its own launch (after evict_kernel<.., DEFER>): every worklist
@@ -2115,6 +2175,7 @@ __global__ __launch_bounds__(BLOCK) void stash_kernel(EvictArgs a) {
   wl_prefix(a.ctl, pre);
   const uint64_t cnt = pre[NSHARD];
   if (cnt == 0) return;
+  a.spill = spill_placing(a.spill, a.ctl, a.inserts, 16);
   const Geo geo = read_geo(a.ctl);
   const bool unreserved = ld_ctl(&a.ctl->stash_count) + cnt <= a.stash_cap;
   const int lane = threadIdx.x & 63;
@@ -2323,7 +2384,7 @@ __device__ __forceinline__ bool last_block(Ctl *c) {
   return last;
 }
 
-__device__ __forceinline__ void evict_finish(Ctl *c, bool items) {
+__device__ __forceinline__ void evict_finish(Ctl *c, bool items, uint64_t inserts) {
   if (items) {
     // this thread's counter updates are done before its block is counted
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -2331,7 +2392,7 @@ __device__ __forceinline__ void evict_finish(Ctl *c, bool items) {
   } else if (blockIdx.x != 0) {
     return;
   }
-  if (threadIdx.x < 64) (void)fold_shards_wave(c, true);
+  if (threadIdx.x < 64) (void)fold_shards_wave(c, true, inserts);
 }
 
 __device__ __forceinline__ uint32_t nth_set_bit(uint64_t m, uint32_t r) {
@@ -3018,7 +3079,7 @@ __device__ __forceinline__ ResizeArgs resize_args(const ReqDesc &d) {
 
 __device__ __forceinline__ EvictArgs evict_args(const ReqDesc &d) {
   return EvictArgs{d.t.buckets, d.t.spill,      d.t.hint,        d.t.stash,        d.t.pending, d.t.ctl,
-                   d.t.wl,      d.t.wl_seg_cap, d.t.stash_cap,   d.t.pending_cap,  d.t.max_evictions};
+                   d.t.wl,      d.t.wl_seg_cap, d.t.stash_cap,   d.t.pending_cap,  d.t.max_evictions, 0};
 }
 
 __device__ __forceinline__ bool has_inserts(const ReqDesc &d) { return d.mode == OP_INSERT || d.mode == OP_MIXED; }
@@ -3165,6 +3226,10 @@ __device__ uint64_t advance(DrainQueue *q, ReqState *rs, const ReqDesc &d, uint3
   }
   r->done = 0;
   if (ph == PH_DONE) {
+    if (has_inserts(d)) {
+      volatile Ctl *c = d.t.ctl;
+      c->inserted += d.n;
+    }
     const uint64_t ticket = d.ticket;
     __hip_atomic_store(&q->host_live[ticket % q->cap], ld_ctl(&d.t.ctl->live), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_SYSTEM);
@@ -3469,8 +3534,9 @@ __device__ __forceinline__ void run_chunk(ReqState *r, const ReqDesc &d, uint32_
     case PH_EVICT: {
       using E = EvictShape<S>;
       __shared__ uint64_t pre[NSHARD + 1];
-      const EvictArgs ea = evict_args(d);
+      EvictArgs ea = evict_args(d);
       wl_prefix(d.t.ctl, pre);
+      ea.spill = spill_placing(ea.spill, d.t.ctl, d.n, S);
       const Geo geo = read_geo(d.t.ctl);
       const uint64_t items = pre[NSHARD];
       const int eg = lane / E::L, esl = lane % E::L;
@@ -3504,7 +3570,7 @@ __device__ __forceinline__ void run_chunk(ReqState *r, const ReqDesc &d, uint32_
       a.n = d.n;
       a.stash_cap = d.t.stash_cap;
       a.pending_cap = d.t.pending_cap;
-      const OpsView view = read_view(d.t.ctl, d.t.stash_cap, d.t.pending_cap);
+      const OpsView view = read_view(d.t.ctl, d.t.stash_cap, d.t.pending_cap, d.t.spill, d.n);
       // one probe variant only (the second candidate after a miss): a
       // second inlined copy would cost the resident grid occupancy
       int64_t live_acc = 0;
@@ -3516,7 +3582,12 @@ __device__ __forceinline__ void run_chunk(ReqState *r, const ReqDesc &d, uint32_
         default: ops_tile<S, OP_MIXED, false, PAIR_BITHASH, Traits<S>::CH, FILTER_ASK>(a, view, c, sh.ops, live_acc, bad_acc); break;
       }
       ops_counts_add(d.t.ctl, c * WAVES + (threadIdx.x >> 6), live_acc, bad_acc);
-      if (c == 0 && threadIdx.x == 0 && (d.mode == OP_MIXED || d.mode == OP_DELETE)) set_removed(d.t.ctl);
+      if (c == 0 && threadIdx.x == 0) {
+        const bool filter = d.t.spill.bits != nullptr;
+        if (d.mode == OP_INSERT) ops_done<OP_INSERT>(d.t.ctl, view, filter);
+        else if (d.mode == OP_DELETE) ops_done<OP_DELETE>(d.t.ctl, view, filter);
+        else if (d.mode == OP_MIXED) ops_done<OP_MIXED>(d.t.ctl, view, filter);
+      }
       break;
     }
     default: break;  // PH_START: no data-parallel work
@@ -3751,7 +3822,11 @@ __global__ __launch_bounds__(BLOCK) void set_ops_kernel(SetArgs a) {
   const uint64_t n_stash = min(ld_ctl(&a.ctl->stash_count), a.stash_cap);
   const uint64_t n_pend = min(ld_ctl(&a.ctl->pending_count), a.pending_cap);
   const bool overflow_used = (n_stash | n_pend) != 0;
-  const bool removed = ld_ctl32(&a.ctl->removed) != 0;
+  OpsView view;
+  view.removed = ld_ctl32(&a.ctl->removed) != 0;
+  view.spill = spill_state(a.spill, a.ctl, a.n);
+  const bool removed = view.removed, filter = a.spill.bits != nullptr;
+  if (MODE == OP_LOOKUP || MODE == OP_DELETE ? view.spill.dropped : view.spill.plain) a.spill = spill_none(SET_S);
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int g = lane >> 5, sl = lane & 31;
   const uint64_t ntiles = (a.n + BLOCK - 1) / BLOCK;
@@ -3876,7 +3951,7 @@ __global__ __launch_bounds__(BLOCK) void set_ops_kernel(SetArgs a) {
     }
     if (active && MODE != OP_INSERT && a.flags_out) __builtin_nontemporal_store(out_f, &a.flags_out[i]);
   }
-  if ((MODE == OP_MIXED || MODE == OP_DELETE) && blockIdx.x == 0 && threadIdx.x == 0) set_removed(a.ctl);
+  if (MODE != OP_LOOKUP && blockIdx.x == 0 && threadIdx.x == 0) ops_done<MODE>(a.ctl, view, filter);
 }
 
 // A lane's fresh copy of a whole 32-slot bucket (128 bytes).
@@ -3942,9 +4017,10 @@ __global__ __launch_bounds__(BLOCK) void set_evict_kernel(SetArgs a) {
   wl_prefix(a.ctl, pre);
   const uint64_t cnt = pre[NSHARD];
   if (cnt == 0) {
-    evict_finish(a.ctl, false);
+    evict_finish(a.ctl, false, a.n);
     return;
   }
+  a.spill = spill_placing(a.spill, a.ctl, a.n, SET_S);
   const Geo geo = read_geo(a.ctl);
   const bool unreserved = ld_ctl(&a.ctl->stash_count) + cnt <= a.stash_cap;
   const int lane = threadIdx.x & 63;
@@ -4022,7 +4098,7 @@ __global__ __launch_bounds__(BLOCK) void set_evict_kernel(SetArgs a) {
     if (fr && unreserved) add64(&sh->stash_unreserved, fr);
     if (sd >> 32) add64(&sh->pending_inserts, sd >> 32);
   }
-  evict_finish(a.ctl, true);
+  evict_finish(a.ctl, true, a.n);
 }
 
 }  // namespace hive
@@ -4041,7 +4117,11 @@ struct hive_table {
   uint64_t stash_cap, pending_cap;
   uint64_t *d_buckets = nullptr;
   uint32_t *d_hint = nullptr;
-  Spill spill{nullptr, 0, 0};  // its bits follow the hint bits, in one allocation
+  Spill spill{nullptr, 0, 0, 0, 0};  // its bits follow the hint bits, in one allocation
+  // Ctl::inserted and Ctl::dropped as of the batches submitted (replays of a
+  // captured graph run on without the host: the device's own decide there)
+  uint64_t inserted = 0;
+  bool dropped = false;
   uint64_t *d_stash = nullptr;
   uint64_t *d_pending = nullptr;
   Ctl *d_ctl = nullptr;
@@ -4381,10 +4461,10 @@ static unsigned evict_lanes_grid(uint64_t max_items) {
 // two-hash tables run evict_lanes_kernel (lanes refilled from the wave's
 // range); the re-placement after a split, a few thousand items that each
 // start a chain at once, keeps one item per lane (evict_kernel).
-static void launch_evict(hive_table *h, uint64_t max_items, hipStream_t st, bool split_steps = false,
-                         bool refill = true) {
-  EvictArgs e{h->d_buckets, h->spill,        h->d_hint,    h->d_stash,   h->d_pending,   h->d_ctl,
-              h->d_wl,      h->wl_seg_cap,   h->stash_cap, h->pending_cap, h->cfg.max_evictions};
+static void launch_evict(hive_table *h, const Spill &spill, uint64_t max_items, uint64_t inserts, hipStream_t st,
+                         bool split_steps = false, bool refill = true) {
+  EvictArgs e{h->d_buckets, spill,         h->d_hint,    h->d_stash,     h->d_pending,         h->d_ctl,
+              h->d_wl,      h->wl_seg_cap, h->stash_cap, h->pending_cap, h->cfg.max_evictions, inserts};
   const dim3 grid(grid_for(max_items, (uint64_t)WAVES * evict_groups_per_wave(h->S), EVICT_GRID));
   if (split_steps && h->S == 16 && h->cfg.hash_pair == PAIR_BITHASH) {
     hipLaunchKernelGGL((evict_kernel<16, PAIR_BITHASH, true>), grid, dim3(BLOCK), 0, st, e);
@@ -4421,8 +4501,8 @@ static void launch_evict(hive_table *h, uint64_t max_items, hipStream_t st, bool
 
 // Fold the shards into the totals (batches without inserts; an eviction
 // launch folds by itself).
-static void launch_finish(hive_table *h, hipStream_t st) {
-  hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(64), 0, st, h->d_ctl);
+static void launch_finish(hive_table *h, uint64_t inserts, hipStream_t st) {
+  hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(64), 0, st, h->d_ctl, inserts);
 }
 
 // Phase timing: close the open span (if any) at an event recorded now on
@@ -4489,7 +4569,7 @@ static hive_status resize_sequence(hive_table *h, uint32_t mode, uint64_t amount
   launch_resize(h, mode, amount, d_ops, true, st);
   phase_mark(h, HIVE_PHASE_DRAIN, st);
   // live entries of a drain (and the batch's worklist)
-  launch_evict(h, batch_items + h->stash_cap + h->pending_cap, st, false, batch_items > 0);
+  launch_evict(h, h->spill, batch_items + h->stash_cap + h->pending_cap, 0, st, false, batch_items > 0);
   return launch_check();
 }
 
@@ -4671,6 +4751,16 @@ static hive_status noalloc_scratch(uint64_t **out) {
   return HIVE_OK;
 }
 
+// The filter a batch about to be enqueued is given: the table's, or none once
+// it places (or an earlier batch placed) without.
+static Spill batch_spill(hive_table *h, uint32_t mode, uint64_t n) {
+  if (mode == OP_INSERT || mode == OP_MIXED) {
+    h->dropped = h->dropped || h->inserted >= h->spill.start || h->inserted + n > h->spill.end;
+    h->inserted += n;
+  }
+  return h->dropped ? spill_none(h->S) : h->spill;
+}
+
 // no_alloc: take the dedupe set from `scratch` and refuse a batch that would
 // grow the table's worklist, so that the call allocates nothing; phase
 // timing (which creates events) is skipped for such a call.
@@ -4733,7 +4823,7 @@ static hive_status run_batch(hive_t h, uint32_t mode, const uint8_t *d_ops, cons
   if (no_alloc) h->timing = false;
   OpsArgs a{};
   a.buckets = h->d_buckets;
-  a.spill = h->spill;
+  a.spill = batch_spill(h, mode, n);
   a.hint = h->d_hint;
   a.stash = h->d_stash;
   a.pending = h->d_pending;
@@ -4758,7 +4848,7 @@ static hive_status run_batch(hive_t h, uint32_t mode, const uint8_t *d_ops, cons
     if ((s = launch_dedupe(dd, mode, d_ops, d_keys, n, st, &a.win)) != HIVE_OK) return s;
   }
   if (h->entry_bytes == 4) {
-    SetArgs sa{(uint32_t *)h->d_buckets, h->spill, h->d_hint, (uint32_t *)h->d_stash, (uint32_t *)h->d_pending, h->d_ctl,
+    SetArgs sa{(uint32_t *)h->d_buckets, a.spill, h->d_hint, (uint32_t *)h->d_stash, (uint32_t *)h->d_pending, h->d_ctl,
                h->d_wl, h->wl_seg_cap, a.dd, a.dd_mask, d_ops, d_keys, d_flags_out, n, h->stash_cap, h->pending_cap,
                h->cfg.max_evictions, a.win};
     phase_mark(h, HIVE_PHASE_PROBE, st);
@@ -4775,7 +4865,7 @@ static hive_status run_batch(hive_t h, uint32_t mode, const uint8_t *d_ops, cons
       hipLaunchKernelGGL(set_evict_kernel, dim3(grid_for(n, BLOCK, EVICT_GRID)), dim3(BLOCK), 0, st, sa);
     } else if (mode != OP_LOOKUP) {
       phase_mark(h, HIVE_PHASE_FINISH, st);
-      launch_finish(h, st);
+      launch_finish(h, 0, st);
     }
     phase_mark(h, -1, st);
     return launch_check();
@@ -4814,12 +4904,13 @@ static hive_status run_batch(hive_t h, uint32_t mode, const uint8_t *d_ops, cons
   }
   if (inserts) {
     phase_mark(h, HIVE_PHASE_EVICT, st);
-    launch_evict(h, n, st, h->timing);
+    launch_evict(h, a.spill, n, n, st, h->timing);
   }
   // the eviction launch folds, that of the post-batch rule too
   if (h->timing ? mode != OP_LOOKUP : (mode == OP_DELETE && !post)) {
     phase_mark(h, HIVE_PHASE_FINISH, st);
-    launch_finish(h, st);
+    // (its own inserts: an eviction launch that is not split in two counts them)
+    launch_finish(h, inserts && h->S == 16 && h->cfg.hash_pair == PAIR_BITHASH ? n : 0, st);
   }
   if ((s = launch_check()) != HIVE_OK) return s;
   if (post && (s = resize_sequence(h, PLAN_POST, 0, nullptr, st)) != HIVE_OK) return s;
@@ -4895,6 +4986,8 @@ hive_status hive_create(const hive_config *cfg_in, uint64_t initial_buckets, voi
   const bool filter = cfg.addressing == HIVE_FIXED && cfg.hash_pair != HIVE_PAIR_TRIPLE && !cfg.probe_both &&
                       cfg.max_evictions >= FIRST_MIN_CHAIN && h->stash_cap >= max_b * S / 100;
   h->spill.first_min = filter ? S * FIRST_MIN_16THS / 16 : S + 1;  // S + 1: by two-choice alone
+  h->spill.start = max_b * S * FILTER_START_PCT / 100;
+  h->spill.end = S == 16 ? max_b * S * FILTER_END_PCT / 100 : ~0ull;
   h->spill.shift = 3;
   while (h->spill.shift > 0 && (max_b << h->spill.shift) / 8 > FILTER_BYTES) --h->spill.shift;
   hive_status s = HIVE_OK;
@@ -5095,6 +5188,8 @@ hive_status hive_clear(hive_t h, void *stream) {
   if (!h) return HIVE_ERR_ARG;
   hipStream_t st = (hipStream_t)stream;
   h->last = st;
+  h->inserted = 0;
+  h->dropped = false;
   return reset_table(h, st);
 }
 
@@ -5247,7 +5342,7 @@ hive_status hive_drain_submit(hive_drain_t d, hive_t h, const hive_batch_desc *b
   if (wl_need > h->wl_cap || dd_size > h->dd_cap) return HIVE_ERR_OOM;  // cannot happen after a good grow
   ReqDesc r;
   memset(&r, 0, sizeof(r));
-  r.t = TableDesc{h->d_buckets,    h->spill, h->d_hint,  h->d_stash,   h->d_pending, h->d_ctl, h->d_wl, h->d_dd,
+  r.t = TableDesc{h->d_buckets,    batch_spill(h, b->op_mode, b->n), h->d_hint,  h->d_stash,   h->d_pending, h->d_ctl, h->d_wl, h->d_dd,
                   h->wl_seg_cap,  h->stash_cap,
                   h->pending_cap, hint_words(h->max_buckets), h->S, h->cfg.max_evictions, h->cfg.resize_k,
                   h->cfg.lf_expand_pct, h->cfg.lf_contract_pct, h->cfg.pre_expand, h->cfg.post_policy,

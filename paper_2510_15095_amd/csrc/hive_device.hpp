@@ -51,7 +51,10 @@ struct alignas(128) Ctl {
   uint32_t removed;        // a batch that may delete ran since the table was empty
   uint64_t stash_count;    // stash slots used (including TOMB)
   uint64_t pending_count;  // pending slots used (including TOMB; may pass capacity on loss)
-  uint64_t pad0_[9];
+  uint64_t inserted;       // operations of the insert and mixed batches since the table was empty
+  uint32_t dropped;        // the spill filter's bits are not kept up any more
+  uint32_t pad_drop_;
+  uint64_t pad0_[7];
   // line 1: totals, folded from the shards after each batch, and error bits
   uint64_t live;
   uint64_t evictions;
