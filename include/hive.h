@@ -127,12 +127,13 @@ typedef struct {
                                  4-7 delete, 8-11 lookup, 12-15 mixed.  A
                                  variant sets the occupancy target (waves
                                  per SIMD) and the bucket loads in flight
-                                 per wave and probe chunk: 0 (default) 4 and
-                                 16, or 8 and 4 where the table's spill
-                                 filter makes that faster; 1: 6 and 16;
-                                 2: 8 and 8; 3: 6 and 8; 4: 8 and 4.
-                                 Inserts take 0, 3 or 4 (their fused round
-                                 holds twice the loads).
+                                 per wave and probe chunk: 1: 6 and 16;
+                                 2: 8 and 8; 3: 6 and 8; 4: 8 and 4; 15: 4
+                                 and 16; 0 (default): the library's choice,
+                                 4 and 16, or 8 and 4 where the table's spill
+                                 filter makes that faster.  Inserts take 0,
+                                 3, 4 or 15 (their fused round holds twice
+                                 the loads).
                                  Non-zero needs S = 16, HIVE_PAIR_BITHASH,
                                  probe_both 0 and 64-bit entries; results
                                  are the same for every variant.  Picked by

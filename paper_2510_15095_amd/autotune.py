@@ -9,8 +9,9 @@
   batches, scored by operations per second;
 * the probe kernel (16-slot BitHash tables): per operation kind (insert,
   delete, lookup, mixed) the variant -- occupancy target in waves per SIMD
-  and bucket loads in flight per wave -- on the bulk workload at 95% load,
-  then the cap on blocks per probe launch (how many 256-operation tiles each
+  and bucket loads in flight per wave -- on the bulk workload at 95% load
+  (lookups of all of its keys and of 2^22), against the library's own choice
+  by table and batch; then the cap on blocks per probe launch (how many 256-operation tiles each
   block strides over).
 
 Each candidate runs once to warm up and is then timed `reps` times with HIP
@@ -131,12 +132,19 @@ def tune_probe_both(n_keys: int = 1 << 24, reps: int = 3) -> dict:
     return {"probe_both": int(best), "scores_mops": {str(k): round(x, 1) for k, x in scores.items()}}
 
 
+def probe_candidates() -> list[int]:
+    """The library's choice (0) and every variant by its name."""
+    return [*range(len(H.PROBE_VARIANTS)), H.PROBE_4X16]
+
+
 def tune_probe_kernel(n_keys: int = 1 << 26, reps: int = 5, mixed_ops: int = 1 << 22,
                       grids=(0, 4096, 8192, 131072, 1 << 20)) -> dict:
     """Probe-kernel variant per operation kind, then the probe grid cap, on
     the bulk workload: 2^26 unique keys built to 95% load in 16-slot buckets
-    (inserts), lookups with 50% hits, deletes of half the keys, and Zipf(0.99)
-    mixed batches (40/40/20) of 2^22 operations on the built table."""
+    (inserts), lookups with 50% hits (of as many keys, and of 2^22: the mean of
+    the two rates), deletes of half the keys, and Zipf(0.99) mixed batches
+    (40/40/20) of 2^22 operations on the built table.  Variant 0, the library's
+    own choice, is the default that a variant has to beat."""
     import torch
     w = wl.bulk_workload(2, n_keys)
     k = torch.from_numpy(w["ins_keys"]).cuda()
@@ -150,7 +158,9 @@ def tune_probe_kernel(n_keys: int = 1 << 26, reps: int = 5, mixed_ops: int = 1 <
     fo = torch.empty(q.numel(), dtype=torch.uint8, device="cuda")
     nb = int(np.ceil(n_keys / (0.95 * 16)))
     kinds = H.PROBE_KINDS
-    ms = {kind: {} for kind in kinds}
+    small = min(q.numel(), 1 << 22)
+    n_ops = {"insert": n_keys, "lookup": n_keys, "delete": dk.numel(), "mixed": mixed_ops}
+    scores = {kind: {} for kind in kinds}
 
     def measure(tuning: int, grid: int) -> dict:
         t = H.Table(nb, max_batch=max(n_keys, mixed_ops), probe_tuning=tuning, probe_grid=grid)
@@ -161,21 +171,20 @@ def tune_probe_kernel(n_keys: int = 1 << 26, reps: int = 5, mixed_ops: int = 1 <
         out = {"insert": _timed(lambda: t.insert(k, v, flags=H.HIVE_UNIQUE), reps, prep=t.clear)}
         build()
         out["lookup"] = _timed(lambda: H.hive_lookup_batch(t.h, q, vo, fo), reps)
+        out["lookup_small"] = _timed(lambda: H.hive_lookup_batch(t.h, q[:small], vo, fo), reps)
         out["delete"] = _timed(lambda: H.hive_delete_batch(t.h, dk, None, H.HIVE_UNIQUE), reps, prep=build)
         out["mixed"] = _timed(lambda: H.hive_mixed_batch(t.h, mo, mk, mv, vo, fo), reps, prep=build)
         t.close()
         return out
 
-    for var in range(len(H.PROBE_VARIANTS)):
-        ins = var if var in H.PROBE_INSERT_VARIANTS else 0
+    for var in probe_candidates():
+        ins = var if var == H.PROBE_4X16 or var in H.PROBE_INSERT_VARIANTS else 0
         got = measure(H.probe_tuning(ins, var, var, var), 0)
-        _progress(f"probe variant {var} {H.PROBE_VARIANTS[var]}: " +
-                  ", ".join(f"{kk} {x:.3f} ms" for kk, x in got.items()))
+        _progress(f"probe variant {var}: " + ", ".join(f"{kk} {x:.3f} ms" for kk, x in got.items()))
         for kind in kinds:
             if kind != "insert" or var == ins:
-                ms[kind][var] = got[kind]
-    n_ops = {"insert": n_keys, "lookup": n_keys, "delete": dk.numel(), "mixed": mixed_ops}
-    scores = {kind: {var: n_ops[kind] / (m * 1e-3) / 1e6 for var, m in ms[kind].items()} for kind in kinds}
+                scores[kind][var] = n_ops[kind] / (got[kind] * 1e-3) / 1e6
+        scores["lookup"][var] = (scores["lookup"][var] + small / (got["lookup_small"] * 1e-3) / 1e6) / 2
     pick = {kind: int(_pick(scores[kind], 0)) for kind in kinds}
     tuning = H.probe_tuning(*(pick[kind] for kind in kinds))
     # the grid cap, scored on the whole bulk step with the chosen variants
@@ -187,7 +196,8 @@ def tune_probe_kernel(n_keys: int = 1 << 26, reps: int = 5, mixed_ops: int = 1 <
         gscores[grid] = step_ops / ((got["insert"] + got["lookup"] + got["delete"]) * 1e-3) / 1e6
     grid = int(_pick(gscores, 0))
     return {"probe_tuning": int(tuning), "probe_grid": grid,
-            "variants": {kind: H.PROBE_VARIANTS[pick[kind]] for kind in kinds},
+            "variants": {kind: (4, 16) if pick[kind] == H.PROBE_4X16 else H.PROBE_VARIANTS[pick[kind]]
+                         for kind in kinds},
             "scores_mops": {kind: {str(var): round(x, 1) for var, x in scores[kind].items()} for kind in kinds},
             "grid_scores_mops": {str(g): round(x, 1) for g, x in gscores.items()}}
 

@@ -4355,18 +4355,19 @@ static hive_status ensure_scratch(hive_table *h, uint64_t n, uint64_t n_dd, hipS
 
 // Probe-kernel variants a table may select per operation kind
 // (hive_config.probe_tuning): occupancy target in waves per SIMD and loads
-// in flight per probe chunk.  Variant 0 is the default, which
-// launch_ops_mode may replace by variant 4; the others exist for
-// 16-slot BitHash tables probing the second candidate after a miss
-// (probe_both = 0).  The insert kernel's fused round holds twice the loads,
-// so variants 1 and 2 would spill registers there and are refused for
-// inserts (kInsertTunings).
+// in flight per probe chunk.  A kind's 0 leaves the choice to launch_ops_mode
+// (variant 0, or 4 where it is faster), TUNING_ZERO asks for variant 0 itself.
+// Variants other than 0 exist for 16-slot BitHash tables probing the second
+// candidate after a miss (probe_both = 0).  The insert kernel's fused round
+// holds twice the loads, so variants 1 and 2 would spill registers there and
+// are refused for inserts (kInsertTunings).
 struct ProbeTuning {
   int waves_per_simd, loads_in_flight;
 };
 static constexpr ProbeTuning kProbeTunings[] = {{OPS_WAVES_PER_EU, 16}, {6, 16}, {8, 8}, {6, 8}, {8, 4}};
 static constexpr int kNumProbeTunings = sizeof(kProbeTunings) / sizeof(kProbeTunings[0]);
-static constexpr uint32_t kInsertTunings = (1u << 0) | (1u << 3) | (1u << 4);
+static constexpr uint32_t TUNING_ZERO = 15;
+static constexpr uint32_t kInsertTunings = (1u << 0) | (1u << 3) | (1u << 4) | (1u << TUNING_ZERO);
 
 // By default, a 16-slot BitHash table with a spill filter takes variant 4
 // (8 waves per SIMD, 4 loads in flight).  The filter ends nearly every miss
@@ -4388,10 +4389,8 @@ static constexpr uint64_t WIDE_LOOKUP_MAX = 1ull << 24;
 template <int S, uint32_t MODE, bool BOTH, int PAIR = PAIR_BITHASH, int V = 0>
 static void launch_ops(const OpsArgs &a, uint32_t grid_cap, hipStream_t st) {
   constexpr ProbeTuning t = kProbeTunings[V];
-  // where launch_ops_mode leaves variant 0 to lookups
-  constexpr bool kReplaced = S == 16 && PAIR == PAIR_BITHASH && V == 0 && MODE != OP_LOOKUP;
   const uint64_t blocks = std::min<uint64_t>((a.n + BLOCK - 1) / BLOCK, grid_cap ? grid_cap : OPS_GRID);
-  if constexpr (!BOTH && PairArity<PAIR>::D == 2 && !kReplaced) {
+  if constexpr (!BOTH && PairArity<PAIR>::D == 2) {
     if (a.spill.bits) {
       hipLaunchKernelGGL((ops_kernel<S, MODE, BOTH, PAIR, t.waves_per_simd, t.loads_in_flight, FILTER_USE>),
                          dim3((unsigned)blocks), dim3(BLOCK), 0, st, a);
@@ -4953,8 +4952,10 @@ hive_status hive_create(const hive_config *cfg_in, uint64_t initial_buckets, voi
   if ((cfg.probe_tuning >> 16) != 0 || !((kInsertTunings >> (cfg.probe_tuning & 15u)) & 1u) ||
       (cfg.probe_tuning && (S != 16 || cfg.hash_pair != HIVE_PAIR_BITHASH || cfg.probe_both || set32)))
     return HIVE_ERR_ARG;
-  for (int kind = 0; kind < 4; ++kind)
-    if (((cfg.probe_tuning >> (4 * kind)) & 15u) >= (uint32_t)kNumProbeTunings) return HIVE_ERR_ARG;
+  for (int kind = 0; kind < 4; ++kind) {
+    const uint32_t v = (cfg.probe_tuning >> (4 * kind)) & 15u;
+    if (v >= (uint32_t)kNumProbeTunings && v != TUNING_ZERO) return HIVE_ERR_ARG;
+  }
   if (cfg.probe_grid > (1u << 20)) return HIVE_ERR_ARG;
   if (initial_buckets < 1) return HIVE_ERR_ARG;
   if (cfg.max_evictions > 1024) return HIVE_ERR_ARG;

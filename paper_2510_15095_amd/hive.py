@@ -183,9 +183,12 @@ def _check(status: int, where: str, warn_ok: bool = False) -> int:
 
 
 # probe-kernel variants (hive_config.probe_tuning): (waves per SIMD, loads in
-# flight) per variant index; inserts take the ones in PROBE_INSERT_VARIANTS
-PROBE_VARIANTS = ((4, 16), (6, 16), (8, 8), (6, 8), (8, 4))
+# flight) per variant index, the first the library's choice; inserts take the
+# ones in PROBE_INSERT_VARIANTS.  PROBE_4X16 asks for 4 waves and 16 loads
+# whatever the library would choose
+PROBE_VARIANTS = (("library",), (6, 16), (8, 8), (6, 8), (8, 4))
 PROBE_INSERT_VARIANTS = (0, 3, 4)
+PROBE_4X16 = 15
 PROBE_KINDS = ("insert", "delete", "lookup", "mixed")
 
 

@@ -244,3 +244,11 @@ def test_replays_and_eager_calls_agree_on_the_filter(H):
         run(look)
         expect(np.concatenate([left, b]), f"eager lookup {r}")
     t.close()
+
+
+@pytest.mark.parametrize("kinds", [(15, 15, 15, 15), (15, 0, 4, 0), (0, 15, 0, 15)])
+def test_4x16_asked_for_by_name(H, kinds):
+    """4 waves and 16 loads by name (15), beside the library's choice (0)."""
+    from test_gpu_probe_variants import run_all_kinds
+    case(f"probe variants by name {kinds}")
+    run_all_kinds(H, H.probe_tuning(*kinds), 0)

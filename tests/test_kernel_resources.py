@@ -50,3 +50,21 @@ def test_launched_kernels_use_no_scratch(scratch, kernel):
     mine = {k: v for k, v in scratch.items() if kernel in k}
     assert mine, f"no kernel named {kernel} among {len(scratch)}"
     assert not any(mine.values()), {k: v for k, v in mine.items() if v}
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2, 3])  # insert, delete, lookup, mixed
+@pytest.mark.parametrize("waves,loads", [(4, 16), (8, 4)])
+def test_probe_variants_of_filter_tables_are_built(scratch, mode, waves, loads):
+    """Variant 0 (4 waves per SIMD, 16 loads) can be asked for on tables with a
+    spill filter, for every kind of batch, beside the library's own choice."""
+    assert any(f"10ops_kernelILi16ELj{mode}ELb0ELi0ELi{waves}ELi{loads}ELi1EE" in k for k in scratch)
+
+
+def test_tuner_measures_every_variant_by_name():
+    """The tuner's candidates are the library's choice and each variant by its
+    own number, 4 waves and 16 loads among them."""
+    from paper_2510_15095_amd import autotune
+    from paper_2510_15095_amd import hive as H
+    got = autotune.probe_candidates()
+    assert got == [0, 1, 2, 3, 4, H.PROBE_4X16] and H.PROBE_VARIANTS[0] == ("library",)
+    assert len(H.PROBE_VARIANTS) == 5
