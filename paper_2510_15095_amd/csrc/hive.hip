@@ -224,9 +224,8 @@ __global__ __launch_bounds__(64) void finish_kernel(Ctl *c, uint64_t inserts) {
 // table is cleared.  (One batch of 2^21 keys to 97 / 99% load: two-choice 200 /
 // 240 us and 94 / 3,858 stash entries, packed 217 / 267 us and 624 / 7,301.
 // Wider buckets gain at any load: 2^25 keys in 32 slots to 99%, 3,237 us, packed
-// 2,638.)  The host counts
-// along (hive_table::inserted) and launches the kernels built without a filter
-// then; the device's own count and flag decide what the bits are worth, for
+// 2,638.)  The host counts along (hive_table::inserted) and launches what
+// suits; the device's own count and flag decide what the bits are worth, for
 // replays of captured launches and for the executor.
 // Slices of new keys into a 2^26-key table, 0-55-65-75-85-90-95-97%, without a
 // filter: 2,083, 428, 426, 440, 251, 320, 261 us, so: 1,609, 423, 427, 436, 244,
@@ -4379,7 +4378,10 @@ static constexpr uint32_t kInsertTunings = (1u << 0) | (1u << 3) | (1u << 4) | (
 // The exception is a lookup of more than WIDE_LOOKUP_MAX keys in buckets
 // larger than the last-level cache: there memory is the bound and the 16
 // loads a wave keeps in flight use it better (2^26 keys in 2^26: 2.05 ms,
-// against 2.08 with 8 and 4; equal at 2^24 keys, 533 and 530 us).  Tables
+// against 2.08 with 8 and 4; equal at 2^24 keys, 533 and 530 us), and the
+// inserts of a plain batch, whose new keys take two dependent rounds: slices of
+// 420,000 of them into 2^22 keys at 65-75 and 75-85% load 64 and 72 us with 8
+// and 4, 48 and 59 with 4 and 16 (both candidates in one round 49 and 63).  Tables
 // without a filter stay at variant 0: 2^22 lookups at load 0.6 127 us
 // against 131, deletes within 4 % of each other, first inserts into 2^18
 // buckets' worth of keys 112 against 97 but later ones 48 against 55.
@@ -4414,10 +4416,10 @@ static void launch_ops_mode_v(uint32_t mode, const OpsArgs &a, uint32_t grid_cap
 }
 
 template <int S, bool BOTH, int PAIR = PAIR_BITHASH>
-static void launch_ops_mode(uint32_t mode, const OpsArgs &a, const hive_config &cfg, hipStream_t st) {
+static void launch_ops_mode(uint32_t mode, const OpsArgs &a, const hive_config &cfg, bool plain, hipStream_t st) {
   if constexpr (S == 16 && !BOTH && PAIR == PAIR_BITHASH) {
     uint32_t v = (cfg.probe_tuning >> (4 * std::min<uint32_t>(mode, OP_MIXED))) & 15u;
-    if (v == 0 && a.spill.bits &&
+    if (v == 0 && a.spill.bits && !(mode == OP_INSERT && plain) &&
         !(mode == OP_LOOKUP && a.n > WIDE_LOOKUP_MAX && cfg.max_buckets * (S * 8) > LAST_LEVEL_CACHE))
       v = 4;
     switch (v) {
@@ -4751,13 +4753,16 @@ static hive_status noalloc_scratch(uint64_t **out) {
 }
 
 // The filter a batch about to be enqueued is given: the table's, or none once
-// it places (or an earlier batch placed) without.
+// it places (or an earlier batch placed) without.  Inserts take the kernel with
+// the filter all the same, which leaves it alone then and probes the second
+// candidate after a miss only: of 2^22 keys that are present already 199 us,
+// 252 with both candidates in one round; of 2^22 new ones 288 and 292.
 static Spill batch_spill(hive_table *h, uint32_t mode, uint64_t n) {
   if (mode == OP_INSERT || mode == OP_MIXED) {
     h->dropped = h->dropped || h->inserted >= h->spill.start || h->inserted + n > h->spill.end;
     h->inserted += n;
   }
-  return h->dropped ? spill_none(h->S) : h->spill;
+  return h->dropped && mode != OP_INSERT ? spill_none(h->S) : h->spill;
 }
 
 // no_alloc: take the dedupe set from `scratch` and refuse a batch that would
@@ -4881,18 +4886,18 @@ static hive_status run_batch(hive_t h, uint32_t mode, const uint8_t *d_ops, cons
       if (small)
         launch_small(mode, a, (uint8_t *)dd, st);
       else if (h->cfg.hash_pair == PAIR_CRC)
-        launch_ops_mode<16, false, PAIR_CRC>(mode, a, h->cfg, st);
+        launch_ops_mode<16, false, PAIR_CRC>(mode, a, h->cfg, h->dropped, st);
       else if (h->cfg.hash_pair == PAIR_MURMUR)
-        launch_ops_mode<16, false, PAIR_MURMUR>(mode, a, h->cfg, st);
+        launch_ops_mode<16, false, PAIR_MURMUR>(mode, a, h->cfg, h->dropped, st);
       else if (h->cfg.hash_pair == PAIR_TRIPLE)
-        launch_ops_mode<16, false, PAIR_TRIPLE>(mode, a, h->cfg, st);
+        launch_ops_mode<16, false, PAIR_TRIPLE>(mode, a, h->cfg, h->dropped, st);
       else if (h->cfg.probe_both)
-        launch_ops_mode<16, true>(mode, a, h->cfg, st);
+        launch_ops_mode<16, true>(mode, a, h->cfg, h->dropped, st);
       else
-        launch_ops_mode<16, false>(mode, a, h->cfg, st);
+        launch_ops_mode<16, false>(mode, a, h->cfg, h->dropped, st);
       break;
-    case 32: launch_ops_mode<32, false>(mode, a, h->cfg, st); break;
-    default: launch_ops_mode<64, false>(mode, a, h->cfg, st); break;
+    case 32: launch_ops_mode<32, false>(mode, a, h->cfg, h->dropped, st); break;
+    default: launch_ops_mode<64, false>(mode, a, h->cfg, h->dropped, st); break;
   }
   if ((s = launch_check()) != HIVE_OK) return s;
   const bool post = linear && h->cfg.post_policy && mode != OP_LOOKUP;
