@@ -434,8 +434,11 @@ struct DdsArgs {
   uint32_t n, mode, bits;  // 2^bits ranges
 };
 
-// Range hash (a bijection: odd factor) of a key.
-__device__ __forceinline__ uint32_t dds_hash(uint32_t k) { return k * 0x9E3779B1u; }
+// Range hash of a key: a bijection, whose top bits pick the range; its low bits
+// pick the slot in a range's table.  (The key times an odd constant put some
+// arithmetic progressions of keys into one range: 12,000 such keys took 460 us
+// in the one-launch form, 64 spread out.)
+__device__ __forceinline__ uint32_t dds_hash(uint32_t k) { return mix32(k); }
 
 __device__ __forceinline__ uint32_t dds_range(uint32_t k, uint32_t bits) {
   return bits ? dds_hash(k) >> (32 - bits) : 0u;
@@ -606,19 +609,19 @@ __global__ __launch_bounds__(DDS_BLOCK) void dds_kernel(DdsArgs d) {
 // over chunks in two launches and a scatter to whole partitions before a
 // resolve of two passes took five launches, and partitions of more distinct
 // keys than their tables a set in HBM.)  Time at 2^16, 2^18 and 2^20 inserts
-// of 2^20 keys: 18, 21 and 35 us (five launches: 46, 51 and 65 us); at 2^22,
-// 2^24 and 2^26 distinct keys: 110, 445 and 2,470 us (483, 1,738 and 7,865);
-// a 2^22 Zipf(0.99) mixed batch 62 us (84).  Slower than before is only a
-// batch of 2^24 operations and more in which every key repeats 16 times and
-// more (2^24 of 2^20 keys: 517 us against 477).  Bound by LDS atomics
+// of 2^20 keys: 18, 21 and 36 us (five launches: 49, 51 and 62 us); at 2^24, 2^26
+// and 2^28 distinct keys: 0.46, 2.87 and 28.1 ms (1.81, 7.95 and 34.0); a 2^22
+// Zipf(0.99) mixed batch 62 us (84).  Slower is only a batch of 2^25 operations
+// and more whose keys repeat dozens of times: 2^26 and 2^28 on 2^20 keys 2.95 and
+// 10.3 ms (2.53 and 8.9); whole inserts of them are not (3.76 and 13.2 ms for 4.04
+// and 14.4), deletes are (3.68 and 12.9 for 3.29 and 11.7).  Bound by LDS atomics
 // and the latency between the phases of a block.
 //
 // Inserts and deletes of a mixed batch share the ranges; bit 31 of a record
 // is the type, so a mixed batch of 2^31 operations and more runs once per
 // type (`only`).  A range with more distinct keys than the table takes is
 // worked through in sub-ranges, as in dds_kernel; beyond 2^25 operations that
-// is the ordinary course, and the first width is picked from the range's
-// record count.  Runs get short with many ranges (two records at 2^25), but
+// is the ordinary course.  Runs get short with many ranges (two records at 2^25), but
 // the runs of neighbouring ranges share cache lines, and the neighbours run
 // on one XCD at about the same time.
 // ---------------------------------------------------------------------------
@@ -633,6 +636,7 @@ struct DdrArgs {
   uint8_t *win;
   uint64_t *rec;     // chunk c's records from c * chunk on, sorted by range
   uint32_t *bounds;  // [chunk][range]: first record of the range's run | its end << 16
+  uint64_t *set, *used;         // ddr_set's words (2 n), and how many of them are taken
   uint32_t n, mode, bits, nch;  // 2^bits ranges, nch chunks
   uint32_t only;                // OP_NONE, or the one type of a mixed batch to record
 };
@@ -658,6 +662,7 @@ __global__ __launch_bounds__(DDR_BLOCK) void ddr_chunk_kernel(DdrArgs d) {
   const uint64_t base = (uint64_t)blockIdx.x * CH;
   const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
   const uint32_t nb = 1u << d.bits;
+  if (blockIdx.x == 0 && tid == 0) *d.used = 0;
   uint32_t kk[PER];
   int ty[PER];  // 0, or 1 for a mixed batch's deletes; -1: not recorded
 #pragma unroll
@@ -759,12 +764,93 @@ __global__ __launch_bounds__(DDR_BLOCK) void ddr_chunk_kernel(DdrArgs d) {
   for (uint32_t t = tid; t < total; t += DDR_BLOCK) d.rec[base + t] = tab[t];
 }
 
+// The records of chunk c in the block's range: c's run, read by the LANES lanes
+// of one group, `body` on each (false: stop).
+template <int LANES, uint32_t CH, typename F>
+__device__ __forceinline__ void ddr_run(const DdrArgs &d, uint32_t c, uint32_t b, F body) {
+  constexpr int LOADS = LANES <= 2 ? 4 : 2;  // reads in flight
+  const uint32_t be = d.bounds[((uint64_t)c << d.bits) + b], end = be >> 16;
+  const uint64_t *run = d.rec + (uint64_t)c * CH;
+  for (uint32_t t0 = (be & 0xFFFFu) + threadIdx.x % LANES; t0 < end; t0 += LANES * LOADS) {
+    uint64_t es[LOADS];
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) es[u] = t0 + u * LANES < end ? run[t0 + u * LANES] : EMPTY;
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u)
+      if (es[u] != EMPTY && !body(es[u])) return;
+  }
+}
+
+// Whether record e is in [lo, lo + width) of its range's hash values.
+__device__ __forceinline__ bool ddr_in(uint64_t e, uint64_t lo, uint64_t width) {
+  return (uint64_t)(dds_hash((uint32_t)(e >> 32)) - (uint32_t)lo) < width;
+}
+
+// Of two records of one key, whether e beats cur.
+__device__ __forceinline__ bool ddr_beats(const DdrArgs &d, uint64_t e, uint64_t cur) {
+  return ddr_keep_last(d, e) ? cur < e : cur > e;
+}
+
+// The records from lo on of range b settled in an open-addressed set in HBM, of
+// twice as many words as records (all ranges together: at most 2 n).
+template <int LANES, uint32_t CH>
+__device__ __forceinline__ void ddr_set(const DdrArgs &d, uint32_t b, uint64_t lo, uint64_t last) {
+  __shared__ unsigned long long s_n, s_at;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  uint64_t mine = 0;
+  for (uint32_t c = threadIdx.x / LANES; c < d.nch; c += DDR_BLOCK / LANES)
+    ddr_run<LANES, CH>(d, c, b, [&](uint64_t e) {
+      mine += ddr_in(e, lo, last - lo) ? 1 : 0;
+      return true;
+    });
+  if (mine) atomicAdd(&s_n, (unsigned long long)mine);
+  __syncthreads();
+  const uint64_t m = 2 * s_n;
+  if (threadIdx.x == 0) s_at = add64(d.used, m);
+  __syncthreads();
+  uint64_t *set = d.set + s_at;
+  for (uint64_t t = threadIdx.x; t < m; t += DDR_BLOCK)
+    __hip_atomic_store(&set[t], EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  for (uint32_t c = threadIdx.x / LANES; c < d.nch; c += DDR_BLOCK / LANES)
+    ddr_run<LANES, CH>(d, c, b, [&](uint64_t e) {
+      if (!ddr_in(e, lo, last - lo)) return true;
+      const uint32_t k = (uint32_t)(e >> 32);
+      // (not by the range hash: a range's keys share its top bits)
+      for (uint64_t s = __umul64hi((uint64_t)(k * 0x9E3779B1u) << 32, m);; s = s + 1 == m ? 0 : s + 1) {
+        uint64_t cur = load_fresh(&set[s]);
+        if (cur == EMPTY) {
+          cur = cas64(&set[s], EMPTY, e);
+          if (cur == EMPTY) return true;
+        }
+        if ((uint32_t)(cur >> 32) != k) continue;
+        if (ddr_beats(d, e, cur))
+          cur = ddr_keep_last(d, e)
+                    ? __hip_atomic_fetch_max(&set[s], e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                    : __hip_atomic_fetch_min(&set[s], e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        d.win[ddr_index(d, ddr_beats(d, e, cur) ? cur : e)] = 0;
+        return true;
+      }
+    });
+}
+
 // The table is sized for the records of a range: up to about 2,048 of the
 // smaller batches, 8,192 at 2^22 operations.  LANES lanes read one chunk's run
 // together: eight where runs are eight records or more; beyond 2^23
 // operations runs are short and there are thousands of chunks, and the
-// dependent reads of bounds and records take the time (2^26 operations: eight
-// lanes 4.1 ms, one 3.5).
+// dependent reads of bounds and records take the time; lanes that read
+// neighbouring chunks clear flags that share cache lines (eight, four, two and
+// one lanes: 2^26 distinct keys 4.31, 3.11, 2.87 and 2.80 ms, 2^26 operations on
+// 2^20 keys 3.19, 3.02, 2.95 and 3.08, of which the cleared flags are 1.4).
+//
+// A pass reads the whole range, so a range of many sub-ranges would take time
+// quadratic in its records (2^20 operations on 2^16 keys of one range: 34 ms).
+// Once more than DDR_PASSES passes are ahead, the rest of the range goes to
+// ddr_set, whose atomics take about the time of that many passes (the same
+// batch 4.1 ms, in one block; beyond 2^29 distinct keys every range).
+constexpr uint64_t DDR_PASSES = 24;
 template <int PER, int BINS, int LANES>
 __global__ __launch_bounds__(DDR_BLOCK) void ddr_resolve_kernel(DdrArgs d) {
   constexpr uint32_t CH = (uint32_t)DDR_BLOCK * PER;
@@ -778,63 +864,73 @@ __global__ __launch_bounds__(DDR_BLOCK) void ddr_resolve_kernel(DdrArgs d) {
   // bounds share cache lines
   const uint32_t b = nb >= 8 ? (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3) : blockIdx.x;
   const uint64_t whole = 1ull << (32 - d.bits), first = (uint64_t)b * whole, last = first + whole;
-  constexpr int LOADS = LANES == 1 ? 4 : 2;  // reads in flight
-  const int sub = threadIdx.x % LANES;
   uint64_t lo = first, width = whole;
   if constexpr (BINS == DDR_BINS_BIG) {
-    // the first width by the range's records
-    if (threadIdx.x == 0) s_claims = 0;
-    __syncthreads();
-    uint32_t mine = 0;
-    for (uint32_t c = threadIdx.x; c < d.nch; c += DDR_BLOCK) {
-      const uint32_t be = d.bounds[(uint64_t)c * nb + b];
-      mine += (be >> 16) - (be & 0xFFFFu);
+    // The first width: the whole range where keys repeat, by a sample of up to
+    // 1,024 records of as many chunks (of 4,096 keys, 88% of the sample are
+    // distinct, of 12,288 96%); else so that the records it may hold fit.
+    const uint64_t per = (uint64_t)d.n >> d.bits;  // records, at most about that many
+    if (per > CAP) {
+      __shared__ uint32_t s_sample, s_distinct;
+      for (int j = threadIdx.x; j < TAB; j += DDR_BLOCK) tab[j] = EMPTY;
+      if (threadIdx.x == 0) s_sample = s_distinct = 0;
+      __syncthreads();
+      bool have = false, fresh = false;
+      if (threadIdx.x < d.nch)
+        ddr_run<1, CH>(d, (uint32_t)((uint64_t)threadIdx.x * d.nch / min(d.nch, (uint32_t)DDR_BLOCK)), b, [&](uint64_t e) {
+          have = true;
+          for (uint32_t s = mix32((uint32_t)(e >> 32)) & (TAB - 1);; s = (s + 1) & (TAB - 1)) {
+            const uint64_t cur =
+                atomicCAS((unsigned long long *)&tab[s], (unsigned long long)EMPTY, (unsigned long long)(e | 0xFFFFFFFFu));
+            if (cur == EMPTY) fresh = true;
+            if (cur == EMPTY || (uint32_t)(cur >> 32) == (uint32_t)(e >> 32)) return false;
+          }
+        });
+      const uint64_t hm = ballot(have), fm = ballot(fresh);
+      if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&s_sample, (uint32_t)__popcll(hm));
+        atomicAdd(&s_distinct, (uint32_t)__popcll(fm));
+      }
+      __syncthreads();
+      if ((uint64_t)s_distinct * 8 > (uint64_t)s_sample * 7)
+        for (uint64_t r = per; r > CAP; r /= 2) width = (width + 1) / 2;
     }
-    if (mine) atomicAdd(&s_claims, mine);
-    __syncthreads();
-    for (uint32_t r = s_claims; r > CAP; r /= 2) width = (width + 1) / 2;
-    __syncthreads();
   }
+  // chunks from the end that holds the winners: most later records of a key
+  // lose to what the table holds, by a load instead of an atomic
+  const bool backwards = ddr_typed(d) || (d.only == OP_NONE ? d.mode : d.only) == OP_INSERT;
   while (lo < last) {
     width = min(width, last - lo);
     for (int j = threadIdx.x; j < TAB; j += DDR_BLOCK) tab[j] = EMPTY;
     if (threadIdx.x == 0) s_claims = 0;
     __syncthreads();
-    for (uint32_t c = threadIdx.x / LANES; c < d.nch; c += DDR_BLOCK / LANES) {
-      const uint32_t be = d.bounds[(uint64_t)c * nb + b], end = be >> 16;
-      const uint64_t *run = d.rec + (uint64_t)c * CH;
-      for (uint32_t t0 = (be & 0xFFFFu) + sub; t0 < end; t0 += LANES * LOADS) {
-        uint64_t es[LOADS];
-#pragma unroll
-        for (int u = 0; u < LOADS; ++u) es[u] = t0 + u * LANES < end ? run[t0 + u * LANES] : EMPTY;
-#pragma unroll
-        for (int u = 0; u < LOADS; ++u) {
-          const uint64_t e = es[u];
-          const uint32_t k = (uint32_t)(e >> 32);
-          if (e == EMPTY || (uint64_t)(dds_hash(k) - (uint32_t)lo) >= width) continue;
-          if (*(volatile uint32_t *)&s_claims > CAP) break;
-          const bool keep_last = ddr_keep_last(d, e);
-          for (uint32_t s = mix32(k) & (TAB - 1);; s = (s + 1) & (TAB - 1)) {
-            uint64_t cur = *(volatile uint64_t *)&tab[s];
+    for (uint32_t c0 = threadIdx.x / LANES; c0 < d.nch; c0 += DDR_BLOCK / LANES) {
+      if (*(volatile uint32_t *)&s_claims > CAP) break;
+      ddr_run<LANES, CH>(d, backwards ? d.nch - 1 - c0 : c0, b, [&](uint64_t e) {
+        if (!ddr_in(e, lo, width)) return true;
+        if (*(volatile uint32_t *)&s_claims > CAP) return false;
+        const uint32_t k = (uint32_t)(e >> 32);
+        const bool keep_last = ddr_keep_last(d, e);
+        for (uint32_t s = mix32(k) & (TAB - 1);; s = (s + 1) & (TAB - 1)) {
+          uint64_t cur = *(volatile uint64_t *)&tab[s];
+          if (cur == EMPTY) {
+            cur = atomicCAS((unsigned long long *)&tab[s], (unsigned long long)EMPTY, (unsigned long long)e);
             if (cur == EMPTY) {
-              cur = atomicCAS((unsigned long long *)&tab[s], (unsigned long long)EMPTY, (unsigned long long)e);
-              if (cur == EMPTY) {
-                atomicAdd(&s_claims, 1u);
-                break;
-              }
+              atomicAdd(&s_claims, 1u);
+              return true;
             }
-            if ((uint32_t)(cur >> 32) != k) continue;
-            // two records of one key: the loser's flag goes (a record met
-            // again after its range was split loses to the same records)
-            if (keep_last ? cur < e : cur > e)
-              cur = keep_last ? atomicMax((unsigned long long *)&tab[s], (unsigned long long)e)
-                              : atomicMin((unsigned long long *)&tab[s], (unsigned long long)e);
-            const uint64_t loser = (keep_last ? cur < e : cur > e) ? cur : e;
-            d.win[ddr_index(d, loser)] = 0;
-            break;
           }
+          if ((uint32_t)(cur >> 32) != k) continue;
+          // two records of one key: the loser's flag goes (a record met
+          // again after its range was split loses to the same records)
+          if (keep_last ? cur < e : cur > e)
+            cur = keep_last ? atomicMax((unsigned long long *)&tab[s], (unsigned long long)e)
+                            : atomicMin((unsigned long long *)&tab[s], (unsigned long long)e);
+          const uint64_t loser = (keep_last ? cur < e : cur > e) ? cur : e;
+          d.win[ddr_index(d, loser)] = 0;
+          return true;
         }
-      }
+      });
     }
     __syncthreads();
     const uint32_t claims = s_claims;
@@ -844,7 +940,12 @@ __global__ __launch_bounds__(DDR_BLOCK) void ddr_resolve_kernel(DdrArgs d) {
       width = (width + 1) / 2;
     } else {
       lo += width;
-      if (claims <= CAP / 2) width *= 2;
+      // as wide as fills half the table at this density, two at least
+      if (claims <= CAP / 2) width *= claims ? max(2u, CAP / 2 / claims) : CAP;
+    }
+    if (lo < last && (last - lo) / width > DDR_PASSES) {
+      ddr_set<LANES, CH>(d, b, lo, last);
+      return;
     }
   }
 }
@@ -4292,25 +4393,37 @@ static uint64_t ddr_chunk(uint64_t n) {
 
 // The dedupe's buffers for a batch of n operations, carved from one scratch
 // allocation (each piece 256-byte aligned): records and range bounds of every
-// chunk (at most DDR_BLOCK * 8 operations), and a winner flag per operation.
-static uint64_t ddr_layout(uint64_t *base, uint64_t n, uint64_t **rec, uint32_t **bounds, uint8_t **win) {
+// chunk (at most DDR_BLOCK * 8 operations), a winner flag per operation and,
+// beyond the one-launch form, the words of ranges that are settled in HBM.
+struct DdrBuffers {
+  uint64_t *rec, *used, *set;
+  uint32_t *bounds;
+  uint8_t *win;
+};
+static uint64_t ddr_layout(uint64_t *base, uint64_t n, DdrBuffers *out) {
   // a chunk is shorter where the batch is (launch_dedupe); its bounds are the
   // larger part then
   const uint64_t ch = ddr_chunk(n), nch = (n + ch - 1) / ch;
-  auto words = [](uint64_t bytes) { return (bytes + 255) / 256 * 32; };
-  const uint64_t w_rec = words(nch * ch * 8), w_bounds = words(nch * (n > DDR_MORE ? DDR_BINS_BIG : DDR_BINS) * 4), w_win = words(n);
-  if (base) {
-    *rec = base;
-    *bounds = (uint32_t *)(base + w_rec);
-    *win = (uint8_t *)(base + w_rec + w_bounds);
-  }
-  return w_rec + w_bounds + w_win;
+  uint64_t at = 0;
+  const auto take = [&](uint64_t bytes) {
+    uint64_t *p = base ? base + at : nullptr;
+    at += (bytes + 255) / 256 * 32;
+    return p;
+  };
+  DdrBuffers d;
+  d.rec = take(nch * ch * 8);
+  d.bounds = (uint32_t *)take(nch * (n > DDR_MORE ? DDR_BINS_BIG : DDR_BINS) * 4);
+  d.win = (uint8_t *)take(n);
+  d.used = take(n > DDS_MAX ? 8 : 0);
+  d.set = take(n > DDS_MAX ? 2 * n * 8 : 0);
+  if (out) *out = d;
+  return at;
 }
 
 // Words of the dedupe scratch for n operations: the dedupe of plain launches
 // or the executor's set.
 static uint64_t dd_words_for(uint64_t n) {
-  return std::max(dd_set_words(n), ddr_layout(nullptr, n, nullptr, nullptr, nullptr));
+  return std::max(dd_set_words(n), ddr_layout(nullptr, n, nullptr));
 }
 
 // Worklist entries a stash drain may append: the whole stash table and the
@@ -4660,7 +4773,7 @@ static void launch_ddr(const DdrArgs &a, hipStream_t st) {
   hipLaunchKernelGGL((ddr_chunk_kernel<PER, BINS>), dim3(a.nch), dim3(DDR_BLOCK), 0, st, a);
   const dim3 ranges(1u << a.bits);
   if (BINS == DDR_BINS_BIG && a.n > 2 * DDR_MORE)
-    hipLaunchKernelGGL((ddr_resolve_kernel<PER, BINS, BINS == DDR_BINS_BIG ? 1 : 8>), ranges, dim3(DDR_BLOCK), 0, st,
+    hipLaunchKernelGGL((ddr_resolve_kernel<PER, BINS, BINS == DDR_BINS_BIG ? 2 : 8>), ranges, dim3(DDR_BLOCK), 0, st,
                        a);
   else
     hipLaunchKernelGGL((ddr_resolve_kernel<PER, BINS, 8>), ranges, dim3(DDR_BLOCK), 0, st, a);
@@ -4686,15 +4799,13 @@ static void launch_small(uint32_t mode, const OpsArgs &a, uint8_t *win, hipStrea
 // flags.
 static hive_status launch_dedupe(uint64_t *dd, uint32_t mode, const uint8_t *d_ops, const uint32_t *d_keys,
                                  uint64_t n, hipStream_t st, const uint8_t **win) {
-  uint64_t *rec = nullptr;
-  uint32_t *bounds = nullptr;
-  uint8_t *flags = nullptr;
-  (void)ddr_layout(dd, n, &rec, &bounds, &flags);
-  *win = flags;
+  DdrBuffers buf;
+  (void)ddr_layout(dd, n, &buf);
+  *win = buf.win;
   if (n <= DDS_MAX) {
     uint32_t bits = 0;
     while (((uint64_t)DDS_PER << bits) < n) ++bits;
-    const DdsArgs a{d_ops, d_keys, flags, (uint32_t)n, mode, bits};
+    const DdsArgs a{d_ops, d_keys, buf.win, (uint32_t)n, mode, bits};
     hipLaunchKernelGGL(dds_kernel, dim3(1u << bits), dim3(DDS_BLOCK), 0, st, a);
     return launch_check();
   }
@@ -4704,7 +4815,7 @@ static hive_status launch_dedupe(uint64_t *dd, uint32_t mode, const uint8_t *d_o
   while ((1u << bits) < DDR_BINS && (1024ull << bits) < n) ++bits;
   while ((1u << bits) < DDR_BINS_BIG && (8192ull << bits) < n) ++bits;
   const uint64_t ch = ddr_chunk(n);
-  DdrArgs a{d_ops, d_keys, flags, rec, bounds, (uint32_t)n, mode, bits, (uint32_t)((n + ch - 1) / ch), OP_NONE};
+  DdrArgs a{d_ops, d_keys, buf.win, buf.rec, buf.bounds, buf.set, buf.used, (uint32_t)n, mode, bits, (uint32_t)((n + ch - 1) / ch), OP_NONE};
   const bool by_type = mode == OP_MIXED && n >= (1ull << 31);  // indices fill the word
   for (uint32_t only : {(uint32_t)OP_INSERT, (uint32_t)OP_DELETE}) {
     if (by_type) a.only = only;
