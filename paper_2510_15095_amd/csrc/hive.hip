@@ -2717,8 +2717,10 @@ __device__ __forceinline__ void drain_all(const DrainArgs &d, uint32_t *hint, Ct
 // A split entry's way: in each round whose range holds its bucket, it stays
 // when one of its candidate hashes still addresses the bucket under the
 // round's next mask, otherwise it moves to the bucket's partner (Section
-// IV-C-1).  One round (the usual call) touches the buckets it splits; more
-// rounds, all of them.  Movers take the first slots of their new buckets,
+// IV-C-1).  One round (the usual call) touches the buckets it splits, and so do
+// two: those left of the first round and those at the second's start (a step of
+// 1,024 pairs over the end of a round at 2^23 buckets took 457 us when it read
+// all of them, now 15).  Movers take the first slots of their new buckets,
 // which are EMPTY and which no other bucket's entries reach: a bucket b beyond
 // the old count has one ancestor, b without its top bits.
 template <int S>
@@ -2789,12 +2791,18 @@ __global__ __launch_bounds__(BLOCK) void resize_kernel(ResizeArgs a, DrainArgs d
   if (dir > 0) {
     const uint32_t rounds = s_rounds;
     const int g = lane / S, sl = lane % S;
-    const uint64_t first = rounds == 1 ? r_sp[0] : 0, count = rounds == 1 ? r_seg[0] : nb;
+    // [0, head) and [r_sp[0], + r_seg[0]), in one where they meet
+    uint64_t head = rounds == 1 ? 0 : min(r_seg[1], nb), tail = r_seg[0];
+    if (rounds > 1 && head >= r_sp[0]) {
+      head = max(head, r_sp[0] + tail);
+      tail = 0;
+    }
+    const uint64_t count = head + tail;
     const uint64_t groups = (uint64_t)gridDim.x * WAVES * T::G;
     // a uniform trip count per wave: the shuffles below take every lane
     for (uint64_t j0 = ((uint64_t)blockIdx.x * WAVES + wv) * T::G; j0 < count; j0 += groups) {
-      const uint64_t src = first + j0 + g;
-      const bool have = j0 + g < count;
+      const uint64_t at = j0 + g, src = at < head ? at : r_sp[0] + (at - head);
+      const bool have = at < count;
       const uint64_t w = have ? a.buckets[src * S + sl] : EMPTY;
       uint64_t b = src;
       if (w != EMPTY) {

@@ -1,0 +1,88 @@
+"""Resize steps over the end of a hashing round and contractions of many pairs:
+parity with the dictionary, geometry, and time against steps of the same size
+that never were slow."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2510_15095_amd import workload as wl
+from test_gpu_batch_paths import H, _check_linear, _linear, case, dev, host  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("S", [16, 32, 64])
+@pytest.mark.parametrize("nb0,deltas", [(1000, (50, 974, 30)), (500, (13, 600, 2000)), (1000, (24, 1, 600, 1200)),
+                                        (3, (2, 2, 1, 9))])
+def test_steps_over_the_end_of_a_round(H, S, nb0, deltas):  # noqa: F811
+    """A few of the first round's last buckets and of the second's first, with
+    none of those between them (nb0 and deltas: 1000 + 50 is 24 and 26), up to
+    all: every key stays in place and reachable, and back down again."""
+    mb = 1 << 13
+    n = nb0 * S * 3 // 4 + 20
+    case(f"steps over a round's end S={S} nb0={nb0} deltas={deltas}")
+    ks = wl.KeyStream(2000 + nb0)
+    keys = ks.range(0, n)
+    t, o = _linear(H, S, nb0, mb, stash_capacity=64, pending_capacity=4096), oracle.O1()
+    t.insert(dev(keys), dev(wl.values_for(keys)), flags=H.HIVE_UNIQUE)
+    o.insert(keys, wl.values_for(keys))
+    nb, at = nb0, n
+    q = ks.range(0, 3 * n)
+    for d in (*deltas, *[-x for x in reversed(deltas)]):
+        t.resize(d)
+        got = t.stats()["n_buckets"]
+        assert got == nb + d if d > 0 else max(nb0, nb + d) <= got <= nb
+        nb = got
+        _check_linear(t, o, S, nb0, mb, nb)
+        v, f = t.lookup(dev(q))
+        ov, of = o.lookup(q)
+        assert np.array_equal(host(f), of) and np.array_equal(host(v), ov)
+        more = ks.range(at, at + n // 16)
+        at += more.size
+        t.insert(dev(more), dev(wl.values_for(more)), flags=H.HIVE_UNIQUE)
+        o.insert(more, wl.values_for(more))
+        gone = more[::2]
+        assert np.array_equal(host(t.delete(dev(gone), flags=H.HIVE_UNIQUE)), o.delete(gone))
+    t.close()
+
+
+def _best(fn, prep, reps=5):
+    import torch
+    best = 1e9
+    for _ in range(reps):
+        prep()
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda.synchronize()
+        a.record()
+        fn()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+def _half_full(H, nb, mb):  # noqa: F811
+    import torch
+    t = _linear(H, 16, nb, mb, max_batch=1 << 20)
+    k = wl.KeyStream(2100).range(0, nb * 8)
+    for a in range(0, k.size, 1 << 24):
+        part = torch.from_numpy(k[a:a + (1 << 24)]).cuda()
+        t.insert(part, part, flags=H.HIVE_UNIQUE)
+    return t
+
+
+def test_a_step_over_a_rounds_end_touches_few_buckets(H):  # noqa: F811
+    """1,024 pairs over the end of a round of 2^22 buckets: at most three times
+    the same step within a round and 20 us (measured 15 and 14 us; with a read of
+    all buckets about 230)."""
+    nb = (1 << 22) - 512
+    case("time of a step over a round's end")
+    t = _half_full(H, nb, 1 << 23)
+    over = _best(lambda: t.resize(1024), lambda: t.resize(nb - t.stats()["n_buckets"]) if t.stats()["n_buckets"] != nb else None)
+    assert t.stats()["n_buckets"] == nb + 1024
+    t.resize(-2048)
+    nb2 = t.stats()["n_buckets"]
+    within = _best(lambda: t.resize(256), lambda: t.resize(nb2 - t.stats()["n_buckets"]) if t.stats()["n_buckets"] != nb2 else None)
+    print(f"over the end {over:.3f} ms, within {within:.3f} ms")
+    assert over <= 3 * within + 0.020
+    t.close()
