@@ -57,8 +57,10 @@ constexpr int BLOCK = 64 * WAVES;
 #endif
 constexpr int EVICT_GRID = 2048;  // most blocks of the eviction phase (all resident at once)
 constexpr int RESIZE_GRID = 1024; // most blocks of resize_kernel (they stride over buckets and stash words)
-constexpr int MERGE_GRID = 256;   // blocks of merge_kernel, one per compute unit
-constexpr int MERGE_BLOCK = 512;
+constexpr int MERGE_GRID = 512;   // blocks of merge_kernel, two per compute unit
+constexpr int MERGE_BLOCK = 512;  // (a larger one has no room beside a resident executor)
+constexpr uint64_t MERGE_RUN = 64;  // pairs of a run, at least
+constexpr int MERGE_LOADS = 4;      // pairs in flight per group of lanes
 // Most blocks of a probe launch: larger batches stride over tiles, about
 // eight tiles per block at 2^26 operations (bulk step +4% against one tile
 // per block, measured over 2,048 .. 65,536 blocks: the launch pays less
@@ -2523,28 +2525,35 @@ __device__ __forceinline__ void split_pair(const ResizeArgs &a, uint64_t im, uin
   }
 }
 
-// State word of a merge phase over n pairs (1: test, 2: move; 0: none left):
-// at most one run of pairs per block of merge_kernel (a claim and a count of
-// each run are atomics on one address, about 64 ns each).
-constexpr uint64_t M28 = (1ull << 28) - 1;
-__device__ __forceinline__ uint64_t merge_phase(uint64_t kind, uint64_t n) {
-  return n ? (kind << 56) | (min(n, (uint64_t)MERGE_GRID) << 28) : 0;
+// State word of a merge phase over n pairs: kind:4 (1 test, 2 move, 0 none
+// left) | runs:12 | number of the phase:48, the last one's plus one.  At most
+// one run of pairs per block of merge_kernel, and of MERGE_RUN pairs at least.
+// (A claim is compared by its distance to the number, so the numbers must not
+// come round: 48 bits are decades of phases.)
+constexpr int MERGE_NUMBER_BITS = 48;
+constexpr uint64_t MERGE_NUMBER = (1ull << MERGE_NUMBER_BITS) - 1;
+static_assert(MERGE_GRID < 1 << 12, "runs of a phase in 12 bits");
+__device__ __forceinline__ uint64_t merge_phase(uint64_t kind, uint64_t n, uint64_t last) {
+  const uint64_t number = (last + 1) & MERGE_NUMBER;
+  const uint64_t runs = min((n + MERGE_RUN - 1) / MERGE_RUN, (uint64_t)MERGE_GRID);
+  return n ? (kind << 60) | (runs << MERGE_NUMBER_BITS) | number : number;
+}
+
+// The word that holds the number of the last phase in which run r was claimed.
+__device__ __forceinline__ uint64_t *merge_claim(const Ctl *c, uint64_t r) {
+  static_assert(MERGE_GRID <= 8 * NSHARD, "eight runs a shard");
+  return &shard_of(c, r % NSHARD)->merge_claim[r / NSHARD];
 }
 
 // Merge pair j of the segment, walked from the top: (lo, lo + 2^m) with
 // lo = sp - 1 - j.  It fits when hi's entries fit lo's EMPTY slots
 // (Section IV-C-2); the first pair that does not fit bounds the commit.
-// FRESH: agent-scope loads and stores, for phases of one launch that read what
-// blocks of other XCDs wrote in the one before: no L2 write-back and no
-// invalidation is needed then (a fence pair per run of pairs made a
-// contraction take 551 us).
-template <int S, bool FRESH = false>
+template <int S>
 __device__ __forceinline__ void merge_test_pair(const ResizeArgs &a, Ctl *c, uint64_t im, uint64_t sp, uint64_t j,
                                                 int g, int sl) {
   using T = Traits<S>;
   const uint64_t lo = sp - 1 - j, hi = lo + im + 1;
-  const uint64_t wl = FRESH ? load_fresh(a.buckets + lo * S + sl) : a.buckets[lo * S + sl];
-  const uint64_t wh = FRESH ? load_fresh(a.buckets + hi * S + sl) : a.buckets[hi * S + sl];
+  const uint64_t wl = a.buckets[lo * S + sl], wh = a.buckets[hi * S + sl];
   const uint64_t fl = (ballot(wl == EMPTY) >> (g * S)) & T::FULL;
   const uint64_t lh = (ballot(wh != EMPTY) >> (g * S)) & T::FULL;
   if (sl == 0 && __builtin_popcountll(lh) > __builtin_popcountll(fl))
@@ -2553,29 +2562,76 @@ __device__ __forceinline__ void merge_test_pair(const ResizeArgs &a, Ctl *c, uin
 
 // Move a merge pair that fits: the r-th live entry of hi goes to the r-th
 // EMPTY slot of lo; stash entries with a candidate in hi now address lo.
-template <int S, bool FRESH = false>
+template <int S>
 __device__ __forceinline__ void merge_move_pair(const ResizeArgs &a, uint64_t im, uint64_t sp, uint64_t j, int g,
                                                 int sl) {
   using T = Traits<S>;
   const uint64_t lo = sp - 1 - j, hi = lo + im + 1;
-  const uint64_t wl = FRESH ? load_fresh(a.buckets + lo * S + sl) : a.buckets[lo * S + sl];
-  const uint64_t wh = FRESH ? load_fresh(a.buckets + hi * S + sl) : a.buckets[hi * S + sl];
+  const uint64_t wl = a.buckets[lo * S + sl], wh = a.buckets[hi * S + sl];
   const uint64_t fl = (ballot(wl == EMPTY) >> (g * S)) & T::FULL;
   const uint64_t lh = (ballot(wh != EMPTY) >> (g * S)) & T::FULL;
   if (wh != EMPTY) {
     const uint32_t r = __builtin_popcountll(lh & ((1ull << sl) - 1ull));
-    uint64_t *to = a.buckets + lo * S + nth_set_bit(fl, r), *from = a.buckets + hi * S + sl;
-    if constexpr (FRESH) {
-      __hip_atomic_store(to, wh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(from, EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      *to = wh;
-      *from = EMPTY;
-    }
+    a.buckets[lo * S + nth_set_bit(fl, r)] = wh;
+    a.buckets[hi * S + sl] = EMPTY;
   }
-  if (sl == 0) {
-    const uint32_t word = FRESH ? ld_ctl32(a.hint + (hi >> 5)) : a.hint[hi >> 5];
-    if ((word >> (hi & 31)) & 1u) set_hint(a.hint, (uint32_t)lo);
+  if (sl == 0 && ((a.hint[hi >> 5] >> (hi & 31)) & 1u)) set_hint(a.hint, (uint32_t)lo);
+}
+
+// Pairs [begin, end) of a merge phase (TEST, or move) by one block of
+// merge_kernel, as the two functions above do one pair.  MERGE_LOADS pairs per
+// group of lanes are in flight, and a word finds its EMPTY slot by two lane
+// permutations (its rank among the live, the slot's among the EMPTY ones): 256
+// blocks that waited for each pair and selected slots bit by bit took 715 us
+// for 2^21 pairs in three rounds.  Loads and stores are agent-scope: the phases
+// of one launch read what blocks of other XCDs wrote in the one before, and so
+// need no L2 write-back and no invalidation (a fence pair per run of pairs made
+// a contraction take 551 us).
+template <int S, bool TEST>
+__device__ __forceinline__ void merge_run(const ResizeArgs &a, Ctl *c, uint64_t im, uint64_t sp, uint64_t begin,
+                                          uint64_t end) {
+  using T = Traits<S>;
+  constexpr int U = MERGE_LOADS;
+  constexpr uint64_t STEP = (uint64_t)(MERGE_BLOCK / 64) * T::G;
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int g = lane / S, sl = lane % S;
+  const uint64_t below = (1ull << sl) - 1ull;
+  // a uniform trip count per wave: every lane reaches the ballots
+  for (uint64_t j0 = begin + (uint64_t)wv * T::G; j0 < end; j0 += U * STEP) {
+    uint64_t wl[U], wh[U];
+    uint32_t hint[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint64_t j = j0 + u * STEP + g, lo = sp - 1 - j, hi = lo + im + 1;
+      const bool have = j < end;
+      wl[u] = have ? load_fresh(a.buckets + lo * S + sl) : EMPTY;
+      wh[u] = have ? load_fresh(a.buckets + hi * S + sl) : EMPTY;
+      hint[u] = !TEST && have && sl == 0 ? ld_ctl32(a.hint + (hi >> 5)) >> (hi & 31) : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint64_t j = j0 + u * STEP + g, lo = sp - 1 - j, hi = lo + im + 1;
+      const uint64_t fl = (ballot(wl[u] == EMPTY) >> (g * S)) & T::FULL;
+      const uint64_t lh = (ballot(wh[u] != EMPTY) >> (g * S)) & T::FULL;
+      const int live = __builtin_popcountll(lh);
+      if constexpr (TEST) {
+        if (sl == 0 && live > __builtin_popcountll(fl))
+          __hip_atomic_fetch_min(&c->merge_commit, j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else {
+        // live words to the group's first lanes, the others behind them
+        const int rank = __builtin_popcountll(lh & below);
+        const int to = (g * S + (wh[u] != EMPTY ? rank : live + sl - rank)) << 2;
+        const uint32_t p0 = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(uint32_t)wh[u]);
+        const uint32_t p1 = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(uint32_t)(wh[u] >> 32));
+        const int slot = __builtin_popcountll(fl & below);  // of an EMPTY slot: its rank
+        const uint64_t w = shfl64(((uint64_t)p1 << 32) | p0, g * S + min(slot, S - 1));
+        if (wl[u] == EMPTY && slot < live)
+          __hip_atomic_store(a.buckets + lo * S + sl, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (wh[u] != EMPTY)
+          __hip_atomic_store(a.buckets + hi * S + sl, EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (hint[u] & 1u) set_hint(a.hint, (uint32_t)lo);
+      }
+    }
   }
 }
 
@@ -2851,8 +2907,7 @@ __global__ __launch_bounds__(BLOCK) void resize_kernel(ResizeArgs a, DrainArgs d
       v->resize_dir = -1;
       v->resize_todo = todo;
       plan_next(v);
-      v->merge_done = 0;
-      v->merge_state = merge_phase(1, v->seg);
+      v->merge_state = merge_phase(1, v->seg, v->merge_state & MERGE_NUMBER);
     }
   }
 }
@@ -2860,63 +2915,114 @@ __global__ __launch_bounds__(BLOCK) void resize_kernel(ResizeArgs a, DrainArgs d
 // A contraction (Section IV-C-2): per hashing round, every pair of the
 // segment is tested, top down, then the pairs above the first that does not
 // fit are moved.  The phases run within one launch: blocks claim runs of pairs
-// of the current phase by an atomic on one word, and the block that completes
-// a phase publishes the next.  A block waits only for runs that other running
-// blocks have claimed, so the launch ends however few blocks run at a time.
+// of the current phase, and the block that completes a phase publishes the
+// next.  A block takes the run of its own number and, when it has waited a
+// while, one that nobody has claimed, so that it waits only for runs that other
+// running blocks have claimed and the launch ends however few blocks run at a
+// time.  Claims are words of their own and completions count on two levels:
+// with one counter for all claims and one for all completions, of about 64 ns
+// an atomic, 131,072 pairs in three rounds (six phases of 256 runs) took 136 us,
+// now 61; three rounds down from 2^20 / 2^23 more buckets 715 / 5,451 us, now
+// 373 / 2,756.  (A launch per phase, with the host between rounds: 64, 290 and
+// 2,609.)  A phase costs about 6 us besides its pairs, and these are bound by
+// what 16 waves a compute unit keep in flight.
 template <int S>
 __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(ResizeArgs a) {
-  using T = Traits<S>;
-  __shared__ uint64_t s_state, s_mine;
+  __shared__ uint64_t s_state;
+  __shared__ uint32_t s_pick, s_won;
   Ctl *c = a.ctl;
-  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
-  const int g = lane / S, sl = lane % S;
+  const uint32_t tid = threadIdx.x;
+  uint64_t seen = ~0ull;  // the phase the block waits in, and for how long
+  uint32_t polls = 0;
   for (;;) {
     if (tid == 0) {
-      uint64_t st = ld_ctl(&c->merge_state);
-      uint64_t mine = ~0ull;
-      if ((st >> 56) != 0 && (st & M28) < ((st >> 28) & M28)) {
-        st = add64(&c->merge_state, 1);
-        if ((st >> 56) != 0 && (st & M28) < ((st >> 28) & M28)) mine = st & M28;
-      }
-      s_state = st;
-      s_mine = mine;
+      s_state = ld_ctl(&c->merge_state);
+      s_pick = ~0u;
     }
     __syncthreads();
-    const uint64_t st = s_state, mine = s_mine;
+    const uint64_t st = s_state, nch = (st >> MERGE_NUMBER_BITS) & 0xFFFu, number = st & MERGE_NUMBER;
+    if ((st >> 60) == 0) return;
+    if (st != seen) {
+      seen = st;
+      polls = 0;
+    }
+    // a run whose last claim is an earlier phase's (a later one's: this block's
+    // view of the state is old, and its phase complete)
+    static_assert(MERGE_GRID <= MERGE_BLOCK, "a thread per run");
+    const bool look = polls == 0 ? tid == blockIdx.x : polls >= 8;
+    uint64_t old = 0;
+    bool open = false;
+    if (look && tid < nch) {
+      old = load_fresh(merge_claim(c, tid));
+      const uint64_t age = (number - old) & MERGE_NUMBER;
+      open = age != 0 && age <= MERGE_NUMBER / 2;
+      // waiting blocks start at different runs
+      if (open) atomicMin(&s_pick, (uint32_t)((tid + nch - blockIdx.x % nch) % nch));
+    }
+    if (tid == 0) s_won = 0;
     __syncthreads();
-    if ((st >> 56) == 0) return;
-    if (mine == ~0ull) {  // all claimed: other blocks are at work on them
+    const uint64_t mine = ((uint64_t)s_pick + blockIdx.x % nch) % nch;
+    if (s_pick != ~0u && tid == mine && open) s_won = cas64(merge_claim(c, mine), old, number) == old;
+    __syncthreads();
+    ++polls;
+    if (!s_won) {  // other blocks are at work
       __builtin_amdgcn_s_sleep(15);
       continue;
     }
-    const bool test = (st >> 56) == 1;
-    const uint64_t nch = (st >> 28) & M28, im = ld_ctl(&c->im), sp = ld_ctl(&c->sp);
+    const bool test = (st >> 60) == 1;
+    const uint64_t im = ld_ctl(&c->im), sp = ld_ctl(&c->sp);
     const uint64_t pairs = test ? ld_ctl(&c->seg) : ld_ctl(&c->merge_commit);
     const uint64_t per = (pairs + nch - 1) / nch, end = min(pairs, (mine + 1) * per);
-    constexpr uint64_t STEP = (uint64_t)(MERGE_BLOCK / 64) * T::G;
-    for (uint64_t j = mine * per + (uint64_t)wv * T::G + g; j < end; j += STEP) {
-      if (test)
-        merge_test_pair<S, true>(a, c, im, sp, j, g, sl);
-      else
-        merge_move_pair<S, true>(a, im, sp, j, g, sl);
-    }
+    if (test)
+      merge_run<S, true>(a, c, im, sp, mine * per, end);
+    else
+      merge_run<S, false>(a, c, im, sp, mine * per, end);
     // every wave's stores and minima are done before the run is counted
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid == 0) {
-      if (add64(&c->merge_done, 1) + 1 == nch) {
-        volatile Ctl *v = c;
-        const uint64_t seg = ld_ctl(&c->seg), commit = ld_ctl(&c->merge_commit);
-        v->merge_done = 0;
-        uint64_t next = 0;
-        if (test && commit > 0) {
-          next = merge_phase(2, commit);
-        } else {
-          merge_segment_done(v, sp, seg, commit);
-          if (v->seg > 0) next = merge_phase(1, v->seg);
+      Shard *sh = shard_of(c, mine % NSHARD);
+      if (add64(&sh->merge_done, 1) + 1 == (nch - mine % NSHARD + NSHARD - 1) / NSHARD) {
+        __hip_atomic_store(&sh->merge_done, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // before the next phase can count on it
+        if (add64(&c->merge_done, 1) + 1 == min(nch, (uint64_t)NSHARD)) {
+          // merge_segment_done and plan_next in registers: loads and stores in
+          // flight together, and no fence (a chain of volatile accesses and an
+          // L2 write-back cost 10 us a segment)
+          const uint64_t seg = ld_ctl(&c->seg), commit = ld_ctl(&c->merge_commit), initial = ld_ctl(&c->initial_buckets);
+          uint64_t buckets = ld_ctl(&c->n_buckets), todo = ld_ctl(&c->resize_todo);
+          const auto put = [](uint64_t *p, uint64_t v) {
+            __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          };
+          put(&c->merge_done, 0);
+          uint64_t next;
+          if (test && commit > 0) {
+            next = merge_phase(2, commit, number);
+          } else {
+            uint64_t im2 = im, sp2 = sp - commit, seg2 = 0;
+            buckets -= commit;
+            todo = commit < seg ? 0 : todo - commit;  // a pair did not fit: the call stops here
+            if (buckets <= initial) todo = 0;
+            if (todo > 0) {
+              if (sp2 == 0) {
+                im2 >>= 1;
+                sp2 = im2 + 1;
+              }
+              seg2 = min(min(todo, sp2), buckets - initial);
+              put(&c->merge_commit, seg2);
+            } else {
+              put((uint64_t *)&c->resize_dir, 0);
+            }
+            put(&c->im, im2);
+            put(&c->sp, sp2);
+            put(&c->seg, seg2);
+            put(&c->n_buckets, buckets);
+            put(&c->resize_todo, todo);
+            next = merge_phase(seg2 > 0 ? 1 : 0, seg2, number);
+          }
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // all of it before the phase
+          __hip_atomic_store(&c->merge_state, next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        __threadfence();
-        __hip_atomic_store(&c->merge_state, next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
     __syncthreads();
@@ -3172,6 +3278,8 @@ struct DrainQueue {
   uint32_t final_seen;        // the host stopped and every submitted batch was ingested
   uint32_t pad_;
 };
+
+constexpr uint64_t M28 = (1ull << 28) - 1;
 
 __device__ __forceinline__ uint64_t make_state(uint32_t ph, uint64_t nch) {
   return ((uint64_t)ph << 56) | ((nch & M28) << 28);

@@ -75,10 +75,11 @@ struct alignas(128) Ctl {
   uint64_t split_happened; // a split ran since the last stash drain
   uint64_t initial_buckets;
   uint64_t max_buckets;
-  uint64_t merge_state;    // merge_kernel: phase:8 | chunks:28 | claimed:28 (0: nothing to merge)
+  uint64_t merge_state;    // merge_kernel: kind of phase:4 (0: nothing to merge) | runs:12 | number:48
   uint64_t pad2_[7];
-  // line 3: maintenance kernels (dump, placement census); runs of the current
-  // phase completed (merge_kernel: not on the line that waiting blocks poll)
+  // line 3: maintenance kernels (dump, placement census); shards whose runs of
+  // the current phase are complete (merge_kernel: not on the line that waiting
+  // blocks poll)
   uint64_t dump_count;
   uint64_t place_first;
   uint64_t place_second;
@@ -107,6 +108,8 @@ struct Shard {
   uint64_t pending_inserts;
   uint64_t stash_unreserved;  // stash placements of launches that needed no reservation
   uint64_t plan_inserts;      // inserts of a mixed batch counted by block s of count_inserts_kernel
+  uint64_t merge_claim[8];    // merge_kernel: phase in which run s, s + NSHARD, ... was claimed last
+  uint64_t merge_done;        // and its runs of the current phase that are complete
 };
 constexpr uint64_t CTL_BYTES = sizeof(Ctl) + NSHARD * SHARD_STRIDE;
 

@@ -86,3 +86,17 @@ def test_a_step_over_a_rounds_end_touches_few_buckets(H):  # noqa: F811
     print(f"over the end {over:.3f} ms, within {within:.3f} ms")
     assert over <= 3 * within + 0.020
     t.close()
+
+
+def test_a_large_contraction_keeps_loads_in_flight(H):  # noqa: F811
+    """2^20 pairs merged: at most 3.5 times as long as splitting them (measured
+    1.6 times; one pair in flight per group of lanes 5 times)."""
+    nb = 1 << 20
+    case("time of a contraction")
+    t = _half_full(H, nb, 2 * nb)
+    up = _best(lambda: t.resize(nb), lambda: t.resize(-nb) if t.stats()["n_buckets"] != nb else None, 3)
+    down = _best(lambda: t.resize(-nb), lambda: t.resize(nb) if t.stats()["n_buckets"] == nb else None, 3)
+    assert t.stats()["n_buckets"] == nb
+    print(f"split {up:.3f} ms, merge {down:.3f} ms")
+    assert down <= 3.5 * up
+    t.close()
