@@ -417,16 +417,24 @@ __device__ __forceinline__ void dedupe_thread(uint64_t *dd, uint64_t mask, uint3
 // the loop ends.  Operations beyond the record list (a hot key's) go to the
 // table directly, and the flags then take a second reading of the keys.
 // ---------------------------------------------------------------------------
+// Most LDS of a block that finds room beside a resident executor's blocks of 25
+// KiB.  (Measured with blocks that wait out a time: next to one of them on a
+// compute unit blocks of 16 waves run with 80 KiB and wait with 81.25, though
+// 135 are free; next to two, blocks of any size do.)
+constexpr uint32_t BESIDE_LDS = 80 * 1024;
 constexpr int DDS_BLOCK = 1024;
 constexpr uint64_t DDS_MAX = 1ull << 14;
 constexpr uint32_t DDS_PER = 512;     // operations per range aimed at
 constexpr int DDS_TAB = 4096;         // table entries (32 KiB)
-constexpr int DDS_LIST = 8192;        // records held (64 KiB)
+constexpr int DDS_LIST = 6080;        // records held (with the table 80 KiB at most, see BESIDE_LDS)
 // the executor's blocks
 constexpr uint64_t DDS_EXEC_MAX = 1ull << 14;
 constexpr int DDS_EXEC_TAB = 2048;
 constexpr int DDS_EXEC_LIST = 1024;
 constexpr int DDS_LOADS = 8;          // keys in flight per thread
+// and of a mixed batch, whose types are in flight too: with 8 the kernel takes 42
+// registers, and 16 waves of more than 40 have no room beside a resident executor
+constexpr int DDS_MIXED_LOADS = 7;
 static_assert(DDS_MAX < (1ull << 31), "an index shares a word with the type bit");
 
 struct DdsArgs {
@@ -490,7 +498,7 @@ __device__ __forceinline__ bool dds_kept(const uint64_t *tab, uint64_t e) {
 
 // Operations base + j * NT + thread of the batch as records, EMPTY
 // where there is none to record or its key is outside [lo, lo + width).
-template <int NT, int U = DDS_LOADS>
+template <int NT, int U>
 __device__ __forceinline__ void dds_read(const DdsArgs &d, uint32_t base, uint32_t lo, uint64_t width, uint64_t *e) {
   uint32_t k[U], o[U];
 #pragma unroll
@@ -506,13 +514,13 @@ __device__ __forceinline__ void dds_read(const DdsArgs &d, uint32_t base, uint32
     // disjoint by contract, so one table takes both
     const uint32_t ty = (d.mode == OP_MIXED && o[j] == OP_DELETE) ? 1u : 0u;
     const bool rec = (o[j] == OP_INSERT || o[j] == OP_DELETE) && valid_key(k[j]) &&
-                     (uint64_t)(dds_hash(k[j]) - lo) < width;
+                     dds_hash(k[j]) - lo <= (uint32_t)(width - 1);
     e[j] = rec ? ((uint64_t)k[j] << 32) | (ty << 31) | i : EMPTY;
   }
 }
 
 // Range `range` of the batch, by a block of NT threads (every one calls it).
-template <int NT, int TAB, int LIST>
+template <int NT, int U, int TAB, int LIST>
 __device__ __forceinline__ void dds_range_of(const DdsArgs &d, uint32_t range, DdsShared<TAB, LIST> &sh) {
   constexpr uint32_t CAP = TAB * 5 / 8;
   static_assert(CAP + NT < TAB, "one claim per thread past the limit still leaves EMPTY words");
@@ -527,12 +535,12 @@ __device__ __forceinline__ void dds_range_of(const DdsArgs &d, uint32_t range, D
     for (int j = threadIdx.x; j < TAB; j += NT) tab[j] = EMPTY;
     if (threadIdx.x == 0) sh.count = sh.claims = 0;
     __syncthreads();
-    for (uint32_t base = 0; base < d.n; base += DDS_LOADS * NT) {
-      uint64_t e[DDS_LOADS], m[DDS_LOADS];
-      dds_read<NT>(d, base, (uint32_t)lo, width, e);
+    for (uint32_t base = 0; base < d.n; base += U * NT) {
+      uint64_t e[U], m[U];
+      dds_read<NT, U>(d, base, (uint32_t)lo, width, e);
       uint32_t c = 0;
 #pragma unroll
-      for (int j = 0; j < DDS_LOADS; ++j) {
+      for (int j = 0; j < U; ++j) {
         m[j] = ballot(e[j] != EMPTY);
         c += (uint32_t)__popcll(m[j]);
       }
@@ -541,7 +549,7 @@ __device__ __forceinline__ void dds_range_of(const DdsArgs &d, uint32_t range, D
       if (lane == 0) at = atomicAdd(&sh.count, c);
       at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
 #pragma unroll
-      for (int j = 0; j < DDS_LOADS; ++j) {
+      for (int j = 0; j < U; ++j) {
         if (e[j] != EMPTY) {
           const uint32_t pos = at + rank_below(m[j]);
           if (pos < LIST)
@@ -566,11 +574,11 @@ __device__ __forceinline__ void dds_range_of(const DdsArgs &d, uint32_t range, D
         d.win[(uint32_t)e & 0x7FFFFFFFu] = dds_kept<TAB>(tab, e);
       }
       if (spilled) {
-        for (uint32_t base = 0; base < d.n; base += DDS_LOADS * NT) {
-          uint64_t e[DDS_LOADS];
-          dds_read<NT>(d, base, (uint32_t)lo, width, e);
+        for (uint32_t base = 0; base < d.n; base += U * NT) {
+          uint64_t e[U];
+          dds_read<NT, U>(d, base, (uint32_t)lo, width, e);
 #pragma unroll
-          for (int j = 0; j < DDS_LOADS; ++j)
+          for (int j = 0; j < U; ++j)
             if (e[j] != EMPTY) d.win[(uint32_t)e[j] & 0x7FFFFFFFu] = dds_kept<TAB>(tab, e[j]);
         }
       }
@@ -585,9 +593,11 @@ __device__ __forceinline__ void dds_range_of(const DdsArgs &d, uint32_t range, D
   }
 }
 
+template <uint32_t MODE>
 __global__ __launch_bounds__(DDS_BLOCK) void dds_kernel(DdsArgs d) {
   __shared__ DdsShared<DDS_TAB, DDS_LIST> sh;
-  dds_range_of<DDS_BLOCK>(d, blockIdx.x, sh);
+  d.mode = MODE;  // known when the reads are compiled
+  dds_range_of<DDS_BLOCK, MODE == OP_MIXED ? DDS_MIXED_LOADS : DDS_LOADS>(d, blockIdx.x, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -611,24 +621,25 @@ __global__ __launch_bounds__(DDS_BLOCK) void dds_kernel(DdsArgs d) {
 // over chunks in two launches and a scatter to whole partitions before a
 // resolve of two passes took five launches, and partitions of more distinct
 // keys than their tables a set in HBM.)  Time at 2^16, 2^18 and 2^20 inserts
-// of 2^20 keys: 18, 21 and 36 us (five launches: 49, 51 and 62 us); at 2^24, 2^26
-// and 2^28 distinct keys: 0.46, 2.87 and 28.1 ms (1.81, 7.95 and 34.0); a 2^22
-// Zipf(0.99) mixed batch 62 us (84).  Slower is only a batch of 2^25 operations
-// and more whose keys repeat dozens of times: 2^26 and 2^28 on 2^20 keys 2.95 and
-// 10.3 ms (2.53 and 8.9); whole inserts of them are not (3.76 and 13.2 ms for 4.04
-// and 14.4), deletes are (3.68 and 12.9 for 3.29 and 11.7).  Bound by LDS atomics
+// of 2^20 keys: 18, 21 and 39 us (five launches: 49, 51 and 62 us); at 2^22, 2^24,
+// 2^26 and 2^28 distinct keys: 0.12, 0.56, 5.3 and 29.7 ms (0.49, 1.80, 7.9 and
+// 34.2).  Slower is only a batch of 2^25 operations and more whose keys repeat
+// dozens of times: 2^26 and 2^28 on 2^20 keys 2.91 and 10.7 ms (2.54 and 8.9); whole
+// inserts of them are not (3.69 and 13.8 ms for 3.99 and 14.4), deletes are (3.62
+// and 13.2 for 3.30 and 11.7).  Bound by LDS atomics
 // and the latency between the phases of a block.
 //
 // Inserts and deletes of a mixed batch share the ranges; bit 31 of a record
 // is the type, so a mixed batch of 2^31 operations and more runs once per
 // type (`only`).  A range with more distinct keys than the table takes is
-// worked through in sub-ranges, as in dds_kernel; beyond 2^25 operations that
-// is the ordinary course.  Runs get short with many ranges (two records at 2^25), but
+// worked through in sub-ranges, as in dds_kernel; beyond 2^24 operations that
+// is the ordinary course.  Runs get short with many ranges (one record from 2^24 on), but
 // the runs of neighbouring ranges share cache lines, and the neighbours run
 // on one XCD at about the same time.
 // ---------------------------------------------------------------------------
 constexpr int DDR_BLOCK = 1024;
-constexpr int DDR_BINS = 512;       // most hash ranges of batches of up to DDR_MORE operations
+constexpr int DDR_BINS = 512;       // most hash ranges of batches of up to 2^20 operations,
+constexpr int DDR_BINS_MID = 1024;  // of up to DDR_MORE
 constexpr int DDR_BINS_BIG = 4096;  // and beyond
 constexpr uint64_t DDR_MORE = 1ull << 22;
 
@@ -653,11 +664,26 @@ __device__ __forceinline__ bool ddr_keep_last(const DdrArgs &d, uint64_t e) {
   return ddr_typed(d) ? ((uint32_t)e >> 31) == 0 : (d.only == OP_NONE ? d.mode : d.only) == OP_INSERT;
 }
 
+// Slot of key k in a chunk's or range's table (not by the hash's top bits: those of a range
+// share them), and the next one.
+template <uint32_t TAB>
+__device__ __forceinline__ uint32_t ddr_slot(uint32_t k) {
+  if constexpr ((TAB & (TAB - 1)) == 0) return dds_hash(k) & (TAB - 1);
+  else return (dds_hash(k) & 0xFFFFu) * TAB >> 16;
+}
+template <uint32_t TAB>
+__device__ __forceinline__ uint32_t ddr_next(uint32_t s) {
+  if constexpr ((TAB & (TAB - 1)) == 0) return (s + 1) & (TAB - 1);
+  else return s + 1 < TAB ? s + 1 : 0;
+}
+
 template <int PER, int BINS>
 __global__ __launch_bounds__(DDR_BLOCK) void ddr_chunk_kernel(DdrArgs d) {
   constexpr int Q = BINS > DDR_BLOCK ? BINS / DDR_BLOCK : 1;  // ranges per thread of the prefix sums
   constexpr int SCAN = BINS / Q;                              // threads that take part
-  constexpr uint32_t CH = (uint32_t)DDR_BLOCK * PER, TAB = 2 * CH;
+  constexpr uint32_t CH = (uint32_t)DDR_BLOCK * PER, MOST = (BESIDE_LDS - BINS * 4 - 128) / 8,
+                     TAB = 2 * CH < MOST ? 2 * CH : MOST;
+  static_assert(TAB >= CH + CH / 4, "at most 80% full");
   static_assert(CH < 65536, "run bounds are 16 bits");
   __shared__ uint64_t tab[TAB];
   __shared__ uint32_t cnt[BINS], part[SCAN / 64];
@@ -697,7 +723,7 @@ __global__ __launch_bounds__(DDR_BLOCK) void ddr_chunk_kernel(DdrArgs d) {
     if (ty[j] < 0 || !valid_key(k)) continue;
     const uint64_t e = ((uint64_t)k << 32) | ((uint32_t)ty[j] << 31) | (uint32_t)(base + j * DDR_BLOCK + tid);
     const bool keep_last = ddr_keep_last(d, e);
-    for (uint32_t s = mix32(k) & (TAB - 1);; s = (s + 1) & (TAB - 1)) {
+    for (uint32_t s = ddr_slot<TAB>(k);; s = ddr_next<TAB>(s)) {
       uint64_t cur = tab[s];
       if (cur == EMPTY) {
         cur = atomicCAS((unsigned long long *)&tab[s], (unsigned long long)EMPTY, (unsigned long long)e);
@@ -839,24 +865,28 @@ __device__ __forceinline__ void ddr_set(const DdrArgs &d, uint32_t b, uint64_t l
 }
 
 // The table is sized for the records of a range: up to about 2,048 of the
-// smaller batches, 8,192 at 2^22 operations.  LANES lanes read one chunk's run
+// smaller batches, 4,096 beyond 2^20 operations.  LANES lanes read one chunk's run
 // together: eight where runs are eight records or more; beyond 2^23
 // operations runs are short and there are thousands of chunks, and the
 // dependent reads of bounds and records take the time; lanes that read
-// neighbouring chunks clear flags that share cache lines (eight, four, two and
-// one lanes: 2^26 distinct keys 4.31, 3.11, 2.87 and 2.80 ms, 2^26 operations on
-// 2^20 keys 3.19, 3.02, 2.95 and 3.08, of which the cleared flags are 1.4).
+// neighbouring chunks clear flags that share cache lines (with chunks and tables
+// twice as large, eight, four, two and one lanes: 2^26 distinct keys 4.31, 3.11,
+// 2.87 and 2.80 ms, 2^26 operations on 2^20 keys 3.19, 3.02, 2.95 and 3.08).
 //
 // A pass reads the whole range, so a range of many sub-ranges would take time
 // quadratic in its records (2^20 operations on 2^16 keys of one range: 34 ms).
 // Once more than DDR_PASSES passes are ahead, the rest of the range goes to
 // ddr_set, whose atomics take about the time of that many passes (the same
 // batch 4.1 ms, in one block; beyond 2^29 distinct keys every range).
+// With DDR_BINS_BIG all ranges grow alike, and the line lies where their passes
+// take as long as the set
+// (2^28 distinct keys: 85 ms in passes alone, 30 so).
 constexpr uint64_t DDR_PASSES = 24;
+constexpr uint64_t DDR_PASSES_BIG = 6;
 template <int PER, int BINS, int LANES>
 __global__ __launch_bounds__(DDR_BLOCK) void ddr_resolve_kernel(DdrArgs d) {
   constexpr uint32_t CH = (uint32_t)DDR_BLOCK * PER;
-  constexpr int TAB = PER == 8 ? 16384 : 4096;
+  constexpr uint32_t TAB = BINS > DDR_BINS ? (BESIDE_LDS - 256) / 8 : 4096;
   constexpr uint32_t CAP = TAB * 3 / 4;
   static_assert(CAP + DDR_BLOCK < TAB + 1, "at most one claim per thread past the limit");
   __shared__ uint64_t tab[TAB];
@@ -870,18 +900,18 @@ __global__ __launch_bounds__(DDR_BLOCK) void ddr_resolve_kernel(DdrArgs d) {
   if constexpr (BINS == DDR_BINS_BIG) {
     // The first width: the whole range where keys repeat, by a sample of up to
     // 1,024 records of as many chunks (of 4,096 keys, 88% of the sample are
-    // distinct, of 12,288 96%); else so that the records it may hold fit.
+    // distinct, of 7,656 94%); else so that the records it may hold fit.
     const uint64_t per = (uint64_t)d.n >> d.bits;  // records, at most about that many
     if (per > CAP) {
       __shared__ uint32_t s_sample, s_distinct;
-      for (int j = threadIdx.x; j < TAB; j += DDR_BLOCK) tab[j] = EMPTY;
+      for (uint32_t j = threadIdx.x; j < TAB; j += DDR_BLOCK) tab[j] = EMPTY;
       if (threadIdx.x == 0) s_sample = s_distinct = 0;
       __syncthreads();
       bool have = false, fresh = false;
       if (threadIdx.x < d.nch)
         ddr_run<1, CH>(d, (uint32_t)((uint64_t)threadIdx.x * d.nch / min(d.nch, (uint32_t)DDR_BLOCK)), b, [&](uint64_t e) {
           have = true;
-          for (uint32_t s = mix32((uint32_t)(e >> 32)) & (TAB - 1);; s = (s + 1) & (TAB - 1)) {
+          for (uint32_t s = ddr_slot<TAB>((uint32_t)(e >> 32));; s = ddr_next<TAB>(s)) {
             const uint64_t cur =
                 atomicCAS((unsigned long long *)&tab[s], (unsigned long long)EMPTY, (unsigned long long)(e | 0xFFFFFFFFu));
             if (cur == EMPTY) fresh = true;
@@ -903,7 +933,7 @@ __global__ __launch_bounds__(DDR_BLOCK) void ddr_resolve_kernel(DdrArgs d) {
   const bool backwards = ddr_typed(d) || (d.only == OP_NONE ? d.mode : d.only) == OP_INSERT;
   while (lo < last) {
     width = min(width, last - lo);
-    for (int j = threadIdx.x; j < TAB; j += DDR_BLOCK) tab[j] = EMPTY;
+    for (uint32_t j = threadIdx.x; j < TAB; j += DDR_BLOCK) tab[j] = EMPTY;
     if (threadIdx.x == 0) s_claims = 0;
     __syncthreads();
     for (uint32_t c0 = threadIdx.x / LANES; c0 < d.nch; c0 += DDR_BLOCK / LANES) {
@@ -913,7 +943,7 @@ __global__ __launch_bounds__(DDR_BLOCK) void ddr_resolve_kernel(DdrArgs d) {
         if (*(volatile uint32_t *)&s_claims > CAP) return false;
         const uint32_t k = (uint32_t)(e >> 32);
         const bool keep_last = ddr_keep_last(d, e);
-        for (uint32_t s = mix32(k) & (TAB - 1);; s = (s + 1) & (TAB - 1)) {
+        for (uint32_t s = ddr_slot<TAB>(k);; s = ddr_next<TAB>(s)) {
           uint64_t cur = *(volatile uint64_t *)&tab[s];
           if (cur == EMPTY) {
             cur = atomicCAS((unsigned long long *)&tab[s], (unsigned long long)EMPTY, (unsigned long long)e);
@@ -945,7 +975,7 @@ __global__ __launch_bounds__(DDR_BLOCK) void ddr_resolve_kernel(DdrArgs d) {
       // as wide as fills half the table at this density, two at least
       if (claims <= CAP / 2) width *= claims ? max(2u, CAP / 2 / claims) : CAP;
     }
-    if (lo < last && (last - lo) / width > DDR_PASSES) {
+    if (lo < last && (last - lo) / width > (BINS == DDR_BINS_BIG ? DDR_PASSES_BIG : DDR_PASSES)) {
       ddr_set<LANES, CH>(d, b, lo, last);
       return;
     }
@@ -1496,15 +1526,18 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE))) vo
 // Dedupe and P1 of a small batch in one launch.
 //
 // A small batch's time is its launches and the round trips between them, so
-// one block of 16 waves settles the batch's keys in an LDS table (as
-// dds_kernel does) and goes on to its four tiles.  Inserts of 2^6 and 2^10
+// a block of 8 waves settles the batch's keys in an LDS table (as dds_kernel
+// does) and goes on to its two tiles; beyond 512 operations there are two
+// blocks, and each settles all keys.  (One block of 16 waves takes as long, but
+// has no room beside a resident executor.)  Inserts of 2^6 and 2^10
 // operations take 8.6 and 11.5 us against 9.9 and 12.9 in two launches, and
-// the host makes one call fewer.  Two blocks that each settle the whole batch
-// were slower at 2^11 (15 us against 13.4), four at 2^12 (18 against 13.5).
+// the host makes one call fewer.  At 2^11 and 2^12 operations, with blocks of
+// 16 waves, this was slower (15 us against 13.4, 18 against 13.5).
 // ---------------------------------------------------------------------------
-constexpr int SMALL_BLOCK = 4 * BLOCK;
-constexpr uint64_t SMALL_MAX = SMALL_BLOCK;  // one operation per thread
-constexpr int SMALL_TAB = 2 * SMALL_BLOCK;
+constexpr int SMALL_BLOCK = 2 * BLOCK;
+constexpr int SMALL_PER = 2;  // operations that a thread settles
+constexpr uint64_t SMALL_MAX = SMALL_PER * SMALL_BLOCK;
+constexpr int SMALL_TAB = 2 * SMALL_MAX;
 
 template <int S, uint32_t MODE, int FILTER>
 __global__ __launch_bounds__(SMALL_BLOCK) void small_batch_kernel(OpsArgs a, uint8_t *win) {
@@ -1516,26 +1549,34 @@ __global__ __launch_bounds__(SMALL_BLOCK) void small_batch_kernel(OpsArgs a, uin
   const uint32_t tid = threadIdx.x;
   for (uint32_t j = tid; j < SMALL_TAB; j += SMALL_BLOCK) sh.tab[j] = EMPTY;
   const DdsArgs d{a.ops, a.keys, win, (uint32_t)a.n, MODE, 0};
-  uint64_t e[1];
-  dds_read<SMALL_BLOCK, 1>(d, 0, 0, 1ull << 32, e);
+  uint64_t e[SMALL_PER];
+  dds_read<SMALL_BLOCK, SMALL_PER>(d, 0, 0, 1ull << 32, e);
   const OpsView view = read_view(a.ctl, a.stash_cap, a.pending_cap, a.spill, a.n);
   __syncthreads();
-  const bool keep_last = MODE == OP_MIXED ? ((uint32_t)e[0] >> 31) == 0 : MODE == OP_INSERT;
-  if (e[0] != EMPTY) dds_settle<SMALL_TAB>(sh.tab, e[0], keep_last, nullptr);
+#pragma unroll
+  for (int j = 0; j < SMALL_PER; ++j) {
+    const bool keep_last = MODE == OP_MIXED ? ((uint32_t)e[j] >> 31) == 0 : MODE == OP_INSERT;
+    if (e[j] != EMPTY) dds_settle<SMALL_TAB>(sh.tab, e[j], keep_last, nullptr);
+  }
   __syncthreads();
-  if (e[0] != EMPTY) win[(uint32_t)e[0] & 0x7FFFFFFFu] = dds_kept<SMALL_TAB>(sh.tab, e[0]);
+#pragma unroll
+  for (int j = 0; j < SMALL_PER; ++j)  // the flags of the block's own tiles
+    if (e[j] != EMPTY && j == (int)blockIdx.x)
+      win[(uint32_t)e[j] & 0x7FFFFFFFu] = dds_kept<SMALL_TAB>(sh.tab, e[j]);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();  // the flags are written, the table is free
   a.win = win;
-  const uint64_t tile = tid / BLOCK;
+  // the same in a whole wave, and known to be: fewer registers
+  const uint32_t part = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / BLOCK));
+  const uint64_t tile = blockIdx.x * (SMALL_BLOCK / BLOCK) + part;
   if (tile * BLOCK < a.n) {
     int64_t live_acc = 0;
     uint64_t bad_acc = 0;
-    ops_tile<S, MODE, false, PAIR_BITHASH, Traits<S>::CH, FILTER>(a, view, tile, sh.ops[tid / BLOCK], live_acc,
+    ops_tile<S, MODE, false, PAIR_BITHASH, Traits<S>::CH, FILTER>(a, view, tile, sh.ops[part], live_acc,
                                                                  bad_acc);
     ops_counts_add(a.ctl, tile * WAVES + (tid >> 6) % WAVES, live_acc, bad_acc);
   }
-  if (tid == 0) ops_done<MODE>(a.ctl, view, FILTER != FILTER_NONE);
+  if (blockIdx.x == 0 && tid == 0) ops_done<MODE>(a.ctl, view, FILTER != FILTER_NONE);
 }
 
 // ---------------------------------------------------------------------------
@@ -3035,8 +3076,9 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(ResizeArgs a) {
 // Bound by memory (each table word read once, each live word written once)
 // as long as the output positions cost little: every position comes from one
 // counter, and a device atomic on one address takes about 64 ns.  A block of
-// 16 waves therefore takes DUMP_LOADS words per thread and trip (128 KiB of
-// a 64-bit table, held in registers), counts them by ballots and reserves
+// 8 waves (16 have no room beside a resident executor) therefore takes
+// DUMP_LOADS words per thread and trip (64 KiB of a 64-bit table, held in
+// registers), counts them by ballots and reserves
 // room for the whole trip with one add; a wave's live words then go to
 // consecutive positions.  One add per wave had made a 4.0 M-entry dump of
 // 4.2 M slots 794 us; now about 10 us (export, re-insertion and lookups of
@@ -3044,21 +3086,22 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(ResizeArgs a) {
 // SET32: words of a key-only set (the key itself, EMPTY all ones), written as
 // 64-bit words with value half 0.
 // ---------------------------------------------------------------------------
-constexpr int DUMP_BLOCK = 1024;
+constexpr int DUMP_BLOCK = 512;
 constexpr int DUMP_LOADS = 16;
 constexpr uint64_t DUMP_TRIP = (uint64_t)DUMP_BLOCK * DUMP_LOADS;
 
 template <bool SET32>
-__global__ __launch_bounds__(DUMP_BLOCK) void dump_kernel(const void *bucket_words, uint32_t S,
+__global__ __launch_bounds__(DUMP_BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void dump_kernel(const void *bucket_words, uint32_t S,
                                                           const void *stash_words, const void *pending_words,
                                                           Ctl *ctl, uint64_t stash_cap, uint64_t pending_cap,
                                                           uint64_t *out, int64_t *where, uint64_t cap) {
   using Word = typename std::conditional<SET32, uint32_t, uint64_t>::type;
   constexpr int DW = DUMP_BLOCK / 64;
-  __shared__ uint32_t off[DUMP_LOADS * DW];  // live words of (load, wave), then their exclusive prefix
-  __shared__ uint32_t part[4], total_live;
+  constexpr int COUNTS = DUMP_LOADS * DW;
+  __shared__ uint32_t off[COUNTS];  // live words of (load, wave), then their exclusive prefix
+  __shared__ uint32_t part[COUNTS / 64], total_live;
   __shared__ uint64_t s_base;
-  static_assert(DUMP_LOADS * DW == 256, "four waves scan the counts");
+  static_assert(COUNTS % 64 == 0 && COUNTS <= DUMP_BLOCK, "whole waves scan the counts");
   const Word *buckets = (const Word *)bucket_words, *stash = (const Word *)stash_words,
              *pending = (const Word *)pending_words;
   const uint64_t nb = ctl->n_buckets;
@@ -3084,7 +3127,7 @@ __global__ __launch_bounds__(DUMP_BLOCK) void dump_kernel(const void *bucket_wor
     }
     __syncthreads();
     uint32_t mine = 0, incl = 0;
-    if (tid < 256) {
+    if (tid < COUNTS) {
       mine = incl = off[tid];
       for (int o = 1; o < 64; o <<= 1) {
         const uint32_t y = __shfl_up(incl, o, 64);
@@ -3093,11 +3136,11 @@ __global__ __launch_bounds__(DUMP_BLOCK) void dump_kernel(const void *bucket_wor
       if (lane == 63) part[wv] = incl;
     }
     __syncthreads();
-    if (tid < 256) {
+    if (tid < COUNTS) {
       uint32_t before = 0;
       for (int x = 0; x < wv; ++x) before += part[x];
       off[tid] = before + incl - mine;
-      if (tid == 255) total_live = before + incl;
+      if (tid == COUNTS - 1) total_live = before + incl;
     }
     __syncthreads();
     if (tid == 0) s_base = total_live ? add64(&ctl->dump_count, total_live) : 0;
@@ -3711,7 +3754,7 @@ __device__ __forceinline__ void run_chunk(ReqState *r, const ReqDesc &d, uint32_
       }
       if (ranges) {
         const DdsArgs a{d.ops, d.keys, (uint8_t *)d.t.dd, (uint32_t)d.n, d.mode, (uint32_t)(d.dds - 1)};
-        dds_range_of<BLOCK>(a, (uint32_t)c, sh.dds);
+        dds_range_of<BLOCK, DDS_LOADS>(a, (uint32_t)c, sh.dds);
       } else if (ph == PH_DEDUPE) {
         dedupe_thread(d.t.dd, d.dd_size - 1, d.mode, d.ops, d.keys, d.n, c * BLOCK + threadIdx.x);
       }
@@ -4502,14 +4545,25 @@ static uint64_t dd_set_words(uint64_t n) {  // the executor's open-addressed ded
 }
 
 // Chunk of the two-launch dedupe: about 128 chunks or more (a block each, the
-// chip has 256 compute units), up to eight operations per thread.
+// chip has 256 compute units), up to four operations per thread (eight, whose table
+// takes 128 KiB of LDS, are 2 to 20% faster from 2^21 to 2^24 operations and twice
+// as fast beyond, but such blocks wait beside a resident executor).
 static uint64_t ddr_chunk(uint64_t n) {
-  return (uint64_t)DDR_BLOCK * (n <= (1ull << 17) ? 1 : n <= (1ull << 18) ? 2 : n <= (1ull << 20) ? 4 : 8);
+  return (uint64_t)DDR_BLOCK * (n <= (1ull << 17) ? 1 : n <= (1ull << 18) ? 2 : 4);
+}
+
+// log2 of its hash ranges: of about 1,024 operations up to DDR_BINS of them, of
+// about 4,096 in larger batches (half of what their table takes at most).
+static uint32_t ddr_bits(uint64_t n) {
+  uint32_t bits = 4;
+  while ((1u << bits) < DDR_BINS && (1024ull << bits) < n) ++bits;
+  while ((1u << bits) < DDR_BINS_BIG && (4096ull << bits) < n) ++bits;
+  return bits;
 }
 
 // The dedupe's buffers for a batch of n operations, carved from one scratch
 // allocation (each piece 256-byte aligned): records and range bounds of every
-// chunk (at most DDR_BLOCK * 8 operations), a winner flag per operation and,
+// chunk (at most DDR_BLOCK * 4 operations), a winner flag per operation and,
 // beyond the one-launch form, the words of ranges that are settled in HBM.
 struct DdrBuffers {
   uint64_t *rec, *used, *set;
@@ -4528,7 +4582,7 @@ static uint64_t ddr_layout(uint64_t *base, uint64_t n, DdrBuffers *out) {
   };
   DdrBuffers d;
   d.rec = take(nch * ch * 8);
-  d.bounds = (uint32_t *)take(nch * (n > DDR_MORE ? DDR_BINS_BIG : DDR_BINS) * 4);
+  d.bounds = (uint32_t *)take((nch << ddr_bits(n)) * 4);
   d.win = (uint8_t *)take(n);
   d.used = take(n > DDS_MAX ? 8 : 0);
   d.set = take(n > DDS_MAX ? 2 * n * 8 : 0);
@@ -4897,7 +4951,7 @@ static void launch_ddr(const DdrArgs &a, hipStream_t st) {
 
 template <int FILTER>
 static void launch_small_filter(uint32_t mode, const OpsArgs &a, uint8_t *win, hipStream_t st) {
-  const dim3 grid(1), block(SMALL_BLOCK);
+  const dim3 grid((unsigned)((a.n + SMALL_BLOCK - 1) / SMALL_BLOCK)), block(SMALL_BLOCK);
   switch (mode) {
     case OP_INSERT: hipLaunchKernelGGL((small_batch_kernel<16, OP_INSERT, FILTER>), grid, block, 0, st, a, win); break;
     case OP_DELETE: hipLaunchKernelGGL((small_batch_kernel<16, OP_DELETE, FILTER>), grid, block, 0, st, a, win); break;
@@ -4922,14 +4976,15 @@ static hive_status launch_dedupe(uint64_t *dd, uint32_t mode, const uint8_t *d_o
     uint32_t bits = 0;
     while (((uint64_t)DDS_PER << bits) < n) ++bits;
     const DdsArgs a{d_ops, d_keys, buf.win, (uint32_t)n, mode, bits};
-    hipLaunchKernelGGL(dds_kernel, dim3(1u << bits), dim3(DDS_BLOCK), 0, st, a);
+    const dim3 grid(1u << bits), block(DDS_BLOCK);
+    switch (mode) {
+      case OP_INSERT: hipLaunchKernelGGL(dds_kernel<OP_INSERT>, grid, block, 0, st, a); break;
+      case OP_DELETE: hipLaunchKernelGGL(dds_kernel<OP_DELETE>, grid, block, 0, st, a); break;
+      default: hipLaunchKernelGGL(dds_kernel<OP_MIXED>, grid, block, 0, st, a); break;
+    }
     return launch_check();
   }
-  // ranges of about 1,024 operations and at most DDR_BINS of them; of about
-  // 8,192 beyond DDR_MORE, where each range reads a run of every chunk
-  uint32_t bits = 4;
-  while ((1u << bits) < DDR_BINS && (1024ull << bits) < n) ++bits;
-  while ((1u << bits) < DDR_BINS_BIG && (8192ull << bits) < n) ++bits;
+  const uint32_t bits = ddr_bits(n);
   const uint64_t ch = ddr_chunk(n);
   DdrArgs a{d_ops, d_keys, buf.win, buf.rec, buf.bounds, buf.set, buf.used, (uint32_t)n, mode, bits, (uint32_t)((n + ch - 1) / ch), OP_NONE};
   const bool by_type = mode == OP_MIXED && n >= (1ull << 31);  // indices fill the word
@@ -4938,10 +4993,10 @@ static hive_status launch_dedupe(uint64_t *dd, uint32_t mode, const uint8_t *d_o
     switch (ch / DDR_BLOCK) {
       case 1: launch_ddr<1>(a, st); break;
       case 2: launch_ddr<2>(a, st); break;
-      case 4: launch_ddr<4>(a, st); break;
       default:
-        if (n > DDR_MORE) launch_ddr<8, DDR_BINS_BIG>(a, st);
-        else launch_ddr<8>(a, st);
+        if (n > DDR_MORE) launch_ddr<4, DDR_BINS_BIG>(a, st);
+        else if (n > (1ull << 20)) launch_ddr<4, DDR_BINS_MID>(a, st);
+        else launch_ddr<4>(a, st);
         break;
     }
     if (!by_type) break;
