@@ -4600,11 +4600,13 @@ static uint64_t dd_words_for(uint64_t n) {
 // pending list.
 static uint64_t drain_words(const hive_table *h) { return stash_slots_for(h->stash_cap) + h->pending_cap; }
 
-// Added to a worklist that holds a batch's entries and a drain: the probe
-// launch's and the drain's per-segment fills are each bounded by their own
-// rounding of whole tiles per segment, which can exceed the rounding of the
-// sum by up to 4 x NSHARD tiles in all.
-constexpr uint64_t WL_SLACK = 4ull * NSHARD * BLOCK;
+// Entries of a worklist that holds those of a batch of n operations and of a
+// drain of d words: the fills of a segment by the two are each rounded up to
+// whole tiles of their own.  (A table of 64 buckets that may grow to 4,096 takes
+// 0.25 MiB for both; with four tiles per segment added to the sum, 0.6.)
+static uint64_t wl_batch_and_drain(uint64_t n, uint64_t d) {
+  return (wl_seg_cap_for(n) + wl_seg_cap_for(d)) * NSHARD;
+}
 
 static hive_status ensure_scratch(hive_table *h, uint64_t n, uint64_t n_dd, hipStream_t st) {
   if (n > h->wl_cap) {
@@ -5067,7 +5069,7 @@ static hive_status run_batch(hive_t h, uint32_t mode, const uint8_t *d_ops, cons
   // the growth before the batch, too) joins the worklist and one eviction
   // launch places both.  The worklist then holds the batch's entries and a
   // full drain.
-  const uint64_t wl_post = n + drain_words(h) + WL_SLACK;
+  const uint64_t wl_post = wl_batch_and_drain(n, drain_words(h));
   const bool rules = linear && (h->cfg.post_policy || h->cfg.pre_expand);
   // (a table without the post-batch rule does not grow its worklist for this
   // alone: a call that needed no allocation before needs none)
@@ -5297,7 +5299,7 @@ hive_status hive_create(const hive_config *cfg_in, uint64_t initial_buckets, voi
   // rules, together with the drain (see run_batch)
   // (of at least min_wl operations)
   const uint64_t batch_wl = cfg.addressing == HIVE_LINEAR && (cfg.post_policy || cfg.pre_expand)
-                                ? std::max(cfg.max_batch, min_wl) + min_wl + WL_SLACK
+                                ? wl_batch_and_drain(std::max(cfg.max_batch, min_wl), min_wl)
                                 : cfg.max_batch;
   if ((s = ensure_scratch(h, std::max<uint64_t>(batch_wl, min_wl), cfg.max_batch, st)) != HIVE_OK) {
     free_table(h);

@@ -100,3 +100,24 @@ def test_a_large_contraction_keeps_loads_in_flight(H):  # noqa: F811
     print(f"split {up:.3f} ms, merge {down:.3f} ms")
     assert down <= 3.5 * up
     t.close()
+
+
+def test_growth_rules_reserve_little_worklist(H):  # noqa: F811
+    """A small table with a rule reserves at most 160 KiB more than one without
+    (a drain and a tile per segment), and its largest batches still fit."""
+    cfg = dict(addressing=H.HIVE_LINEAR, max_buckets=4096, max_batch=1 << 14)
+    plain = H.Table(64, **cfg)
+    ruled = H.Table(64, pre_expand=1, **cfg)
+    a, b = plain.stats()["bytes_reserved"], ruled.stats()["bytes_reserved"]
+    print(f"bytes reserved: {a} without a rule, {b} with one")
+    plain.close()
+    case("batches at the worklist's limit")
+    o = oracle.O1()
+    ks = wl.KeyStream(77)
+    for i in range(3):
+        kh = ks.range(i << 14, (i + 1) << 14)
+        ruled.insert(dev(kh), dev(wl.values_for(kh)))
+        o.insert(kh, wl.values_for(kh))
+    assert np.array_equal(ruled.dump(), o.dump())
+    ruled.close()
+    assert b - a <= 160 * 1024
