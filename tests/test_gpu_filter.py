@@ -252,3 +252,41 @@ def test_4x16_asked_for_by_name(H, kinds):
     from test_gpu_probe_variants import run_all_kinds
     case(f"probe variants by name {kinds}")
     run_all_kinds(H, H.probe_tuning(*kinds), 0)
+
+
+@pytest.mark.parametrize("bits", [8, 4, 2, 1])
+def test_filters_of_fewer_bits_per_bucket(H, bits):  # noqa: F811
+    """Large tables have fewer filter bits a bucket.  Keys that crowd into 3,000
+    first candidates, about 12 each, so that many sit elsewhere: lookups of them
+    and of absent keys of the same buckets, before and after deletes."""
+    import torch
+    nb = {8: 4_000_000, 4: 5_400_000, 2: 10_600_000, 1: 21_100_000}[bits]
+    got = []
+    out = torch.empty(1 << 24, dtype=torch.uint32, device="cuda")
+    lo = 1
+    while lo < 12 * nb:  # 12 candidates for every bucket
+        keys = torch.arange(lo, lo + (1 << 24), dtype=torch.int64, device="cuda").to(torch.uint32)
+        H.hive_hash_buckets("bithash1", keys, nb, out)
+        got.append(keys.cpu().numpy()[out.cpu().numpy() < 3000])
+        lo += 1 << 24
+    keys = np.random.default_rng(bits).permutation(np.concatenate(got))
+    absent, present = keys[:keys.size // 8], keys[keys.size // 8:]
+    gone = present[: present.size // 3]
+    case(f"{nb} buckets, {present.size} keys in 3,000 of them")
+    t = H.Table(nb, max_batch=1 << 17)
+    o = oracle.O1()
+    for part in np.array_split(present, 3):
+        t.insert(dev(part), dev(wl.values_for(part)))
+        o.insert(part, wl.values_for(part))
+    elsewhere = t.placement()[1]
+    assert elsewhere > present.size // 20, f"only {elsewhere} of {present.size} in second candidates"
+    for step in range(2):
+        v, f = t.lookup(dev(keys))
+        ov, of = o.lookup(keys)
+        assert np.array_equal(host(f), of) and np.array_equal(host(v)[of == 1], ov[of == 1])
+        assert of.sum() == (present.size if step == 0 else present.size - gone.size)
+        if step == 0:
+            assert host(t.delete(dev(gone))).sum() == gone.size
+            o.delete(gone)
+    assert absent.size > 1000
+    t.close()
