@@ -1724,7 +1724,9 @@ __device__ __forceinline__ Mask interleave_slots(const uint64_t *m) {
 // whose request rate bound the eviction launches: 112 -> 91 us in the batches
 // of a growing table, 270 -> 213 us after a 2^26-key build to 95%.  (Atomic
 // loads are at most 8 bytes wide: sixteen scattered lines of requests.)  A
-// view that is older all the same costs a failed CAS and a reload, no more.
+// view that is older all the same costs a failed CAS and the round it was made in:
+// of its chain's bounded rounds, so that about a tenth more entries end in the
+// stash at 97% load (712 for 648 of 2^26 keys).
 // The block ends in its own wait for the loads, so the registers are complete
 // when it returns.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -3869,7 +3871,7 @@ __global__ void wall_clock_kernel(uint64_t *out) { *out = wall_clock64(); }
 __device__ __forceinline__ void invalidate_l1() { asm volatile("buffer_inv sc0" ::: "memory"); }
 
 // Occupancy target: 3 waves per SIMD (at most 168 VGPRs).  The 16-slot build
-// spills three registers of the control loop, none inside a phase; a cap of
+// spills 39 registers, mostly of the control loop; a cap of
 // 128 (4 waves) spills inside the phases and runs slower.
 template <int S>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void drain_worker_kernel(DrainQueue *q) {
@@ -4009,8 +4011,6 @@ struct SetArgs {
   Ctl *ctl;
   uint64_t *wl;  // eviction worklist (keys widened to 64 bits), NSHARD segments
   uint64_t wl_seg_cap;
-  const uint64_t *dd;  // dedupe set, or null
-  uint64_t dd_mask;
   const uint8_t *ops;
   const uint32_t *keys;
   uint8_t *flags_out;
@@ -4100,10 +4100,7 @@ __global__ __launch_bounds__(BLOCK) void set_ops_kernel(SetArgs a) {
     const bool valid = active && op <= OP_LOOKUP && valid_key(k);
     bool work = valid;
     if (work && op != OP_LOOKUP) {
-      if (a.win)
-        work = __builtin_nontemporal_load(&a.win[i]) != 0;
-      else if (a.dd)
-        work = dedupe_winner(a.dd, a.dd_mask, k, (uint32_t)i);
+      if (a.win) work = __builtin_nontemporal_load(&a.win[i]) != 0;
     }
     uint32_t c1 = 0, c2 = 0;
     if (work) {
@@ -4761,14 +4758,9 @@ static void launch_evict(hive_table *h, const Spill &spill, uint64_t max_items, 
   }
   switch (h->S) {
     case 16:
-      if (!refill && h->cfg.hash_pair != PAIR_TRIPLE) {
-        if (h->cfg.hash_pair == PAIR_CRC)
-          hipLaunchKernelGGL((evict_kernel<16, PAIR_CRC>), grid, dim3(BLOCK), 0, st, e);
-        else if (h->cfg.hash_pair == PAIR_MURMUR)
-          hipLaunchKernelGGL((evict_kernel<16, PAIR_MURMUR>), grid, dim3(BLOCK), 0, st, e);
-        else
-          hipLaunchKernelGGL(evict_kernel<16>, grid, dim3(BLOCK), 0, st, e);
-      } else if (h->cfg.hash_pair == PAIR_CRC)
+      if (!refill)  // after a resize alone: LINEAR tables, whose pair is BitHash
+        hipLaunchKernelGGL(evict_kernel<16>, grid, dim3(BLOCK), 0, st, e);
+      else if (h->cfg.hash_pair == PAIR_CRC)
         hipLaunchKernelGGL(evict_lanes_kernel<PAIR_CRC>, dim3(evict_lanes_grid<PAIR_CRC>(max_items)), dim3(BLOCK),
                            0, st, e);
       else if (h->cfg.hash_pair == PAIR_MURMUR)
@@ -5137,7 +5129,7 @@ static hive_status run_batch(hive_t h, uint32_t mode, const uint8_t *d_ops, cons
   }
   if (h->entry_bytes == 4) {
     SetArgs sa{(uint32_t *)h->d_buckets, a.spill, h->d_hint, (uint32_t *)h->d_stash, (uint32_t *)h->d_pending, h->d_ctl,
-               h->d_wl, h->wl_seg_cap, a.dd, a.dd_mask, d_ops, d_keys, d_flags_out, n, h->stash_cap, h->pending_cap,
+               h->d_wl, h->wl_seg_cap, d_ops, d_keys, d_flags_out, n, h->stash_cap, h->pending_cap,
                h->cfg.max_evictions, a.win};
     phase_mark(h, HIVE_PHASE_PROBE, st);
     const uint64_t cap = h->cfg.probe_grid ? h->cfg.probe_grid : OPS_GRID;
