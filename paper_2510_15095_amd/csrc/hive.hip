@@ -249,8 +249,10 @@ __global__ __launch_bounds__(64) void finish_kernel(Ctl *c, uint64_t inserts) {
 // tables with an eviction bound under FIRST_MIN_CHAIN, and those whose stash
 // holds less than the default 1% of the slots (a stash sized for two-choice
 // placement may not hold the entries above).
-// shift: 8 bits a bucket while the filter stays within FILTER_BYTES, so that
-// it is served by the L2s while bucket lines stream through them; at 95% load
+// shift: 8 bits a bucket while the filter stays within FILTER_BYTES, beyond which
+// fewer bits in fewer lines are ahead (2^24 lookups without hits at 53 / 90% load:
+// 458 / 615 us with 8 bits in 5.20 M buckets, 441 / 591 with 4 in 5.28 M; its lines
+// mostly miss the L2s, which bucket lines stream through); at 95% load
 // a missing key finds its bit set with probability 0.74 / 0.59 / 0.41 / 0.25
 // for 1 / 2 / 4 / 8 bits.
 // LINEAR tables have none: their unsplit buckets are full, so that most bits
